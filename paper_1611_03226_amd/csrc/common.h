@@ -134,7 +134,9 @@ struct DpdArgs {
   float2 *y;
   const int64_t *y_idx;   // device [read, write] or nullptr
   int64_t y_mask;
-  const float2 *h;        // [B_max][M]
+  const float2 *h;        // [B_max][M] (head pass)
+  float2 *ht;             // the same, tap-major: coef_rows_bytes(M), read by the bodies
+  int32_t fill_ht;        // the head pass writes ht from h
   const float2 *hist;     // [B_max][M-1] or nullptr
   const int32_t *B;       // [n_firings] branch sets, or nullptr
   int32_t B_const;        // branch count of every firing when B is nullptr
@@ -148,7 +150,7 @@ struct DpdArgs {
   int32_t tile;           // outputs per workgroup (tiled kernel)
   int32_t tiles_per_firing;
   const int32_t *order;   // processing order, pairs (firing, branch set) grouped by Horner length, or nullptr
-  float2 *corr;           // [n_firings][M-1] head corrections (tiled kernels)
+  float2 *corr;           // [n_firings][M-1] head corrections, or nullptr: none (no firing has a history)
   // With grp set (one segment), the head pass derives each firing's history
   // sources from the scan's group table and writes the prev/off tables itself.
   const int64_t *grp;     // [groups][B_max][2] from k_scan, or nullptr
@@ -313,7 +315,10 @@ hipError_t launch_dpd_network(const DpdNetArgs &a, hipStream_t s, const KTiming 
 // into B [S*nf] and channel offsets into off [B_max][S*nf], from ctrl [S][nf].
 hipError_t launch_mask_tables(const int32_t *ctrl, int32_t *B, int64_t *off, const DpdNetArgs &a, hipStream_t s);
 
-bool dpd_tiled_shape(int M);
+// Bytes of the tap-major coefficients of an M-tap actor, and the kernel that
+// writes them from h [B_max][M].
+size_t coef_rows_bytes(int M);
+hipError_t launch_coef_rows(const float2 *h, float2 *ht, int B_max, int M, hipStream_t s);
 hipError_t launch_dpd_heads(const DpdArgs &a, hipStream_t s);
 // Body form for M = 16 from the environment: the VALU form, or the
 // matrix-core form with DFHIP_BODY=mx (measured slower on MI355X: the
@@ -322,7 +327,6 @@ hipError_t launch_dpd_heads(const DpdArgs &a, hipStream_t s);
 bool dpd_body_mx_env();
 hipError_t launch_dpd_body(const DpdArgs &a, hipStream_t s, int tile, int outputs_per_thread,
                            const KTiming *timing = nullptr);
-hipError_t launch_dpd_commit(const DpdCommitArgs &a, hipStream_t s);
 // Add delta to one counter (word 0 or 1 of a channel slot) and check the
 // channel's ring invariant.
 hipError_t launch_advance(int64_t *idx, int64_t delta, int32_t *err, hipStream_t s);

@@ -40,76 +40,138 @@ __device__ __forceinline__ float2 ldc_masked(cfloat2p p, int i, uint32_t keep) {
                      __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, v.y) & keep));
 }
 
-// LDS slot of window sample i: one pad slot per 8 samples, so the K-strided
-// register-window reads of a wavefront fall on distinct banks.
-__host__ __device__ constexpr int lds_slot(int i) { return i + (i >> 3); }
-__host__ __device__ constexpr int lds_window(int n) { return lds_slot(n) + 1; }
+// LDS slot of window sample i for K outputs per thread: one pad slot per K
+// samples, so a wavefront's K-strided 8-byte window reads start 2K + 2 words
+// apart and each half wavefront covers the 64 banks once (K = 4 with one pad
+// per 8 samples put two lanes on a bank).  Samples K apart are K + 1 slots
+// apart, so a thread's reads of sample K * thread + c are one base and an
+// offset known at compile time.
+template <int K>
+__host__ __device__ constexpr int lds_slot(int i) { return (int)((unsigned)i + (unsigned)i / K); }
+template <int K>
+__host__ __device__ constexpr int lds_window(int n) { return lds_slot<K>(n) + 1; }
 
+// Coefficients as the bodies read them: [taps][kCoefRow] complex, tap-major,
+// with a fixed row length, so that the branches of one tap are consecutive
+// (a few wide scalar loads instead of one per branch) at offsets known at
+// compile time.
+constexpr int kCoefRow = kMaxBranches;
 
 // Taps of K consecutive outputs q0..q0+K-1.  Tap m of output q0+k reads
 // window sample k+M-1-m, so iterating the taps in order slides a window of
 // K samples (one new LDS read per tap; the shift is a register rename).
 // Reads stay inside the window buffer (index < tile+M-1); in a partial tile,
 // slots past the staged samples only feed outputs that are not stored.
-// hg: the firing's coefficients [B][M] (uniform address: scalar loads).
+// ht: the firing's coefficients, tap-major (uniform address: scalar loads).
 // MASKED: set is the firing's branch set (B = its Horner length) and the
 // coefficients of branches outside it read as zero; without MASKED the set
 // is the prefix 0..B-1 and the coefficients are used as loaded.
 // Software pipeline of depth one: tap m+1's coefficients and sample are
-// loaded before tap m's arithmetic; a compiler fence after each tap keeps
-// later loads from being hoisted (which would keep every tap's
-// coefficients live at once and spill).
-template <int M, int K, int B, bool MASKED>
-__device__ __forceinline__ void horner_taps(cfloat2p hg, uint32_t set, const float2 *sx, int q0, float (&ar)[K],
-                                            float (&ai)[K]) {
-  auto coef = [&](int b, int i) {
-    if constexpr (MASKED) return ldc_masked(hg, i, 0u - ((set >> b) & 1u));
-    else return ldc(hg, i);
-  };
-  float2 wv[K];
-  float pv[K];
+// loaded before tap m's arithmetic (tap_fence).
+// MT: the tap count when it is compiled in (4, 8, 16), else 0 and the taps
+// are a loop over Mr, K taps a turn (the window's register rename repeats
+// after K taps), and the remaining ones under uniform branches.
+template <int K, int B, bool MASKED>
+__device__ __forceinline__ void load_coefs(cfloat2p row, uint32_t set, float2 (&hc)[B]) {
+#pragma unroll
+  for (int b = 0; b < B; ++b) {
+    if constexpr (MASKED) hc[b] = ldc_masked(row, b, 0u - ((set >> b) & 1u));
+    else hc[b] = ldc(row, b);
+  }
+}
+
+// One tap for the K outputs: y[k] += x P(p).
+template <int K, int B>
+__device__ __forceinline__ void horner_tap(const float2 (&hc)[B], const float2 (&wv)[K], const float (&pv)[K],
+                                           float (&ar)[K], float (&ai)[K]) {
 #pragma unroll
   for (int k = 0; k < K; ++k) {
-    wv[k] = sx[lds_slot(q0 + M - 1 + k)];
-    pv[k] = fmaf(wv[k].x, wv[k].x, wv[k].y * wv[k].y);   // explicit: no contraction freedom
+    float Pr = hc[B - 1].x, Pi = hc[B - 1].y;
+#pragma unroll
+    for (int b = B - 2; b >= 0; --b) {
+      Pr = fmaf(Pr, pv[k], hc[b].x);
+      Pi = fmaf(Pi, pv[k], hc[b].y);
+    }
+    ar[k] = fmaf(wv[k].x, Pr, ar[k]);
+    ar[k] = fmaf(-wv[k].y, Pi, ar[k]);
+    ai[k] = fmaf(wv[k].x, Pi, ai[k]);
+    ai[k] = fmaf(wv[k].y, Pr, ai[k]);
   }
+}
+
+// Nothing is scheduled across: a tap's loads, its arithmetic and the first
+// use of what was loaded stay in that order, so the one wait of a tap (LDS
+// and scalar loads return out of order, it is for all of them) comes after
+// the whole arithmetic and before the next loads.  Left to itself the
+// scheduler moves the loads down to their use.
+__device__ __forceinline__ void tap_fence() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// The window moved by one sample.
+template <int K>
+__device__ __forceinline__ void slide(float2 (&wv)[K], float (&pv)[K], float2 wn) {
+#pragma unroll
+  for (int k = K - 1; k > 0; --k) {
+    wv[k] = wv[k - 1];
+    pv[k] = pv[k - 1];
+  }
+  wv[0] = wn;
+  pv[0] = fmaf(wn.x, wn.x, wn.y * wn.y);   // explicit: no contraction freedom
+}
+
+// One tap with the next tap's loads in flight: coefficients from `next`, the
+// sample that enters the window from `in()`.
+template <int K, int B, bool MASKED, class In>
+__device__ __forceinline__ void piped_tap(cfloat2p next, uint32_t set, In in, float2 (&hc)[B], float2 (&wv)[K],
+                                          float (&pv)[K], float (&ar)[K], float (&ai)[K]) {
+  float2 hn[B];
+  load_coefs<K, B, MASKED>(next, set, hn);
+  const float2 wn = in();
+  tap_fence();
+  horner_tap<K, B>(hc, wv, pv, ar, ai);
+  tap_fence();
+  slide<K>(wv, pv, wn);
+#pragma unroll
+  for (int b = 0; b < B; ++b) hc[b] = hn[b];
+  tap_fence();
+}
+
+template <int MT, int K, int B, bool MASKED>
+__device__ __forceinline__ void horner_taps(cfloat2p ht, uint32_t set, const float2 *sx, int q0, int Mr,
+                                            float (&ar)[K], float (&ai)[K]) {
+  float2 wv[K];
+  float pv[K];
   float2 hc[B];
+  const int M = MT ? MT : Mr;
+  const float2 *wp = sx + q0 / K * (K + 1);              // sample q0, q0 a multiple of K
 #pragma unroll
-  for (int b = 0; b < B; ++b) hc[b] = coef(b, b * M);
+  for (int k = 0; k < K; ++k) {
+    wv[k] = wp[lds_slot<K>(M - 1 + k)];
+    pv[k] = fmaf(wv[k].x, wv[k].x, wv[k].y * wv[k].y);
+  }
+  load_coefs<K, B, MASKED>(ht, set, hc);
+  if constexpr (MT != 0) {
 #pragma unroll
-  for (int m = 0; m < M; ++m) {
-    float2 hn[B];
-    float2 wn = make_float2(0.f, 0.f);
-    if (m + 1 < M) {
+    for (int m = 0; m + 1 < MT; ++m)
+      piped_tap<K, B, MASKED>(ht + (m + 1) * kCoefRow, set, [&] { return wp[lds_slot<K>(MT - 2 - m)]; }, hc, wv, pv, ar, ai);
+    horner_tap<K, B>(hc, wv, pv, ar, ai);
+  } else {
+    int left = M - 1;                                    // taps after the current one
+    for (; left >= K; left -= K) {
 #pragma unroll
-      for (int b = 0; b < B; ++b) hn[b] = coef(b, b * M + m + 1);
-      wn = sx[lds_slot(q0 + M - 2 - m)];
+      for (int j = 0; j < K; ++j)
+        piped_tap<K, B, MASKED>(ht + (j + 1) * kCoefRow, set, [&] { return wp[lds_slot<K>(left - 1 - j)]; }, hc, wv,
+                                pv, ar, ai);
+      ht += K * kCoefRow;
     }
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-      float Pr = hc[B - 1].x, Pi = hc[B - 1].y;
-#pragma unroll
-      for (int b = B - 2; b >= 0; --b) {
-        Pr = fmaf(Pr, pv[k], hc[b].x);
-        Pi = fmaf(Pi, pv[k], hc[b].y);
-      }
-      ar[k] = fmaf(wv[k].x, Pr, ar[k]);
-      ar[k] = fmaf(-wv[k].y, Pi, ar[k]);
-      ai[k] = fmaf(wv[k].x, Pi, ai[k]);
-      ai[k] = fmaf(wv[k].y, Pr, ai[k]);
-    }
-    asm volatile("" ::: "memory");
-    if (m + 1 < M) {
-#pragma unroll
-      for (int b = 0; b < B; ++b) hc[b] = hn[b];
-#pragma unroll
-      for (int k = K - 1; k > 0; --k) {
-        wv[k] = wv[k - 1];
-        pv[k] = pv[k - 1];
-      }
-      wv[0] = wn;
-      pv[0] = fmaf(wn.x, wn.x, wn.y * wn.y);
-    }
+    for (int j = 0; j < K - 1; ++j)
+      if (left > j)                                      // uniform
+        piped_tap<K, B, MASKED>(ht + (j + 1) * kCoefRow, set, [&] { return wp[lds_slot<K>(left - 1 - j)]; }, hc, wv,
+                                pv, ar, ai);
+    horner_tap<K, B>(hc, wv, pv, ar, ai);
   }
 }
 
@@ -203,11 +265,51 @@ __device__ __forceinline__ void head_correction(cfloat2p hg, BOf B_of, SrcOf src
   }
 }
 
+// The same for any tap count (M <= 32): rows of 32 lanes, two firings per
+// wavefront, the taps a loop and psi moved by lane shuffles.
+template <class BOf, class SrcOf, class Sample, class Emit>
+__device__ __forceinline__ void head_correction_any(cfloat2p hg, int M, BOf B_of, SrcOf src_of, Sample sample,
+                                                    int b_first, int b_step, Emit emit) {
+  const int L = M - 1;
+  const int lane = threadIdx.x & 63, row = lane >> 5, i = lane & 31;
+  const uint32_t set = (uint32_t)B_of(row);
+  int Bw = set_len(set);
+  Bw = __builtin_amdgcn_readfirstlane(max(Bw, __shfl_xor(Bw, 32)));
+  for (int b = b_first; b < Bw; b += b_step) {           // uniform
+    float2 xv = make_float2(0.f, 0.f);
+    if (in_set(set, b) && i < L) xv = sample(row, b, src_of(row, b), i);
+    const float pp = fmaf(xv.x, xv.x, xv.y * xv.y);
+    float pb = 1.f;
+    for (int e = 0; e < b; ++e) pb *= pp;
+    const float pr = pb * xv.x, pi = pb * xv.y;
+    float sr = 0.f, si = 0.f;
+    for (int m = 1; m < M; ++m) {
+      const float2 c = ldc(hg, b * M + m);
+      const int from = 32 * row + ((L + i - m) & 31);    // history sample i - m (meaningful for m > i)
+      const float vr = __shfl(pr, from), vi = __shfl(pi, from);
+      if (m > i) {
+        sr = fmaf(c.x, vr, sr);
+        sr = fmaf(-c.y, vi, sr);
+        si = fmaf(c.x, vi, si);
+        si = fmaf(c.y, vr, si);
+      }
+    }
+    emit(b, in_set(set, b), sr, si);
+  }
+}
+
 // The tile pipeline.  A workgroup of NT threads computes tiles of K*NT
 // consecutive outputs of one firing (B uniform over the tile), walking the
 // batch's tiles with a grid stride.  Loads are issued well before their use:
-// the descriptor of tile i+2 (one register, lane-distributed) and the window
+// the descriptor of tile i+2 and the window
 // and head corrections of tile i+1 are loaded while tile i is computed.
+// Bound by VALU issue (16 taps, 2^24 samples, mean length 5.5: 55 M wavefront
+// instructions of arithmetic, 90 us of the chip's issue); the body takes
+// 108 us there, 131 us before the taps were fenced (loads ahead of a tap, one
+// wait behind it), the stores moved behind the wait for the next window, the
+// window slots spread over all banks and the addresses made uniform bases
+// with 32-bit offsets.  The run-time tap loop takes 22 us for 2^21 samples of
+// 10 taps (mean length 6); one thread per sample and tap took 110 us.
 // Samples before the firing start are staged as zeros; a firing's first
 // M-1 outputs then add their head correction.  Every rounding step is an
 // explicit fmaf or a single operation, so all kernels built from these
@@ -217,51 +319,85 @@ __device__ __forceinline__ void head_correction(cfloat2p hg, BOf B_of, SrcOf src
 struct Job {
   const float2 *x;        // input ring
   float2 *y;              // output ring
-  const float2 *h;        // coefficients [B][M] of the firing's actor
+  const float2 *h;        // coefficients of the firing's actor, tap-major [M][kCoefRow]
   const float2 *corr;     // the firing's head corrections [M-1] (used when head)
   int64_t x_mask, y_mask;
-  int64_t xb, yb;         // ring positions of the firing's first input / output sample
-  int t0;                 // first output of the tile within the firing
+  int64_t xb, yb;         // ring positions of the tile's first input / output sample
   int nout;               // outputs in the tile
   uint32_t set;           // active branches of the firing (bit set)
   int B;                  // its Horner length (highest active branch + 1)
-  int head;               // first tile of a firing with active branches (0/1)
+  int first;              // first tile of its firing (0/1): no samples before it
+  int head;               // ... whose outputs take head corrections (0/1)
 };
 
-template <int M, int K>
+// Where a run of n consecutive ring samples from position p starts, and
+// whether it runs past the ring's end (uniform; a linear array never does).
+__device__ __forceinline__ bool ring_run(int64_t p, int64_t mask, int n, int64_t *slot) {
+  *slot = p & mask;
+  return mask >= 0 && *slot + n > mask + 1;
+}
+
+template <int K>
 struct TileRegs {
   float2 win[K + 1];
   float2 cv;              // head correction of output threadIdx.x (< M-1)
 };
 
-// Loads of tile j into registers (issued early, consumed by commit).
-template <int M, int K>
-__device__ __forceinline__ void load_tile(TileRegs<M, K> &r, const Job &j) {
+// Loads of tile j into registers (issued early, consumed by commit): sample
+// i of the window (i < nout + M - 1, the first M - 1 before the tile) by
+// thread i mod NT.  Addresses are a uniform base and a 32-bit offset; a tile
+// that runs past the ring's end (one in ring / tile) takes the masked form.
+// Indices are clamped into the window, and below a firing's start onto its
+// first sample (commit_tile writes 0 there), so that no load is conditional
+// and none is waited for here.
+template <int K>
+__device__ __forceinline__ void load_tile(TileRegs<K> &r, const Job &j, int M) {
+  const int tid = threadIdx.x, nt = blockDim.x, lo = j.first ? M - 1 : 0, hi = j.nout + M - 2;
+  int64_t slot;
+  if (!ring_run(j.xb - (M - 1), j.x_mask, j.nout + M - 1, &slot)) {
+    const char *p = (const char *)(j.x + slot);
 #pragma unroll
-  for (int u = 0; u < K + 1; ++u) {
-    const int idx = threadIdx.x + u * blockDim.x;
-    const int64_t pos = (int64_t)j.t0 - (M - 1) + idx;
-    r.win[u] = (idx < j.nout + M - 1 && pos >= 0) ? j.x[(j.xb + pos) & j.x_mask] : make_float2(0.f, 0.f);
+    for (int u = 0; u < K; ++u)
+      r.win[u] = *(const float2 *)(p + (uint32_t)min(max(tid + u * nt, lo), hi) * 8u);
+    if (tid < M - 1) r.win[K] = *(const float2 *)(p + (uint32_t)min(K * nt + tid, hi) * 8u);
+  } else {
+#pragma unroll
+    for (int u = 0; u < K; ++u) r.win[u] = j.x[(slot + min(max(tid + u * nt, lo), hi)) & j.x_mask];
+    if (tid < M - 1) r.win[K] = j.x[(slot + min(K * nt + tid, hi)) & j.x_mask];
   }
-  r.cv = (j.head && (int)threadIdx.x < M - 1) ? j.corr[threadIdx.x] : make_float2(0.f, 0.f);
+  if (j.head && tid < M - 1) r.cv = j.corr[tid];
 }
 
-template <int M, int K>
-__device__ __forceinline__ void commit_tile(float2 *sx, float2 *sc, const TileRegs<M, K> &r, const Job &j) {
+// Waits for the loads of load_tile.  The workgroup does so before it stores a
+// tile's outputs: loads and stores count on one counter in issue order, and a
+// wait at the next commit would be for the stores too.
+template <int K>
+__device__ __forceinline__ void settle(TileRegs<K> &r) {
 #pragma unroll
-  for (int u = 0; u < K + 1; ++u) {
-    const int idx = threadIdx.x + u * blockDim.x;
-    if (idx < j.nout + M - 1) sx[lds_slot(idx)] = r.win[u];
+  for (int u = 0; u < K + 1; ++u) asm volatile("" : "+v"(r.win[u].x), "+v"(r.win[u].y));
+  asm volatile("" : "+v"(r.cv.x), "+v"(r.cv.y));
+}
+
+// nt is a multiple of K, so a thread's slots are equally spaced.
+template <int K>
+__device__ __forceinline__ void commit_tile(float2 *sx, float2 *sc, const TileRegs<K> &r, const Job &j, int M) {
+  const int tid = threadIdx.x, step = lds_slot<K>(blockDim.x);
+  float2 *p = sx + lds_slot<K>(tid);
+  p[0] = j.first && tid < M - 1 ? make_float2(0.f, 0.f) : r.win[0];
+#pragma unroll
+  for (int u = 1; u < K; ++u) p[u * step] = r.win[u];
+  if (tid < M - 1) {
+    p[K * step] = r.win[K];
+    if (j.head) sc[tid] = r.cv;
   }
-  if (j.head && (int)threadIdx.x < M - 1) sc[threadIdx.x] = r.cv;
 }
 
 // The tile's main arithmetic (window in sx) for this thread's K outputs.
 // BC: largest Horner length compiled (10 or 16; fewer unrolled paths keep
 // the register budget of the common configurations small).  MASKED: tiles
 // may carry branch sets that are not prefixes (bit-mask control tokens).
-template <int M, int K, int BC, bool MASKED>
-__device__ __forceinline__ void tile_compute(const float2 *sx, cfloat2p hg, const Job &j, float (&ar)[K],
+template <int MT, int K, int BC, bool MASKED>
+__device__ __forceinline__ void tile_compute(const float2 *sx, cfloat2p ht, const Job &j, int M, float (&ar)[K],
                                              float (&ai)[K]) {
   const int q0 = threadIdx.x * K;
 #pragma unroll
@@ -270,7 +406,7 @@ __device__ __forceinline__ void tile_compute(const float2 *sx, cfloat2p hg, cons
   switch (j.B) {
 #define DF_CASE(n) \
   case n:                                                  \
-    if constexpr (n <= BC) horner_taps<M, K, n, MASKED>(hg, j.set, sx, q0, ar, ai); \
+    if constexpr (n <= BC) horner_taps<MT, K, n, MASKED>(ht, j.set, sx, q0, M, ar, ai); \
     break;
     DF_CASE(1) DF_CASE(2) DF_CASE(3) DF_CASE(4) DF_CASE(5) DF_CASE(6) DF_CASE(7) DF_CASE(8)
     DF_CASE(9) DF_CASE(10) DF_CASE(11) DF_CASE(12) DF_CASE(13) DF_CASE(14) DF_CASE(15) DF_CASE(16)
@@ -281,8 +417,8 @@ __device__ __forceinline__ void tile_compute(const float2 *sx, cfloat2p hg, cons
 
 // Store this thread's outputs; in a firing's first tile, outputs q < M-1
 // first add their head correction (staged in sc).
-template <int M, int K>
-__device__ __forceinline__ void tile_store(const float2 *sc, const Job &j, float (&ar)[K], float (&ai)[K]) {
+template <int K>
+__device__ __forceinline__ void tile_store(const float2 *sc, const Job &j, int M, float (&ar)[K], float (&ai)[K]) {
   const int q0 = threadIdx.x * K;
   if (q0 >= j.nout) return;
   if (j.head && q0 < M - 1) {
@@ -295,10 +431,29 @@ __device__ __forceinline__ void tile_store(const float2 *sc, const Job &j, float
       }
     }
   }
-  const int64_t yo = j.yb + j.t0 + q0;
+  int64_t slot;
+  if (!ring_run(j.yb, j.y_mask, j.nout, &slot)) {
+    char *p = (char *)(j.y + slot);
+    const uint32_t off = (uint32_t)q0 * 8u;              // a multiple of 32
+    if (q0 + K <= j.nout) {
+      if (((uintptr_t)p & 15) == 0) {                    // uniform: pairs of outputs in 16-byte stores
 #pragma unroll
-  for (int k = 0; k < K; ++k)
-    if (q0 + k < j.nout) j.y[(yo + k) & j.y_mask] = make_float2(ar[k], ai[k]);
+        for (int k = 0; k < K; k += 2)
+          *(float4 *)(p + off + 8 * k) = make_float4(ar[k], ai[k], ar[k + 1], ai[k + 1]);
+      } else {
+#pragma unroll
+        for (int k = 0; k < K; ++k) *(float2 *)(p + off + 8 * k) = make_float2(ar[k], ai[k]);
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < K; ++k)
+        if (q0 + k < j.nout) *(float2 *)(p + off + 8 * k) = make_float2(ar[k], ai[k]);
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+      if (q0 + k < j.nout) j.y[(slot + q0 + k) & j.y_mask] = make_float2(ar[k], ai[k]);
+  }
 }
 
 // Word w of a lane-distributed descriptor (lane w holds word w).
@@ -309,40 +464,57 @@ __device__ __forceinline__ uint64_t qword_at(uint32_t dv, int w) {
   return (uint64_t)dword_at(dv, w) | ((uint64_t)dword_at(dv, w + 1) << 32);
 }
 
-// The whole pipelined loop over tiles blockIdx.x, +gridDim.x, ... < n_items.
-// src.fetch(k) loads tile k's raw descriptor lane-distributed into one
-// register (a vector load, two tiles ahead); src.expand(dv, k, job) turns it
-// into the uniform Job (lane reads) when the tile's loads are issued.
-template <int M, int K, int BC, bool MASKED, class Src>
-__device__ __forceinline__ void run_tiles(float2 *sx, float2 *sc, int64_t n_items, Src &src) {
-  const int64_t s = gridDim.x;
-  int64_t item = blockIdx.x;
-  if (item >= n_items) return;                       // uniform
+// A workgroup's tiles: blockIdx.x, + gridDim.x, ... < n_items.  Tiles come
+// grouped by Horner length, longest first, so a compute unit whose workgroups
+// all walk forwards is bound by arithmetic first and by memory last.  Every
+// second workgroup of a compute unit (workgroups 256 apart share one of the
+// 256 units) walks its own tiles backwards, so that long and short ones
+// overlap all the time; which tiles a workgroup has does not change.
+struct Walk {
+  int64_t item, step, left;
+  __device__ __forceinline__ bool start(int64_t n_items) {
+    const int64_t b = blockIdx.x, g = gridDim.x;
+    if (b >= n_items) return false;
+    left = (uint64_t)(n_items - b + g - 1) / (uint32_t)g;
+    const bool back = (blockIdx.x >> 8) & 1;
+    item = back ? b + (left - 1) * g : b;
+    step = back ? -g : g;
+    return true;
+  }
+};
+
+// The whole pipelined loop over a workgroup's tiles.
+// src.fetch(k) loads tile k's raw descriptor two tiles ahead; src.expand(raw,
+// job) turns it into the uniform Job when the tile's loads are issued.
+// MT: the compiled tap count, or 0 (any count, Mr).
+template <int MT, int K, int BC, bool MASKED, class Src>
+__device__ __forceinline__ void run_tiles(float2 *sx, float2 *sc, int64_t n_items, Src &src, int Mr) {
+  const int M = MT ? MT : Mr;
+  Walk w;
+  if (!w.start(n_items)) return;                     // uniform
   Job cur, nxt;
-  src.expand(src.fetch(item), item, cur);
-  TileRegs<M, K> regs;
-  load_tile<M, K>(regs, cur);
-  bool has_next = item + s < n_items;
-  if (has_next) src.expand(src.fetch(item + s), item + s, nxt);
+  src.expand(src.fetch(w.item), cur);
+  TileRegs<K> regs;
+  load_tile<K>(regs, cur, M);
+  if (w.left > 1) src.expand(src.fetch(w.item + w.step), nxt);
   for (;;) {
-    commit_tile<M, K>(sx, sc, regs, cur);
+    commit_tile<K>(sx, sc, regs, cur, M);
     __syncthreads();
-    const bool has_nn = item + 2 * s < n_items;
-    if (has_next) load_tile<M, K>(regs, nxt);
-    const uint32_t dv_nn = has_nn ? src.fetch(item + 2 * s) : 0u;
+    if (w.left > 1) load_tile<K>(regs, nxt, M);
+    typename Src::Raw nn{};
+    if (w.left > 2) nn = src.fetch(w.item + 2 * w.step);
     float ar[K], ai[K];
-    tile_compute<M, K, BC, MASKED>(sx, as_const(cur.h), cur, ar, ai);
-    tile_store<M, K>(sc, cur, ar, ai);
-    if (!has_next) break;
+    tile_compute<MT, K, BC, MASKED>(sx, as_const(cur.h), cur, M, ar, ai);
+    if (w.left > 1) settle<K>(regs);
+    tile_store<K>(sc, cur, M, ar, ai);
+    if (w.left == 1) break;
     __syncthreads();
-    item += s;
+    w.item += w.step;
     cur = nxt;
-    if (has_nn) src.expand(dv_nn, item + s, nxt);
-    has_next = has_nn;
+    if (w.left > 2) src.expand(nn, nxt);
+    --w.left;
   }
 }
-
-
 
 // ------------------------------------------------------------------ matrix cores
 // Matrix-core form of a tile for M = 16 taps.  The per-tap polynomial is a
@@ -384,9 +556,11 @@ __device__ __forceinline__ float row_shr(float v) {
 
 // Window and row-sum buffer sizes of a matrix-core tile (float2 slots): the
 // blocks read window samples up to index tile + 30, and one block ahead.
-__host__ __device__ constexpr int mx_window(int tile) { return lds_window(tile + 48); }
+template <int K>
+__host__ __device__ constexpr int mx_window(int tile) { return lds_window<K>(tile + 48); }
 __host__ __device__ constexpr int mx_row(int tile) { return tile + 32; }
-__host__ __device__ constexpr int mx_lds(int tile) { return lds_corr(16) + mx_window(tile) + 4 * mx_row(tile) + 256; }
+template <int K>
+__host__ __device__ constexpr int mx_lds(int tile) { return lds_corr(16) + mx_window<K>(tile) + 4 * mx_row(tile) + 256; }
 
 // Coefficient operand of the tile's firing: lane l holds h_b[m] for branch
 // b = 4c + l/16, tap m = l%16 (zero for branches outside the set).
@@ -421,7 +595,7 @@ __device__ __forceinline__ void mx_load_coef(MxCoef &c, const Job &j) {
   for (int k = 0; k < 4; ++k) {
     const int b = 4 * k + (lane >> 4);
     const bool on = b < j.B && (!MASKED || in_set(j.set, b));
-    const float2 v = on ? j.h[b * 16 + (lane & 15)] : make_float2(0.f, 0.f);
+    const float2 v = on ? j.h[(lane & 15) * kCoefRow + b] : make_float2(0.f, 0.f);
     c.hr[k] = v.x;
     c.hi[k] = v.y;
   }
@@ -465,18 +639,18 @@ __device__ __forceinline__ void mx_block(const float2 xv, const MxCoef &c, float
 
 // Blocks [k0, k1) of the tile for this wavefront (block k0 - 1 first, for
 // the part of its row sums that falls into block k0).
-template <int NCH>
+template <int K, int NCH>
 __device__ __forceinline__ void mx_blocks(const float2 *sx, float2 *rb, int rs, const MxCoef &c, int k0, int k1) {
   const int lane = threadIdx.x & 63, j = lane & 15, rho = lane >> 4;
   float cr = 0.f, ci = 0.f;                          // carried into lanes 0..2 from the block before
   if (k0 > 0) {
     float mr, mi;
-    mx_block<NCH>(sx[lds_slot(16 * (k0 - 1) + j)], c, mr, mi, cr, ci);
+    mx_block<NCH>(sx[lds_slot<K>(16 * (k0 - 1) + j)], c, mr, mi, cr, ci);
   }
   float2 *dst = rb + rho * rs + j;
-  float2 xv = sx[lds_slot(16 * k0 + j)];             // the next block's sample is read one block ahead
+  float2 xv = sx[lds_slot<K>(16 * k0 + j)];             // the next block's sample is read one block ahead
   for (int k = k0; k < k1; ++k) {
-    const float2 xn = sx[lds_slot(16 * (k + 1) + j)];
+    const float2 xn = sx[lds_slot<K>(16 * (k + 1) + j)];
     float mr, mi, nr, ni;
     mx_block<NCH>(xv, c, mr, mi, nr, ni);
     dst[16 * k] = make_float2(mr + cr, mi + ci);
@@ -505,7 +679,7 @@ __device__ __forceinline__ void mx_store(const float2 *sc, const float2 *rb, int
       vr = vr + sc[q].x;
       vi = vi + sc[q].y;
     }
-    j.y[(j.yb + j.t0 + q) & j.y_mask] = make_float2(vr, vi);
+    j.y[(j.yb + q) & j.y_mask] = make_float2(vr, vi);
   }
 }
 
@@ -520,17 +694,17 @@ __device__ __forceinline__ void mx_tile(const float2 *sx, const float2 *sc, floa
   const int nch = (j.B + 3) >> 2;
   if (j.B > 0) {
     switch (nch) {
-      case 1: mx_blocks<1>(sx, rb, rs, c, k0, k1); break;
-      case 2: mx_blocks<2>(sx, rb, rs, c, k0, k1); break;
-      case 3: mx_blocks<3>(sx, rb, rs, c, k0, k1); break;
-      default: if constexpr (BC > 12) mx_blocks<4>(sx, rb, rs, c, k0, k1); break;
+      case 1: mx_blocks<K, 1>(sx, rb, rs, c, k0, k1); break;
+      case 2: mx_blocks<K, 2>(sx, rb, rs, c, k0, k1); break;
+      case 3: mx_blocks<K, 3>(sx, rb, rs, c, k0, k1); break;
+      default: if constexpr (BC > 12) mx_blocks<K, 4>(sx, rb, rs, c, k0, k1); break;
     }
   }
   __syncthreads();
   if (j.B > 0) {
     mx_store<K>(sc, rb, rs, j);
   } else {                                           // no active branch: zeros
-    for (int q = threadIdx.x; q < j.nout; q += blockDim.x) j.y[(j.yb + j.t0 + q) & j.y_mask] = make_float2(0.f, 0.f);
+    for (int q = threadIdx.x; q < j.nout; q += blockDim.x) j.y[(j.yb + q) & j.y_mask] = make_float2(0.f, 0.f);
   }
 }
 
@@ -541,36 +715,34 @@ template <int K, int BC, bool MASKED, class Src>
 __device__ __forceinline__ void run_tiles_mx(float2 *sx, float2 *sc, float2 *rb, float2 *sh, int64_t n_items,
                                              Src &src) {
   constexpr int M = 16;
-  const int64_t s = gridDim.x;
-  int64_t item = blockIdx.x;
-  if (item >= n_items) return;                       // uniform
+  Walk w;
+  if (!w.start(n_items)) return;                     // uniform
   Job cur, nxt;
-  src.expand(src.fetch(item), item, cur);
-  TileRegs<M, K> regs;
+  src.expand(src.fetch(w.item), cur);
+  TileRegs<K> regs;
   MxCoef cl;                                         // coefficient loads of the tile to commit
-  load_tile<M, K>(regs, cur);
+  load_tile<K>(regs, cur, M);
   mx_load_coef<MASKED>(cl, cur);
-  bool has_next = item + s < n_items;
-  if (has_next) src.expand(src.fetch(item + s), item + s, nxt);
+  if (w.left > 1) src.expand(src.fetch(w.item + w.step), nxt);
   for (;;) {
-    commit_tile<M, K>(sx, sc, regs, cur);
+    commit_tile<K>(sx, sc, regs, cur, M);
     mx_commit_coef(sh, cl);
     __syncthreads();
-    const bool has_nn = item + 2 * s < n_items;
-    if (has_next) {
-      load_tile<M, K>(regs, nxt);
+    if (w.left > 1) {
+      load_tile<K>(regs, nxt, M);
       mx_load_coef<MASKED>(cl, nxt);
     }
-    const uint32_t dv_nn = has_nn ? src.fetch(item + 2 * s) : 0u;
+    typename Src::Raw nn{};
+    if (w.left > 2) nn = src.fetch(w.item + 2 * w.step);
     MxCoef c;
     mx_read_coef(sh, c);
     mx_tile<K, BC>(sx, sc, rb, c, cur);
-    if (!has_next) break;
+    if (w.left == 1) break;
     __syncthreads();
-    item += s;
+    w.item += w.step;
     cur = nxt;
-    if (has_nn) src.expand(dv_nn, item + s, nxt);
-    has_next = has_nn;
+    if (w.left > 2) src.expand(nn, nxt);
+    --w.left;
   }
 }
 

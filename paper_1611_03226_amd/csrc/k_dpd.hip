@@ -34,41 +34,31 @@ __device__ __forceinline__ float2 hist_sample(const DpdArgs &a, int64_t Rx, int 
   return make_float2(0.f, 0.f);
 }
 
-// ------------------------------------------------------------------ generic
-// One thread per output sample, direct form with per-branch sources.  Any
-// B_max <= 16 and M <= 32.
-__global__ __launch_bounds__(256) void k_dpd_generic(DpdArgs a) {
-  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (t >= a.n_firings * a.r) return;
-  const int64_t g = t / a.r;
-  const int64_t i = t - g * a.r;
-  const uint32_t set = a.B ? (uint32_t)a.B[g] : prefix_set(a.B_const);
-  const int64_t Rx = a.x_idx ? a.x_idx[0] : 0;
-  const int64_t Wy = a.y_idx ? a.y_idx[1] : 0;
-  float ar = 0.f, ai = 0.f;
-  for (int b = 0; b < kMaxBranches; ++b) {
-    if (!in_set(set, b)) continue;
-    const int64_t pf = (i < a.M - 1) ? prev_of(a, b, g) : -1;
-    for (int m = 0; m < a.M; ++m) {
-      const int64_t ii = i - m;
-      const float2 xv = ii >= 0 ? a.x[(Rx + g * a.r + ii) & a.x_mask]
-                                : hist_sample(a, Rx, b, g, pf, ii);
-      const float p = xv.x * xv.x + xv.y * xv.y;
-      float pb = 1.f;
-      for (int k = 0; k < b; ++k) pb *= p;
-      const float sr = pb * xv.x, si = pb * xv.y;
-      const float2 c = a.h[b * a.M + m];
-      ar += c.x * sr - c.y * si;
-      ai += c.x * si + c.y * sr;
-    }
+// ------------------------------------------------------------------ coefficients
+// Tap-major coefficients (see kCoefRow) from [B_max][M]: by one workgroup of
+// a head pass, or a launch of their own.
+__device__ __forceinline__ void coef_rows(const float2 *h, float2 *ht, int B_max, int M) {
+  for (int t = threadIdx.x; t < M * kCoefRow; t += blockDim.x) {
+    const int m = t / kCoefRow, b = t % kCoefRow;
+    ht[t] = b < B_max ? h[b * M + m] : make_float2(0.f, 0.f);
   }
-  a.y[(Wy + t) & a.y_mask] = make_float2(ar, ai);
+}
+
+__global__ __launch_bounds__(512) void k_coef_rows(const float2 *h, float2 *ht, int B_max, int M) {
+  coef_rows(h, ht, B_max, M);
+}
+
+size_t coef_rows_bytes(int M) { return sizeof(float2) * kCoefRow * (size_t)M; }
+
+hipError_t launch_coef_rows(const float2 *h, float2 *ht, int B_max, int M, hipStream_t s) {
+  hipLaunchKernelGGL(k_coef_rows, dim3(1), dim3(512), 0, s, h, ht, B_max, M);
+  return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ commit
 // Advance the channel indices by the batch's token counts and carry each
 // branch's history: the last M-1 input samples of its last feeding firing.
-// One workgroup (a kernel of its own, or the body's last workgroup).
+// One workgroup (the body's last).
 __device__ __forceinline__ void dpd_commit_block(const DpdCommitArgs &a) {
   const int64_t Rx = a.x_idx[0];
   __syncthreads();
@@ -90,16 +80,20 @@ __device__ __forceinline__ void dpd_commit_block(const DpdCommitArgs &a) {
 }
 
 // ------------------------------------------------------------------ heads
-// Head corrections of every firing with B > 0 (four firings per
-// wavefront); corr[g][q], q < M-1.  Read by the tiled body.  With a group
+// Head corrections of every firing with B > 0 (four firings per wavefront
+// for M = 4, 8, 16; two for any other tap count, M = 0 here); corr[g][q],
+// q < M-1.  Read by the tiled body.  With a group
 // table (one segment) the wavefront also derives the history sources of its
-// four firings and writes their prev/off table entries: the four firings lie
+// firings and writes their prev/off table entries: its firings lie
 // in one 64-firing group, so a ballot of the group's feed flags per branch
 // plus the group's entry (count and last feeder before it) gives them;
-// with order_out it also writes the four firings' processing slots.
-template <int M, bool TABLES>
+// with order_out it also writes the firings' processing slots.
+template <int MT, bool TABLES>
 __global__ __launch_bounds__(256) void k_dpd_heads(DpdArgs a) {
-  // The workgroup's four wavefronts share four firings; wavefront w takes
+  constexpr int RL = MT ? 16 : 32;                    // lanes per firing
+  constexpr int NR = 64 / RL;                         // firings of the workgroup
+  const int M = MT ? MT : a.M;
+  // The workgroup's four wavefronts share its firings; wavefront w takes
   // branches w, w+4, w+8, w+12 (more wavefronts in flight, a quarter of the
   // serial work each); each branch's sum goes to LDS and one wavefront adds
   // them in increasing branch order, as a single pass would.
@@ -119,10 +113,11 @@ __global__ __launch_bounds__(256) void k_dpd_heads(DpdArgs a) {
       *a.err_ahead = 0;
     }
   }
-  const int64_t g0 = hb * 4;
+  if (a.fill_ht && hb == 0) coef_rows(a.h, a.ht, a.B_max, M);
+  const int64_t g0 = hb * NR;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t Rx = a.x_idx ? as_const(a.x_idx)[0] : 0;
-  const int lane = threadIdx.x & 63, row = lane >> 4, i = lane & 15;
+  const int lane = threadIdx.x & 63, row = lane / RL, i = lane % RL;
   const int64_t g = g0 + row;                         // this lane's firing
   int64_t pf[kMaxBranches];
   if constexpr (TABLES) {
@@ -147,12 +142,12 @@ __global__ __launch_bounds__(256) void k_dpd_heads(DpdArgs a) {
       }
     }
     if (a.order_out && w == 0) {
-      // processing slot of each of the four firings: its length's first
+      // processing slot of each of the firings: its length's first
       // slot in this group plus the firings of that length before it here
       const int NV = a.B_max + 1;
       const int Ll = gin ? set_len(Bl) : -1;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
+      for (int q = 0; q < NR; ++q) {
         const int lq = (int)(g0 & 63) + q;            // group lane of firing g0 + q
         if (g0 + q >= a.n_firings) break;             // uniform
         const uint32_t Sq = (uint32_t)__builtin_amdgcn_readlane((int)Bl, lq);
@@ -170,17 +165,19 @@ __global__ __launch_bounds__(256) void k_dpd_heads(DpdArgs a) {
     const int64_t gr = g0 + r;
     return gr < a.n_firings ? (a.B ? (uint32_t)a.B[gr] : prefix_set(a.B_const)) : 0u;
   };
-  head_correction<M, 4>(
-      as_const(a.h), B_of,
-      [&](int r, int b) {
-        if constexpr (TABLES) return pf[b];              // this lane's row
-        else return prev_of(a, b, g0 + r);
-      },
-      [&](int r, int b, int64_t p, int q) { return hist_sample(a, Rx, b, g0 + r, p, (int64_t)q - (M - 1)); },
-      w, 4, [&](int b, bool, float sr, float si) { part[b][lane] = make_float2(sr, si); });
+  const auto src_of = [&](int r, int b) {
+    if constexpr (TABLES) return pf[b];                // this lane's row
+    else return prev_of(a, b, g0 + r);
+  };
+  const auto sample = [&](int r, int b, int64_t p, int q) {
+    return hist_sample(a, Rx, b, g0 + r, p, (int64_t)q - (M - 1));
+  };
+  const auto emit = [&](int b, bool, float sr, float si) { part[b][lane] = make_float2(sr, si); };
+  if constexpr (MT != 0) head_correction<MT, NR>(as_const(a.h), B_of, src_of, sample, w, 4, emit);
+  else head_correction_any(as_const(a.h), M, B_of, src_of, sample, w, 4, emit);
   __syncthreads();
   const uint32_t set = B_of(row);
-  if (w == 0 && head_live<M, 4>(set)) {
+  if (w == 0 && i < M - 1 && set != 0u) {
     float cr = 0.f, ci = 0.f;
     for (int b = 0; b < kMaxBranches; ++b)
       if (in_set(set, b)) {
@@ -198,43 +195,47 @@ __global__ __launch_bounds__(256) void k_dpd_heads(DpdArgs a) {
 struct SingleSrc {
   const DpdArgs &a;
   int64_t Rx, Wy;
-  __device__ uint32_t fetch(int64_t it) const {
-    const int lane = threadIdx.x & 63;
-    const int64_t k = it / a.tiles_per_firing;
-    if (a.order) return lane < 2 ? (uint32_t)a.order[2 * k + lane] : 0u;
-    if (lane == 0) return (uint32_t)k;
-    if (lane == 1) return a.B ? (uint32_t)a.B[k] : prefix_set(a.B_const);
-    return 0u;
+  __device__ SingleSrc(const DpdArgs &a_)
+      : a(a_), Rx(a_.x_idx ? as_const(a_.x_idx)[0] : 0), Wy(a_.y_idx ? as_const(a_.y_idx)[1] : 0) {}
+  struct Raw {
+    uint32_t g, set, tile;                           // firing, branch set, tile of the firing
+  };
+  // scalar loads: a vector load here would share the window loads' counter
+  __device__ Raw fetch(int64_t it) const {
+    const uint32_t k = (uint32_t)it / (uint32_t)a.tiles_per_firing;
+    const uint32_t tile = (uint32_t)it - k * (uint32_t)a.tiles_per_firing;
+    if (a.order) return {(uint32_t)as_const(a.order)[2 * (int64_t)k], (uint32_t)as_const(a.order)[2 * (int64_t)k + 1], tile};
+    return {k, a.B ? (uint32_t)as_const(a.B)[k] : prefix_set(a.B_const), tile};
   }
-  __device__ void expand(uint32_t dv, int64_t it, Job &j) const {
-    const int64_t k = it / a.tiles_per_firing;
-    const int64_t tk = it - k * a.tiles_per_firing;
-    const int64_t g = dword_at(dv, 0);
-    const uint32_t set = dword_at(dv, 1);
+  __device__ void expand(const Raw &q, Job &j) const {
+    const int64_t g = q.g;
+    const uint32_t set = q.set;
+    const int64_t t0 = (int64_t)q.tile * a.tile;
     j.x = a.x;
     j.y = a.y;
-    j.h = a.h;
+    j.h = a.ht;
     j.corr = a.corr + g * (a.M - 1);
     j.x_mask = a.x_mask;
     j.y_mask = a.y_mask;
-    j.xb = Rx + g * a.r;
-    j.yb = Wy + g * a.r;
-    j.t0 = (int)(tk * a.tile);
-    j.nout = (int)min((int64_t)a.tile, a.r - j.t0);
+    j.xb = Rx + g * a.r + t0;
+    j.yb = Wy + g * a.r + t0;
+    j.nout = (int)min((int64_t)a.tile, a.r - t0);
     j.set = set;
     j.B = set_len(set);
-    j.head = (j.t0 == 0 && set != 0u) ? 1 : 0;
+    j.first = t0 == 0;
+    j.head = (t0 == 0 && set != 0u && a.corr) ? 1 : 0;
   }
 };
 
 // Grid-stride loop over the batch's tiles in the length-grouped firing order,
-// pipelined as run_tiles describes.
-template <int M, int K, int BC, bool MASKED>
+// pipelined as run_tiles describes.  MT: the compiled tap count (4, 8, 16),
+// or 0: any count, the taps a loop.
+template <int MT, int K, int BC, bool MASKED>
 __global__ __launch_bounds__(256) void k_dpd_tiled(DpdArgs a) {
   extern __shared__ float2 lds[];   // [M-1] head corrections, window
-  float2 *sc = lds, *sx = sc + lds_corr(M);
-  SingleSrc src{a, a.x_idx ? as_const(a.x_idx)[0] : 0, a.y_idx ? as_const(a.y_idx)[1] : 0};
-  run_tiles<M, K, BC, MASKED>(sx, sc, a.n_firings * a.tiles_per_firing, src);
+  float2 *sc = lds, *sx = sc + lds_corr(MT ? MT : a.M);
+  SingleSrc src(a);
+  run_tiles<MT, K, BC, MASKED>(sx, sc, a.n_firings * a.tiles_per_firing, src, a.M);
   if (!a.ticket) return;
   // The last workgroup to finish commits the batch: every other workgroup
   // has read the channel indices by then (it read them before finishing),
@@ -256,8 +257,8 @@ __global__ __launch_bounds__(256) void k_dpd_tiled(DpdArgs a) {
 template <int K, int BC, bool MASKED>
 __global__ __launch_bounds__(256) void k_dpd_tiled_mx(DpdArgs a) {
   extern __shared__ float2 lds[];   // [15] head corrections, window, 4 row-sum rows, coefficients
-  float2 *sc = lds, *sx = sc + lds_corr(16), *rb = sx + mx_window(a.tile), *sh = rb + 4 * mx_row(a.tile);
-  SingleSrc src{a, a.x_idx ? as_const(a.x_idx)[0] : 0, a.y_idx ? as_const(a.y_idx)[1] : 0};
+  float2 *sc = lds, *sx = sc + lds_corr(16), *rb = sx + mx_window<K>(a.tile), *sh = rb + 4 * mx_row(a.tile);
+  SingleSrc src(a);
   run_tiles_mx<K, BC, MASKED>(sx, sc, rb, sh, a.n_firings * a.tiles_per_firing, src);
   if (!a.ticket) return;
   __shared__ int last_block;                         // commit by the last workgroup, as above
@@ -278,7 +279,7 @@ static hipError_t launch_tiled_mx(const DpdArgs &a0, hipStream_t s, int tile, co
   a.tile = tile;
   a.tiles_per_firing = (int32_t)((a.r + tile - 1) / tile);
   const int threads = tile / K;
-  const size_t lds = (size_t)mx_lds(tile) * sizeof(float2);
+  const size_t lds = (size_t)mx_lds<K>(tile) * sizeof(float2);
   const int64_t items = a.n_firings * a.tiles_per_firing;
   if (items <= 0) return hipSuccess;
   const int64_t resident = resident_blocks((const void *)k_dpd_tiled_mx<K, BC, MASKED>, threads, lds);
@@ -291,26 +292,28 @@ static hipError_t launch_tiled_mx(const DpdArgs &a0, hipStream_t s, int tile, co
   return hipGetLastError();
 }
 
-template <int M, int K, int BC, bool MASKED>
+template <int MT, int K, int BC, bool MASKED>
 static hipError_t launch_tiled(const DpdArgs &a0, hipStream_t s, int tile, const KTiming *t) {
   DpdArgs a = a0;
   a.tile = tile;
   a.tiles_per_firing = (int32_t)((a.r + tile - 1) / tile);
   const int threads = tile / K;
-  const size_t lds = (size_t)(lds_window(tile + M - 1) + lds_corr(M)) * sizeof(float2);
+  const size_t lds = (size_t)(lds_window<K>(tile + a.M - 1) + lds_corr(a.M)) * sizeof(float2);
   const int64_t items = a.n_firings * a.tiles_per_firing;
   if (items <= 0) return hipSuccess;
-  const int64_t resident = resident_blocks((const void *)k_dpd_tiled<M, K, BC, MASKED>, threads, lds);
+  const int64_t resident = resident_blocks((const void *)k_dpd_tiled<MT, K, BC, MASKED>, threads, lds);
   const int64_t blocks = items < resident ? items : resident;
   if (t)
-    hipExtLaunchKernelGGL((k_dpd_tiled<M, K, BC, MASKED>), dim3((unsigned)blocks), dim3(threads), lds, s, t->start, t->stop,
+    hipExtLaunchKernelGGL((k_dpd_tiled<MT, K, BC, MASKED>), dim3((unsigned)blocks), dim3(threads), lds, s, t->start, t->stop,
                           0, a);
   else
-    hipLaunchKernelGGL((k_dpd_tiled<M, K, BC, MASKED>), dim3((unsigned)blocks), dim3(threads), lds, s, a);
+    hipLaunchKernelGGL((k_dpd_tiled<MT, K, BC, MASKED>), dim3((unsigned)blocks), dim3(threads), lds, s, a);
   return hipGetLastError();
 }
 
-bool dpd_tiled_shape(int M) { return M == 4 || M == 8 || M == 16; }
+// Tap counts compiled into the head pass and the bodies; any other count
+// runs the kernels whose taps are a loop.
+static bool compiled_taps(int M) { return M == 4 || M == 8 || M == 16; }
 
 bool dpd_body_mx_env() {
   const char *v = getenv("DFHIP_BODY");
@@ -318,41 +321,41 @@ bool dpd_body_mx_env() {
 }
 
 hipError_t launch_dpd_heads(const DpdArgs &a, hipStream_t s) {
-  if (a.n_firings <= 0 || !dpd_tiled_shape(a.M)) return hipSuccess;
-  if (!a.corr) return hipErrorInvalidValue;
+  if (a.n_firings <= 0) return hipSuccess;
+  if (!a.corr || a.M < 1 || a.M > kMaxTaps || (a.fill_ht && !a.ht)) return hipErrorInvalidValue;
   if (a.grp && (a.seg_firings != a.n_firings || !a.tab_prev)) return hipErrorInvalidValue;
   if (a.ahead_blocks < 0 || (a.ahead_blocks && (!a.grp || a.ahead.n_segs != 1 || !a.ahead.grp || !a.ahead.ticket ||
                                                a.ahead_blocks != (scan_groups(1, a.ahead.seg_firings) + 3) / 4)))
     return hipErrorInvalidValue;
-  const dim3 grid((unsigned)((a.n_firings + 3) / 4 + a.ahead_blocks));
+  const int nr = compiled_taps(a.M) ? 4 : 2;           // firings per workgroup
+  const dim3 grid((unsigned)((a.n_firings + nr - 1) / nr + a.ahead_blocks));
 #define DF_HEADS(m)                                                                     \
-  if (a.M == m) {                                                                       \
+  if (m == 0 || a.M == m) {                                                             \
     if (a.grp)                                                                          \
       hipLaunchKernelGGL((k_dpd_heads<m, true>), grid, dim3(256), 0, s, a);             \
     else                                                                                \
       hipLaunchKernelGGL((k_dpd_heads<m, false>), grid, dim3(256), 0, s, a);            \
   }
-  DF_HEADS(16) else DF_HEADS(8) else DF_HEADS(4)
+  DF_HEADS(16) else DF_HEADS(8) else DF_HEADS(4) else DF_HEADS(0)
 #undef DF_HEADS
   return hipGetLastError();
 }
 
 hipError_t launch_dpd_body(const DpdArgs &a, hipStream_t s, int tile, int outputs_per_thread, const KTiming *t) {
   if (a.n_firings <= 0) return hipSuccess;
-  if (!dpd_tiled_shape(a.M)) {
-    const int64_t total = a.n_firings * a.r;
-    const dim3 grid((unsigned)((total + 255) / 256));
-    if (t)
-      hipExtLaunchKernelGGL(k_dpd_generic, grid, dim3(256), 0, s, t->start, t->stop, 0, a);
-    else
-      hipLaunchKernelGGL(k_dpd_generic, grid, dim3(256), 0, s, a);
-    return hipGetLastError();
-  }
-  if (!a.corr) return hipErrorInvalidValue;          // launch_dpd_heads fills it first
+  if (!a.ht || a.M < 1 || a.M > kMaxTaps) return hipErrorInvalidValue;
+  // Shape: 2048 outputs with eight per thread where firings fill such tiles
+  // and there is one for each of the 256 compute units (fewer scalar loads,
+  // LDS reads and |x|^2 per output; ms against 1024 with four: 32 firings of
+  // 65536, 10 taps 0.022 / 0.029; 256 of 4096, 16 taps 0.016 / 0.021; 4096 of
+  // 4096 0.108 / 0.107; 128 of 4096 0.014 / 0.014), else 1024 with four (777
+  // firings of 1000: 0.019 / 0.023).  A caller's own choice of either value
+  // stands (df_set_tile).
   // Tile: a multiple of 64*K outputs, at most 256 threads, no larger than
   // needed for one firing.
-  const int K = outputs_per_thread == 8 ? 8 : 4;
-  int tl = tile > 0 ? tile : 1024;
+  const bool big = tile <= 0 && a.r >= 2048 && a.n_firings * a.r >= 256 * 2048;
+  const int K = outputs_per_thread == 8 || (outputs_per_thread == 0 && big) ? 8 : 4;
+  int tl = tile > 0 ? tile : (outputs_per_thread == 0 && big ? 2048 : 1024);
   const int64_t rr = ((a.r + 64 * K - 1) / (64 * K)) * (64 * K);
   if ((int64_t)tl > rr) tl = (int)rr;
   tl = (tl / (64 * K)) * (64 * K);
@@ -369,21 +372,13 @@ hipError_t launch_dpd_body(const DpdArgs &a, hipStream_t s, int tile, int output
                     : (small ? launch_tiled_mx<8, 10, false>(a, s, tl, t) : launch_tiled_mx<8, 16, false>(a, s, tl, t));
   }
 #define DF_TILED(m, k)                                                                      \
-  if (a.M == m && K == k)                                                                   \
+  if ((m == 0 || a.M == m) && K == k)                                                       \
     return a.masked ? launch_tiled<m, k, 16, true>(a, s, tl, t)                             \
                     : (small ? launch_tiled<m, k, 10, false>(a, s, tl, t) : launch_tiled<m, k, 16, false>(a, s, tl, t));
   DF_TILED(16, 4) DF_TILED(16, 8) DF_TILED(8, 4) DF_TILED(8, 8) DF_TILED(4, 4) DF_TILED(4, 8)
+  DF_TILED(0, 4) DF_TILED(0, 8)
 #undef DF_TILED
   return hipErrorInvalidValue;
-}
-
-__global__ __launch_bounds__(1024) void k_dpd_commit(DpdCommitArgs a) { dpd_commit_block(a); }
-
-hipError_t launch_dpd_commit(const DpdCommitArgs &a, hipStream_t s) {
-  int threads = a.B_max * (a.M - 1);
-  threads = threads < 64 ? 64 : (threads > 1024 ? 1024 : ((threads + 63) / 64) * 64);
-  hipLaunchKernelGGL(k_dpd_commit, dim3(1), dim3(threads), 0, s, a);
-  return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ small helpers

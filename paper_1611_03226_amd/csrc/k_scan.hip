@@ -32,6 +32,7 @@
 // (popcount / highest bit of the ballot bits below its lane) and writes
 // off_b, prev_b (paths without a head pass that does it).
 #include <algorithm>
+#include <mutex>
 
 #include "scan_dev.h"
 
@@ -100,8 +101,10 @@ int64_t resident_blocks(const void *kernel, int threads, size_t lds_bytes) {
   };
   static Entry cache[64];
   static int used = 0;
+  static std::mutex mu;
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) dev = 0;
+  std::lock_guard<std::mutex> lock(mu);
   for (int i = 0; i < used; ++i)
     if (cache[i].k == kernel && cache[i].threads == threads && cache[i].lds == lds_bytes && cache[i].dev == dev)
       return cache[i].n;

@@ -21,8 +21,11 @@ namespace {
 // holds one copy until the process ends.
 constexpr size_t kScratchBytes = size_t(12) << 20;
 constexpr int kMaxDevices = 64;
+// Tap-major coefficients of the call, behind the counted scratch (at most
+// kMaxTaps rows of 16 complex64).
+constexpr size_t kCoefBytes = size_t(32) * 16 * 8;
 
-__device__ __align__(256) unsigned char scratch[kScratchBytes];
+__device__ __align__(256) unsigned char scratch[kScratchBytes + kCoefBytes];
 
 std::mutex g_mu;
 unsigned char *g_ptr[kMaxDevices] = {};
@@ -77,6 +80,8 @@ extern "C" df_status df_dpd_forward_noalloc(void *stream, const void *x, const i
   if (z.prev) sc.prev = (int64_t *)(base + off);
   off += align256(z.prev);
   if (z.grp) sc.grp = base + off;
+  if (z.ht > kCoefBytes) return fail(nullptr, DF_EINVAL, "df_dpd_forward_noalloc: bad tap count");
+  sc.ht = (float2 *)(base + kScratchBytes);
   e = dpd_forward_enqueue(sc, (hipStream_t)stream, x, ctrl, h, y, S, len, r, B_max, M, hist);
   if (e != hipSuccess) return fail_hip(nullptr, e, "df_dpd_forward_noalloc");
   return DF_OK;

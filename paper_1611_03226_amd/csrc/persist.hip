@@ -42,6 +42,7 @@ struct InstDesc {
   int64_t *ctrl_idx;
   int64_t ctrl_mask;
   const float2 *h;
+  const float2 *ht;       // tap-major coefficients (bodies)
   float2 *hist;
   int64_t r;
   int32_t B_max;
@@ -57,8 +58,8 @@ struct PItem {
   const float2 *h;
   const float2 *corr;     // head corrections of the firing [M-1]
   int64_t x_mask, y_mask;
-  int64_t xb, yb;         // ring positions of the firing's first input / output sample
-  int32_t t0, nout;
+  int64_t xb, yb;         // ring positions of the tile's first input / output sample
+  int32_t first, nout;    // first: the firing's first tile
   uint32_t set;           // the firing's branch set
   int32_t head;
 };
@@ -224,13 +225,13 @@ __device__ __forceinline__ void pers_items(const PersArgs &a, int64_t blk, int64
     PItem p;
     p.x = d.x;
     p.y = d.y;
-    p.h = d.h;
+    p.h = d.ht;
     p.corr = a.corr_all + gf * (a.M - 1);
     p.x_mask = d.x_mask;
     p.y_mask = d.y_mask;
-    p.xb = Rx + j * d.r;
-    p.yb = d.y_idx[1] + j * d.r;
-    p.t0 = (int32_t)t0;
+    p.xb = Rx + j * d.r + t0;
+    p.yb = d.y_idx[1] + j * d.r + t0;
+    p.first = t0 == 0;
     p.nout = (int32_t)min((int64_t)a.tile, d.r - t0);
     p.set = set;
     p.head = (t0 == 0 && set != 0u) ? 1 : 0;
@@ -242,11 +243,15 @@ __device__ __forceinline__ void pers_items(const PersArgs &a, int64_t blk, int64
 struct ItemSrc {
   const PersArgs &a;
   static constexpr int kWords = (int)(sizeof(PItem) / 4);
-  __device__ uint32_t fetch(int64_t it) const {
+  struct Raw {
+    uint32_t dv;          // lane-distributed words
+  };
+  __device__ Raw fetch(int64_t it) const {
     const int lane = threadIdx.x & 63;
-    return lane < kWords ? reinterpret_cast<const uint32_t *>(a.items + it)[lane] : 0u;
+    return {lane < kWords ? reinterpret_cast<const uint32_t *>(a.items + it)[lane] : 0u};
   }
-  __device__ void expand(uint32_t dv, int64_t, Job &j) const {
+  __device__ void expand(const Raw &q, Job &j) const {
+    const uint32_t dv = q.dv;
     j.x = (const float2 *)qword_at(dv, offsetof(PItem, x) / 4);
     j.y = (float2 *)qword_at(dv, offsetof(PItem, y) / 4);
     j.h = (const float2 *)qword_at(dv, offsetof(PItem, h) / 4);
@@ -255,7 +260,7 @@ struct ItemSrc {
     j.y_mask = (int64_t)qword_at(dv, offsetof(PItem, y_mask) / 4);
     j.xb = (int64_t)qword_at(dv, offsetof(PItem, xb) / 4);
     j.yb = (int64_t)qword_at(dv, offsetof(PItem, yb) / 4);
-    j.t0 = (int)dword_at(dv, offsetof(PItem, t0) / 4);
+    j.first = (int)dword_at(dv, offsetof(PItem, first) / 4);
     j.nout = (int)dword_at(dv, offsetof(PItem, nout) / 4);
     j.set = dword_at(dv, offsetof(PItem, set) / 4);
     j.B = set_len(j.set);
@@ -320,14 +325,14 @@ __global__ __launch_bounds__(512) void k_pers_body(PersArgs a) {
   extern __shared__ float2 lds[];   // [M-1] head corrections, window
   float2 *sc = lds, *sx = sc + lds_corr(M);
   ItemSrc src{a};
-  run_tiles<M, K, BC, MASKED>(sx, sc, as_const(a.tile_base)[a.n_inst], src);
+  run_tiles<M, K, BC, MASKED>(sx, sc, as_const(a.tile_base)[a.n_inst], src, a.M);
 }
 
 // The same walk with matrix-core tiles (M = 16).
 template <int K, int BC, bool MASKED>
 __global__ __launch_bounds__(512) void k_pers_body_mx(PersArgs a) {
   extern __shared__ float2 lds[];   // [15] head corrections, window, 4 row-sum rows, coefficients
-  float2 *sc = lds, *sx = sc + lds_corr(16), *rb = sx + mx_window(a.tile), *sh = rb + 4 * mx_row(a.tile);
+  float2 *sc = lds, *sx = sc + lds_corr(16), *rb = sx + mx_window<K>(a.tile), *sh = rb + 4 * mx_row(a.tile);
   ItemSrc src{a};
   run_tiles_mx<K, BC, MASKED>(sx, sc, rb, sh, as_const(a.tile_base)[a.n_inst], src);
 }
@@ -409,7 +414,7 @@ void destroy_persistent(df_graph *g) {
 
 template <int M, int K, int BC, bool MASKED>
 static hipError_t launch_pers_body(const PersArgs &a, int threads, int blocks, hipStream_t s, const KTiming *t) {
-  const size_t lds = (size_t)(lds_window(a.tile + M - 1) + lds_corr(M)) * sizeof(float2);
+  const size_t lds = (size_t)(lds_window<K>(a.tile + M - 1) + lds_corr(M)) * sizeof(float2);
   if (t)
     hipExtLaunchKernelGGL((k_pers_body<M, K, BC, MASKED>), dim3(blocks), dim3(threads), lds, s, t->start, t->stop, 0, a);
   else
@@ -419,7 +424,7 @@ static hipError_t launch_pers_body(const PersArgs &a, int threads, int blocks, h
 
 template <int K, int BC, bool MASKED>
 static hipError_t launch_pers_body_mx(const PersArgs &a, int threads, int blocks, hipStream_t s, const KTiming *t) {
-  const size_t lds = (size_t)mx_lds(a.tile) * sizeof(float2);
+  const size_t lds = (size_t)mx_lds<K>(a.tile) * sizeof(float2);
   if (t)
     hipExtLaunchKernelGGL((k_pers_body_mx<K, BC, MASKED>), dim3(blocks), dim3(threads), lds, s, t->start, t->stop, 0, a);
   else
@@ -625,6 +630,7 @@ static df_status fire_many(df_graph *g, int32_t n_actors, const int32_t *actors,
       d.ctrl_idx = fc.idx;
       d.ctrl_mask = fc.mask;
       d.h = a.h;
+      d.ht = a.ht;
       d.hist = a.hist;
       d.r = a.dp.firing_size;
       d.B_max = a.dp.n_branches_max;

@@ -138,6 +138,7 @@ extern "C" df_status df_graph_create(df_graph **out, int device, void *stream) {
 
 static void free_actor(Actor &a) {
   (void)hipFree(a.h);
+  (void)hipFree(a.ht);
   (void)hipFree(a.hist);
   (void)hipFree(a.order);
   (void)hipFree(a.corr);
@@ -353,7 +354,8 @@ extern "C" df_status df_actor_create(df_graph *g, df_actor_kind kind, const void
     a.dp.coeffs = nullptr;
     const size_t hb = sizeof(float2) * p.n_branches_max * p.n_taps;
     const size_t sb = sizeof(float2) * p.n_branches_max * std::max(p.n_taps - 1, 1);
-    if ((e = hipMalloc(&a.h, hb)) != hipSuccess || (e = hipMalloc(&a.hist, sb)) != hipSuccess ||
+    if ((e = hipMalloc(&a.h, hb)) != hipSuccess || (e = hipMalloc(&a.ht, coef_rows_bytes(p.n_taps))) != hipSuccess ||
+        (e = hipMalloc(&a.hist, sb)) != hipSuccess ||
         (e = hipMalloc(&a.scan[0].last, sizeof(int64_t) * p.n_branches_max)) != hipSuccess ||
         (e = hipMalloc(&a.scan[1].last, sizeof(int64_t) * p.n_branches_max)) != hipSuccess ||
         (e = hipMalloc(&a.scan[0].err, sizeof(int32_t))) != hipSuccess ||
@@ -363,10 +365,12 @@ extern "C" df_status df_actor_create(df_graph *g, df_actor_kind kind, const void
       return fail(g, DF_ENOMEM, "actor allocation failed");
     }
     e = hipMemcpy(a.h, p.coeffs, hb, p.coeffs_on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = launch_coef_rows(a.h, a.ht, p.n_branches_max, p.n_taps, nullptr);
     if (e == hipSuccess) e = hipMemset(a.hist, 0, sb);
     if (e == hipSuccess) e = hipMemset(a.ticket, 0, sizeof(int32_t));
     for (auto &sl : a.scan)
       if (e == hipSuccess) e = hipMemset(sl.err, 0, sizeof(int32_t));
+    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);   // the graph's stream does not wait for this one
     if (e != hipSuccess) {
       free_actor(a);
       return fail_hip(g, e, "actor init");
@@ -676,11 +680,10 @@ df_status dfh::dpd_enqueue(df_graph *g, Actor &a, int64_t n, bool may_run_ahead)
   Fifo &fy = g->fifos[a.ports[DF_DPD_OUT]];
   const int64_t r = a.dp.firing_size;
   const int bm = a.dp.n_branches_max, M = a.dp.n_taps;
-  // tiled bodies: the head pass fills the prev/off tables from the group
-  // table, and places the firings in processing order (grouped by Horner
-  // length: pays off only for many workgroups)
-  const bool heads_tables = dpd_tiled_shape(M);
-  const bool ordered = heads_tables && n > 64;
+  // the head pass fills the prev/off tables from the group table, and places
+  // the firings in processing order (grouped by Horner length: pays off only
+  // for many workgroups)
+  const bool ordered = n > 64;
   const int64_t pos = fc.read_h;
 
   // this batch's scan: the one run ahead if it assumed this batch, else a new one
@@ -702,7 +705,7 @@ df_status dfh::dpd_enqueue(df_graph *g, Actor &a, int64_t n, bool may_run_ahead)
   }
   Actor::ScanSlot &sl = a.scan[s];
   if (!scanned)
-    HIPCHK(g, launch_scan(scan_args(g, a, sl, pos, n, ordered, g->err_dev), g->stream, !heads_tables, false));
+    HIPCHK(g, launch_scan(scan_args(g, a, sl, pos, n, ordered, g->err_dev), g->stream, false, false));
   ScanArgs sa{};                                     // where the scan left its tables
   sa.n_segs = 1;
   sa.seg_firings = n;
@@ -717,6 +720,7 @@ df_status dfh::dpd_enqueue(df_graph *g, Actor &a, int64_t n, bool may_run_ahead)
   da.y_idx = fy.idx;
   da.y_mask = fy.mask;
   da.h = a.h;
+  da.ht = a.ht;
   da.hist = a.hist;
   da.B = sl.B;
   da.order = ordered ? a.order : nullptr;
@@ -732,19 +736,17 @@ df_status dfh::dpd_enqueue(df_graph *g, Actor &a, int64_t n, bool may_run_ahead)
   da.mx = g->body_mx;
   da.err = g->err_dev;
   da.err_ahead = err_ahead;
-  if (heads_tables) {
-    da.grp = sa.grp;
-    da.tab_prev = a.prev;
-    da.tab_off = a.off;
-    da.hist_mode = a.dp.history_mode;
-    da.obase = sa.lgrp;
-    da.order_out = ordered ? a.order : nullptr;
-  }
+  da.grp = sa.grp;
+  da.tab_prev = a.prev;
+  da.tab_off = a.off;
+  da.hist_mode = a.dp.history_mode;
+  da.obase = sa.lgrp;
+  da.order_out = ordered ? a.order : nullptr;
   // The next batch's scan, if its control tokens are already in the channel
   // (pushed before this batch): run by extra workgroups of the head pass into
   // the other slot (whose last readers, the previous batch's kernels, are
   // done), beside this batch's head corrections.
-  const bool run_ahead = may_run_ahead && !g->no_scan_ahead && heads_tables && n > 64 &&
+  const bool run_ahead = may_run_ahead && !g->no_scan_ahead && n > 64 &&
                          fc.write_lo - (pos + n) >= n;
   if (run_ahead) {
     const int t = s ^ 1;
@@ -765,17 +767,11 @@ df_status dfh::dpd_enqueue(df_graph *g, Actor &a, int64_t n, bool may_run_ahead)
   ca.B_max = bm;
   ca.M = M;
   ca.err = g->err_dev;
-  // the tiled body's last workgroup commits the batch; the generic body
-  // leaves it to a kernel of its own
-  const bool fused = dpd_tiled_shape(M);
-  if (fused) {
-    da.ticket = a.ticket;
-    da.commit = ca;
-  }
+  da.ticket = a.ticket;                              // the body's last workgroup commits the batch
+  da.commit = ca;
   KTiming kt;
   HIPCHK(g, prof_pair(g, &kt, (int)(&a - g->actors.data())));
   HIPCHK(g, launch_dpd_body(da, g->stream, g->tile, g->outputs_per_thread, g->prof ? &kt : nullptr));
-  if (!fused) HIPCHK(g, launch_dpd_commit(ca, g->stream));
 
   fc.read_h += n;
   fx.read_h += n * r;
@@ -1209,7 +1205,8 @@ extern "C" df_status df_set_tile(df_graph *g, int32_t tile_outputs, int32_t outp
   ENTER(g);
   if (outputs_per_thread != 0 && outputs_per_thread != 4 && outputs_per_thread != 8)
     return fail(g, DF_EINVAL, "outputs_per_thread must be 4 or 8");
-  const int k = outputs_per_thread ? outputs_per_thread : g->outputs_per_thread;
+  const int set = outputs_per_thread ? outputs_per_thread : g->outputs_per_thread;
+  const int k = set ? set : 4;
   if (tile_outputs != 0 && (tile_outputs < 64 * k || tile_outputs > 512 * k || tile_outputs % (64 * k)))
     return fail(g, DF_EINVAL, "tile_outputs must be a multiple of %d in %d..%d", 64 * k, 64 * k, 512 * k);
   if (blocks_per_cu < 0 || blocks_per_cu > 16) return fail(g, DF_EINVAL, "blocks_per_cu outside 0..16");

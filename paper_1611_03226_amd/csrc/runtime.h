@@ -47,6 +47,7 @@ struct Actor {
   // predistortion
   df_dpd_params dp{};
   float2 *h = nullptr;       // [B_max][M]
+  float2 *ht = nullptr;      // the same, tap-major (launch_coef_rows)
   float2 *hist = nullptr;    // [B_max][M-1] carried branch histories
   int64_t scratch_n = 0;
   int32_t *order = nullptr;  // [scratch_n][2] (firing, branch set) grouped by Horner length
@@ -95,7 +96,7 @@ struct df_graph {
   int64_t *idx_pool = nullptr;   // device [kMaxFifos][kCtrWords] channel counter slots
   int32_t *err_dev = nullptr;    // sticky device error word
   int tile = 0;                  // 0 = default
-  int outputs_per_thread = 4;
+  int outputs_per_thread = 0;    // 0 = default (by the batch: launch_dpd_body)
   bool body_mx = false;          // M = 16 bodies on the matrix cores (DFHIP_BODY=mx)
   int blocks_per_cu = 0;          // persistent grid; 0 = default
   dfh::Persistent *pers = nullptr;
@@ -131,16 +132,17 @@ void destroy_persistent(df_graph *g);
 
 // Scratch of one stateless predistortion forward call: validated branch
 // counts B [n], history sources prev [B_max][n], scan group table grp, head
-// corrections corr [n][M-1] (n = S*len/r firings; without control tokens only
-// corr, [S][M-1]).  Nothing in it needs to start at zero.
+// corrections corr [n][M-1] (n = S*len/r firings; without control tokens none
+// of them is used and corr has [S][M-1]), tap-major coefficients ht.  Nothing in it needs to start at zero.
 struct FwdScratch {
   int32_t *B = nullptr;
   int64_t *prev = nullptr;
   void *grp = nullptr;        // scan scratch (scan_scratch_bytes)
   float2 *corr = nullptr;
+  float2 *ht = nullptr;       // tap-major coefficients
 };
 struct FwdScratchSize {
-  size_t B = 0, prev = 0, grp = 0, corr = 0;
+  size_t B = 0, prev = 0, grp = 0, corr = 0, ht = 0;
 };
 FwdScratchSize dpd_forward_scratch_size(int64_t S, int64_t len, int64_t r, int32_t B_max, int32_t M,
                                         bool with_ctrl);

@@ -82,6 +82,7 @@ FwdScratchSize dfh::dpd_forward_scratch_size(int64_t S, int64_t len, int64_t r, 
                                              bool with_ctrl) {
   FwdScratchSize z{};
   const int64_t L1 = std::max(M - 1, 1);
+  z.ht = coef_rows_bytes(M);
   if (!with_ctrl) {
     z.corr = sizeof(float2) * L1 * S;
     return z;
@@ -107,18 +108,21 @@ hipError_t dfh::dpd_forward_enqueue(const FwdScratch &sc, hipStream_t s, const v
   a.h = (const float2 *)h;
   a.B_max = B_max;
   a.M = M;
-  a.corr = sc.corr;
+  a.ht = sc.ht;
   a.mx = dpd_body_mx_env();
   if (!ctrl) {
-    // All branches active in every firing: a row is one convolution.
+    // All branches active in every firing: a row is one convolution from
+    // zero state, so there are no histories to correct for.
     a.B_const = B_max;
     a.seg_firings = 1;
     a.n_firings = S;
     a.r = len;
-    hipError_t e = launch_dpd_heads(a, s);
-    if (e == hipSuccess) e = launch_dpd_body(a, s, 0, 4);
+    hipError_t e = launch_coef_rows(a.h, a.ht, B_max, M, s);
+    if (e == hipSuccess) e = launch_dpd_body(a, s, 0, 0);
     return e;
   }
+  a.corr = sc.corr;
+  a.fill_ht = 1;
   const int64_t nf = len / r, n = S * nf;
   ScanArgs sa{};
   sa.ctrl = ctrl;
@@ -143,7 +147,7 @@ hipError_t dfh::dpd_forward_enqueue(const FwdScratch &sc, hipStream_t s, const v
   a.n_firings = n;
   a.r = r;
   e = launch_dpd_heads(a, s);
-  if (e == hipSuccess) e = launch_dpd_body(a, s, 0, 4);
+  if (e == hipSuccess) e = launch_dpd_body(a, s, 0, 0);
   return e;
 }
 
@@ -163,14 +167,22 @@ extern "C" df_status df_dpd_forward(void *stream, const void *x, const int32_t *
   if (st || nothing) return st;
   hipStream_t s = (hipStream_t)stream;
   const FwdScratchSize z = dpd_forward_scratch_size(S, len, r, B_max, M, ctrl != nullptr);
-  FwdScratch sc{};
-  hipError_t e = hipMallocAsync((void **)&sc.corr, z.corr, s);
-  if (e == hipSuccess && z.B) e = hipMallocAsync((void **)&sc.B, z.B, s);
-  if (e == hipSuccess && z.prev) e = hipMallocAsync((void **)&sc.prev, z.prev, s);
-  if (e == hipSuccess && z.grp) e = hipMallocAsync((void **)&sc.grp, z.grp, s);
-  if (e == hipSuccess) e = dpd_forward_enqueue(sc, s, x, ctrl, h, y, S, len, r, B_max, M, hist);
-  for (void *p : {(void *)sc.corr, (void *)sc.B, (void *)sc.prev, (void *)sc.grp})
-    if (p) (void)hipFreeAsync(p, s);
+  // one allocation holds every region (an allocation and its release cost
+  // more host time than a launch)
+  const auto al = [](size_t v) { return (v + 255) & ~(size_t)255; };
+  char *p = nullptr;
+  hipError_t e = hipMallocAsync((void **)&p, al(z.corr) + al(z.ht) + al(z.B) + al(z.prev) + z.grp, s);
+  if (e == hipSuccess) {
+    FwdScratch sc{};
+    sc.corr = (float2 *)p;
+    sc.ht = (float2 *)(p + al(z.corr));
+    char *q = p + al(z.corr) + al(z.ht);
+    if (z.B) sc.B = (int32_t *)q;
+    if (z.prev) sc.prev = (int64_t *)(q + al(z.B));
+    if (z.grp) sc.grp = q + al(z.B) + al(z.prev);
+    e = dpd_forward_enqueue(sc, s, x, ctrl, h, y, S, len, r, B_max, M, hist);
+  }
+  if (p) (void)hipFreeAsync(p, s);
   if (e != hipSuccess) return fail_hip(nullptr, e, "df_dpd_forward");
   return DF_OK;
 }
