@@ -4,15 +4,20 @@
 // threshold) and Med (5-pixel median).  Each batch covers n_frames
 // consecutive tokens of the actor's channels; see MdpArgs.
 //
-// Word path (width a multiple of 4): a work item is a strip of V words (4V
-// pixels; V = 4 when the width is a multiple of 16, else 1) of kRun
-// consecutive output rows of one frame; consecutive lanes take consecutive
-// strips, so every row load of a wave is one contiguous run.  The vertical
-// window slides down the item in registers; the words left and right of the
-// strip give the horizontal halo, with the nearest in-frame pixel repeated
-// at the left and right frame edges.  Pixels are processed four per word in
-// 16-bit lanes (md_swar.h).  Any other width takes the byte path: one thread
-// per pixel.
+// Word path (any width from 20 on, and 4, 8, 12, 16): a work item is a strip
+// of V words (4V pixels; V = 1 below width 16, else 4) of kRun consecutive
+// output rows of one frame; consecutive lanes take consecutive strips, so
+// every row load of a wave is one contiguous run.  The last strip of a row
+// ends at the row's last pixel and may overlap its neighbour (whose pixels it
+// rewrites with the same values); rows start at any byte, which the loads and
+// stores of words allow.  The vertical window slides down the item in
+// registers; the words left and right of the strip give the horizontal halo,
+// with the nearest in-frame pixel repeated at the left and right frame edges.
+// Pixels are processed four per word in 16-bit lanes (md_swar.h).  Any other
+// width takes the byte path: one thread per pixel (64 frames of 854x480:
+// Gauss 121 us and Med 73 us by bytes, 22 and 21 us by strips;
+// 128 frames of 1000x600: 70 and 52 us with one word per strip, 60 and 45 with
+// four).
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
@@ -39,15 +44,21 @@ __device__ inline uint8_t *out_frame(uint8_t *ring, const int64_t *idx, int64_t 
   return ring + write_slot(idx[1] + f, map) * WH;
 }
 
-typedef __attribute__((address_space(1))) uint32_t gu32;
+typedef __attribute__((address_space(1))) uint8_t gu8;
+// words and vectors of them at any byte address
+typedef uint32_t __attribute__((aligned(1))) u32_any;
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef u32x4 __attribute__((aligned(1))) u32x4_any;
+typedef __attribute__((address_space(1))) u32_any gu32_any;
+typedef __attribute__((address_space(1))) u32x4_any gu32x4_any;
 
 // A global pointer that is the same in every lane, held in scalar registers,
 // so that loads and stores use the scalar base + 32-bit vector offset form.
-__device__ inline gu32 *uniform_ptr(const void *p) {
+__device__ inline gu8 *uniform_ptr(const void *p) {
   const uint64_t v = (uint64_t)p;
   const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
   const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  return (gu32 *)(((uint64_t)hi << 32) | lo);
+  return (gu8 *)(((uint64_t)hi << 32) | lo);
 }
 
 // Frame and part of a word-path workgroup.  Workgroups are dispatched to the
@@ -67,51 +78,52 @@ __device__ inline FramePart frame_part(uint32_t b, uint32_t bpf) {
   return {b / bpf, b % bpf};
 }
 
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(1))) u32x4 gu32x4;
-
-// Word columns of a word-path strip: its first word c0, V words, and the
-// clamped neighbour words; at a frame edge the perm selectors repeat the
-// edge pixel instead of using the missing neighbour, so every load is
-// unconditional.
+// Pixel columns of a word-path strip: its first pixel x0 (4V of them), and
+// the neighbour words, kept inside the row; at a frame edge the perm
+// selectors repeat the edge pixel instead of using the missing neighbour, so
+// every load is unconditional.  `row` is the byte offset of a row.
 template <int V>
 struct Strip {
-  uint32_t c0, cl, cr;
-  bool left_edge, right_edge;
-  __device__ Strip(int s, int Wq) {
-    c0 = (uint32_t)(s * V);
-    left_edge = s == 0;
-    right_edge = (s + 1) * V == Wq;
-    cl = left_edge ? c0 : c0 - 1;
-    cr = right_edge ? c0 + V - 1 : c0 + V;
+  uint32_t x0, xl, xr;
+  bool left_edge;
+  int avail;                                // pixels of the row right of the strip
+  __device__ Strip(int s, int W) {
+    x0 = (uint32_t)min(4 * V * s, W - 4 * V);
+    left_edge = x0 == 0;                    // else x0 >= 4 (see word_path)
+    avail = W - (int)x0 - 4 * V;
+    xl = left_edge ? 0 : x0 - 4;
+    xr = avail ? (uint32_t)min((int)x0 + 4 * V, W - 4) : x0 + 4 * V - 4;
   }
   // w[0] = left neighbour word, w[1..V] = the strip, w[V+1] = right neighbour
-  __device__ void load(const gu32 *src, uint32_t row, uint32_t (&w)[V + 2]) const {
+  __device__ void load(const gu8 *src, uint32_t row, uint32_t (&w)[V + 2]) const {
     if constexpr (V == 4) {
-      const u32x4 m = *(const gu32x4 *)(src + row + c0);
+      const u32x4 m = *(const gu32x4_any *)(src + row + x0);
       w[1] = m.x;
       w[2] = m.y;
       w[3] = m.z;
       w[4] = m.w;
     } else {
-      w[1] = src[row + c0];
+      w[1] = *(const gu32_any *)(src + row + x0);
     }
-    w[0] = src[row + cl];
-    w[V + 1] = src[row + cr];
+    w[0] = *(const gu32_any *)(src + row + xl);
+    w[V + 1] = *(const gu32_any *)(src + row + xr);
   }
-  __device__ void store(gu32 *dst, uint32_t row, const uint32_t (&v)[V]) const {
+  __device__ void store(gu8 *dst, uint32_t row, const uint32_t (&v)[V]) const {
     if constexpr (V == 4) {
       u32x4 m;
       m.x = v[0];
       m.y = v[1];
       m.z = v[2];
       m.w = v[3];
-      __builtin_nontemporal_store(m, (gu32x4 *)(dst + row + c0));
+      __builtin_nontemporal_store(m, (gu32x4_any *)(dst + row + x0));
     } else {
-      __builtin_nontemporal_store(v[0], dst + row + c0);
+      __builtin_nontemporal_store(v[0], (gu32_any *)(dst + row + x0));
     }
   }
 };
+
+// Byte offset of frame row y (a frame has at most 2^32 bytes).
+__device__ inline uint32_t row_off(int y, int W) { return (uint32_t)y * (uint32_t)W; }
 
 // ------------------------------------------------------------------ Gauss
 
@@ -123,24 +135,24 @@ __global__ __launch_bounds__(kWordThreads) void k_gauss5_w(MdpArgs a, int64_t f0
   const FramePart fp = frame_part(blockIdx.x, (uint32_t)bpf);
   const int64_t f = f0 + __builtin_amdgcn_readfirstlane(fp.frame);
   const int32_t local = (int32_t)__builtin_amdgcn_readfirstlane(fp.part) * kWordThreads + (int32_t)threadIdx.x;
-  const int32_t Wq = a.W >> 2, Ws = Wq / V;
+  const int32_t Ws = (a.W + 4 * V - 1) / (4 * V);
   const int32_t sx = local % Ws, run = local / Ws;
   if (run >= n_runs) return;
   const int64_t WH = (int64_t)a.W * a.H;
-  const gu32 *src = uniform_ptr(in_frame(a.in0, a.in0_idx, a.in0_mask, f, WH));
-  gu32 *dst = uniform_ptr(out_frame(a.out0, a.out0_idx, a.out0_mask, f, WH));
-  gu32 *dst2 = TWO ? uniform_ptr(out_frame(a.out1, a.out1_idx, a.out1_mask, f, WH)) : nullptr;
+  const gu8 *src = uniform_ptr(in_frame(a.in0, a.in0_idx, a.in0_mask, f, WH));
+  gu8 *dst = uniform_ptr(out_frame(a.out0, a.out0_idx, a.out0_mask, f, WH));
+  gu8 *dst2 = TWO ? uniform_ptr(out_frame(a.out1, a.out1_idx, a.out1_mask, f, WH)) : nullptr;
   const int H = a.H;
   const int y0 = FULL ? min(run * kRun, H - kRun) : run * kRun;
   const int yend = min(y0 + kRun, H);
-  const Strip<V> st(sx, Wq);
-  const uint32_t sel_l0 = swar::win2_left(st.left_edge), sel_rV = swar::win2_right(st.right_edge);
+  const Strip<V> st(sx, a.W);
+  const uint32_t sel_l0 = swar::win2_left(st.left_edge), sel_rV = swar::win2_right_avail(st.avail);
   const uint32_t sel_l = swar::win2_left(false), sel_r = swar::win2_right(false);
   uint32_t he[V][5] = {}, ho[V][5] = {}, mid[V][5] = {};
 #pragma unroll
   for (int r = 0; r < kRun + 4; ++r) {
     uint32_t w[V + 2];
-    st.load(src, (uint32_t)(min(max(y0 - 2 + r, 0), H - 1) * Wq), w);
+    st.load(src, row_off(min(max(y0 - 2 + r, 0), H - 1), a.W), w);
 #pragma unroll
     for (int j = 0; j < V; ++j) {
 #pragma unroll
@@ -165,8 +177,8 @@ __global__ __launch_bounds__(kWordThreads) void k_gauss5_w(MdpArgs a, int64_t f0
                                                  swar::vround5(ho[j][0], ho[j][1], ho[j][2], ho[j][3], ho[j][4]));
           v[j] = filtered ? filt : mid[j][2];
         }
-        st.store(dst, (uint32_t)(y * Wq), v);
-        if (TWO) st.store(dst2, (uint32_t)(y * Wq), v);
+        st.store(dst, row_off(y, a.W), v);
+        if (TWO) st.store(dst2, row_off(y, a.W), v);
       }
     }
   }
@@ -196,20 +208,23 @@ __global__ __launch_bounds__(kMdThreads) void k_gauss5_b(MdpArgs a, int64_t f0, 
 
 // ------------------------------------------------------------------ Thres
 
+// 16 pixels per thread; the last thread's end at the frame's last pixel (and
+// may overlap its neighbour's); a frame starts at any byte.
 __global__ __launch_bounds__(kMdThreads) void k_thres_v(MdpArgs a, int64_t f0, int32_t bpf) {
   const int64_t f = f0 + __builtin_amdgcn_readfirstlane(blockIdx.x / (uint32_t)bpf);
   const int64_t q = (int64_t)(blockIdx.x % (uint32_t)bpf) * kMdThreads + threadIdx.x;
   const int64_t WH = (int64_t)a.W * a.H;
-  if (q >= WH / 16) return;
-  const u32x4 c = __builtin_nontemporal_load((const u32x4 *)in_frame(a.in0, a.in0_idx, a.in0_mask, f, WH) + q);
-  const u32x4 p = __builtin_nontemporal_load((const u32x4 *)in_frame(a.in1, a.in1_idx, a.in1_mask, f, WH) + q);
+  if (16 * q >= WH) return;
+  const int64_t at = min(16 * q, WH - 16);
+  const u32x4 c = __builtin_nontemporal_load((const u32x4_any *)(in_frame(a.in0, a.in0_idx, a.in0_mask, f, WH) + at));
+  const u32x4 p = __builtin_nontemporal_load((const u32x4_any *)(in_frame(a.in1, a.in1_idx, a.in1_mask, f, WH) + at));
   const uint32_t t = (uint32_t)a.thr;
   u32x4 o;
   o.x = swar::absdiff_gt(c.x, p.x, t);
   o.y = swar::absdiff_gt(c.y, p.y, t);
   o.z = swar::absdiff_gt(c.z, p.z, t);
   o.w = swar::absdiff_gt(c.w, p.w, t);
-  __builtin_nontemporal_store(o, (u32x4 *)out_frame(a.out0, a.out0_idx, a.out0_mask, f, WH) + q);
+  __builtin_nontemporal_store(o, (u32x4_any *)(out_frame(a.out0, a.out0_idx, a.out0_mask, f, WH) + at));
 }
 
 __global__ __launch_bounds__(kMdThreads) void k_thres_b(MdpArgs a, int64_t f0, int32_t bpf) {
@@ -230,23 +245,23 @@ __global__ __launch_bounds__(kWordThreads) void k_med5_w(MdpArgs a, int64_t f0, 
   const FramePart fp = frame_part(blockIdx.x, (uint32_t)bpf);
   const int64_t f = f0 + __builtin_amdgcn_readfirstlane(fp.frame);
   const int32_t local = (int32_t)__builtin_amdgcn_readfirstlane(fp.part) * kWordThreads + (int32_t)threadIdx.x;
-  const int32_t Wq = a.W >> 2, Ws = Wq / V;
+  const int32_t Ws = (a.W + 4 * V - 1) / (4 * V);
   const int32_t sx = local % Ws, run = local / Ws;
   if (run >= n_runs) return;
   const int64_t WH = (int64_t)a.W * a.H;
-  const gu32 *src = uniform_ptr(in_frame(a.in0, a.in0_idx, a.in0_mask, f, WH));
-  gu32 *dst = uniform_ptr(out_frame(a.out0, a.out0_idx, a.out0_mask, f, WH));
+  const gu8 *src = uniform_ptr(in_frame(a.in0, a.in0_idx, a.in0_mask, f, WH));
+  gu8 *dst = uniform_ptr(out_frame(a.out0, a.out0_idx, a.out0_mask, f, WH));
   const int H = a.H;
   const int y0 = FULL ? min(run * kRun, H - kRun) : run * kRun;
   const int yend = min(y0 + kRun, H);
-  const Strip<V> st(sx, Wq);
-  const uint32_t sel_l0 = swar::win1_left(st.left_edge), sel_rV = swar::win1_right(st.right_edge);
+  const Strip<V> st(sx, a.W);
+  const uint32_t sel_l0 = swar::win1_left(st.left_edge), sel_rV = swar::win1_right_avail(st.avail);
   const uint32_t sel_l = swar::win1_left(false), sel_r = swar::win1_right(false);
   uint32_t up[V] = {}, cen[V + 2] = {};   // row above the centre row; centre row with its neighbour words
 #pragma unroll
   for (int r = 0; r < kRun + 2; ++r) {
     uint32_t w[V + 2];
-    st.load(src, (uint32_t)(min(max(y0 - 1 + r, 0), H - 1) * Wq), w);
+    st.load(src, row_off(min(max(y0 - 1 + r, 0), H - 1), a.W), w);
     if (r >= 2) {
       const int y = y0 + r - 2;
       if (FULL || y < yend) {
@@ -258,7 +273,7 @@ __global__ __launch_bounds__(kWordThreads) void k_med5_w(MdpArgs a, int64_t f0, 
           const uint32_t R = swar::perm(cen[j + 2], cen[j + 1], j == V - 1 ? sel_rV : sel_r);
           v[j] = swar::med5_bytes(cen[j + 1], up[j], w[j + 1], L, R);
         }
-        st.store(dst, (uint32_t)(y * Wq), v);
+        st.store(dst, row_off(y, a.W), v);
       }
     }
     // the current centre row is the row above the next one
@@ -484,10 +499,18 @@ __global__ void k_advance_n(Counters c, int n, int32_t *err) {
 
 namespace {
 
+// Words per strip of the word path, or 0: the byte path.  With four words the
+// last strip starts at pixel W - 16, which must be 0 or leave room for the
+// word on its left (W >= 20).
+int word_path(int32_t W) {
+  if (W >= 20 || W == 16) return 4;
+  return W % 4 == 0 ? 1 : 0;
+}
+
 template <int V>
 hipError_t launch_gauss5_words(const MdpArgs &a, hipStream_t s, const KTiming *t) {
   const int32_t n_runs = div_up32(a.H, kRun);
-  const int32_t bpf = div_up32((int64_t)n_runs * (a.W / (4 * V)), kWordThreads);
+  const int32_t bpf = div_up32((int64_t)n_runs * div_up32(a.W, 4 * V), kWordThreads);
   const bool full = a.H >= kRun;
   if (a.out1)
     return full ? launch_frames(k_gauss5_w<V, true, true>, kWordThreads, a, bpf, s, t, n_runs)
@@ -499,7 +522,7 @@ hipError_t launch_gauss5_words(const MdpArgs &a, hipStream_t s, const KTiming *t
 template <int V>
 hipError_t launch_med5_words(const MdpArgs &a, hipStream_t s, const KTiming *t) {
   const int32_t n_runs = div_up32(a.H, kRun);
-  const int32_t bpf = div_up32((int64_t)n_runs * (a.W / (4 * V)), kWordThreads);
+  const int32_t bpf = div_up32((int64_t)n_runs * div_up32(a.W, 4 * V), kWordThreads);
   return a.H >= kRun ? launch_frames(k_med5_w<V, true>, kWordThreads, a, bpf, s, t, n_runs)
                      : launch_frames(k_med5_w<V, false>, kWordThreads, a, bpf, s, t, n_runs);
 }
@@ -508,22 +531,22 @@ hipError_t launch_med5_words(const MdpArgs &a, hipStream_t s, const KTiming *t) 
 
 hipError_t launch_gauss5(const MdpArgs &a, hipStream_t s, const KTiming *t) {
   if (a.n_frames <= 0) return hipSuccess;
-  if (a.W % 16 == 0) return launch_gauss5_words<4>(a, s, t);
-  if (a.W % 4 == 0) return launch_gauss5_words<1>(a, s, t);
+  if (word_path(a.W) == 4) return launch_gauss5_words<4>(a, s, t);
+  if (word_path(a.W) == 1) return launch_gauss5_words<1>(a, s, t);
   return launch_frames(k_gauss5_b, kMdThreads, a, div_up32((int64_t)a.W * a.H, kMdThreads), s, t);
 }
 
 hipError_t launch_thres(const MdpArgs &a, hipStream_t s, const KTiming *t) {
   if (a.n_frames <= 0) return hipSuccess;
   const int64_t WH = (int64_t)a.W * a.H;
-  if (WH % 16 == 0) return launch_frames(k_thres_v, kMdThreads, a, div_up32(WH / 16, kMdThreads), s, t);
+  if (WH >= 16) return launch_frames(k_thres_v, kMdThreads, a, div_up32(div_up32(WH, 16), kMdThreads), s, t);
   return launch_frames(k_thres_b, kMdThreads, a, div_up32(WH, kMdThreads), s, t);
 }
 
 hipError_t launch_med5(const MdpArgs &a, hipStream_t s, const KTiming *t) {
   if (a.n_frames <= 0) return hipSuccess;
-  if (a.W % 16 == 0) return launch_med5_words<4>(a, s, t);
-  if (a.W % 4 == 0) return launch_med5_words<1>(a, s, t);
+  if (word_path(a.W) == 4) return launch_med5_words<4>(a, s, t);
+  if (word_path(a.W) == 1) return launch_med5_words<1>(a, s, t);
   return launch_frames(k_med5_b, kMdThreads, a, div_up32((int64_t)a.W * a.H, kMdThreads), s, t);
 }
 

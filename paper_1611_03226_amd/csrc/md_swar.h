@@ -54,6 +54,18 @@ __host__ __device__ inline uint32_t win2_right(bool edge) { return edge ? 0x0303
 __host__ __device__ inline uint32_t win1_left(bool edge) { return edge ? 0x06050404u : 0x06050403u; }
 __host__ __device__ inline uint32_t win1_right(bool edge) { return edge ? 0x03030201u : 0x04030201u; }
 
+// The right selectors with `avail` in-frame pixels to the right of p3.  With
+// 1..3 of them r is the row's last word, in which p4 is byte 4 - avail.
+__host__ __device__ inline uint32_t win2_right_avail(int avail) {
+  if (avail <= 0 || avail >= 4) return win2_right(avail <= 0);
+  const uint32_t p4 = 8u - (uint32_t)avail, p5 = avail > 1 ? p4 + 1 : p4;
+  return 0x0302u | (p4 << 16) | (p5 << 24);
+}
+__host__ __device__ inline uint32_t win1_right_avail(int avail) {
+  if (avail <= 0 || avail >= 4) return win1_right(avail <= 0);
+  return 0x00030201u | ((8u - (uint32_t)avail) << 24);
+}
+
 // Horizontal 5-tap binomial sums (1,4,6,4,1) of four pixels p0..p3 given
 // the 8-byte window X = (p-2, p-1, p0, p1, p2, p3, p4, p5) as lo (bytes
 // 0..3) and hi (bytes 4..7).  Returns the sums of (p0, p2) in *even and of
