@@ -191,7 +191,7 @@ struct MotionArgs {
   const int64_t *index_idx;
   int64_t index_mask;
   int32_t *count;         // [n] opened-mask counts
-  const int64_t *emit_off;// [n+1] exclusive scan of emit flags (emit pass)
+  const int64_t *emit_off;// [n+3] exclusive scan of emit flags and the write positions before the batch (emit pass)
   uint32_t *bits;         // bit-packed opened masks [n][H][W/32] (count pass)
   int64_t n;
   int64_t frame_base;     // global index of firing 0
@@ -199,6 +199,30 @@ struct MotionArgs {
   int32_t permille;
   int32_t words_per_row;  // W/32 rounded up
 };
+
+// Write counters of a motion actor's mask and index channels, in page-locked
+// host memory: the number of the batch whose commit wrote the word in its high
+// half, the counter's low 32 bits in its low half (one store each, so nothing
+// orders them).
+struct MotionCounts {
+  uint64_t word[2];
+};
+
+// Emit scan and commit of one batch (see k_emit_commit).
+struct MotionCommitArgs {
+  const int32_t *count;   // [n]
+  int64_t n;
+  int64_t thresh;         // emit when 1000 * count >= thresh
+  int64_t *emit_off;      // [n+3]
+  int64_t *cur_idx, *prev_idx, *out_idx, *index_idx;
+  MotionCounts *host;     // or nullptr
+  uint32_t seq;
+  int32_t *err;
+};
+
+// Bytes allocated behind the last token of a byte channel and behind a motion
+// actor's state: 16-byte accesses to the end of a frame stay inside.
+constexpr size_t kFrameSlack = 64;
 
 // ---------------------------------------------------------------- adjoint
 // Coefficient adjoint over firings laid out as in DpdArgs' stateless mode.
@@ -332,8 +356,7 @@ hipError_t launch_dpd_body(const DpdArgs &a, hipStream_t s, int tile, int output
 hipError_t launch_advance(int64_t *idx, int64_t delta, int32_t *err, hipStream_t s);
 hipError_t launch_fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t s);
 hipError_t launch_motion_count(const MotionArgs &a, hipStream_t s);
-hipError_t launch_motion_emit_scan(const int32_t *count, int64_t n, int64_t emit_threshold,
-                                   int64_t *emit_off, hipStream_t s);
+hipError_t launch_motion_emit_commit(const MotionCommitArgs &a, hipStream_t s);
 hipError_t launch_motion_emit(const MotionArgs &a, hipStream_t s);
 hipError_t launch_adj(const AdjArgs &a, hipStream_t s);
 hipError_t launch_stream_copy(const void *src, void *dst, int64_t bytes, hipStream_t s);
@@ -342,7 +365,5 @@ hipError_t launch_stream_copy(const void *src, void *dst, int64_t bytes, hipStre
 hipError_t launch_hbm_ref(int mode, const void *src, void *dst, int64_t bytes, hipStream_t s);
 hipError_t launch_mp_adj(const float2 *u, const float2 *a, const float2 *g, float2 *Gu, int64_t n_streams,
                          int64_t len, int K, int Q, hipStream_t s);
-hipError_t launch_motion_commit(const int64_t *emit_off, int64_t n, int64_t *cur_idx, int64_t *prev_idx,
-                                int64_t *out_idx, int64_t *index_idx, int32_t *err, hipStream_t s);
 
 }  // namespace dfh

@@ -11,9 +11,8 @@
 // Emission depends on the whole frame, so a batch runs
 //   bits pass:   opened masks, bit-packed (32 pixels per word, transposed
 //                bit order below), and counts
-//   emit scan:   output slots of the emitted frames
+//   emit scan:   output slots of the emitted frames, channel indices
 //   expand pass: emitted masks as 0/255 bytes at their output slots
-//   commit:      channel indices.
 //
 // Bits pass layout: a wavefront owns a band of rows of one frame chunk and
 // one chunk of 62 consecutive 32-pixel words (lane l <-> word chunk*62+l-1;
@@ -35,31 +34,6 @@
 namespace dfh {
 
 constexpr int MW_CHUNK = 62;   // output words per wavefront
-
-// 32 pixels of row y starting at pixel x0 (x0 < W); bytes past the row end
-// read as 0.  `fast`: 16-byte loads (row starts and the word are aligned and
-// the word lies inside the row).
-__device__ __forceinline__ void load_word(const uint8_t *frame, int y, int x0, int W, bool fast, uint32_t (&v)[8]) {
-  const uint8_t *p = frame + (int64_t)y * W + x0;
-  if (fast) {
-    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-    const u32x4 a = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
-    const u32x4 b = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p + 16));
-    v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
-    v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
-  } else {
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      uint32_t w = 0;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int x = x0 + 4 * k + i;
-        if (x < W) w |= (uint32_t)p[4 * k + i] << (8 * i);
-      }
-      v[k] = w;
-    }
-  }
-}
 
 typedef short i16x2 __attribute__((ext_vector_type(2)));
 
@@ -130,27 +104,25 @@ __device__ __forceinline__ uint32_t thresh_tbits(const Spread &c, const Spread &
   return ~keep;
 }
 
-// Row y of the F+1 frames a wavefront needs: buf[f] is the previous frame of
-// frame f and buf[f+1] its current frame (self-delay form: frames j0-1 ..
-// j0+F-1 of the input channel, the first from the state for j0 = 0; the
-// two-channel form has F = 1: buf[0] from the PREV channel, buf[1] from CUR).
-// Every load is unconditional: callers clamp y into the frame and point the
-// frames past the batch at its last frame (those results are masked).
-template <int F, bool FAST>
-__device__ __forceinline__ void load_rows(const uint8_t *const (&fr)[F + 1], int y, int x0, int W,
-                                          uint32_t (&buf)[F + 1][8]) {
-#pragma unroll
-  for (int f = 0; f <= F; ++f) load_word(fr[f], y, x0, W, FAST, buf[f]);
-}
+// 16 bytes at any byte address
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef u32x4 __attribute__((aligned(1))) u32x4_any;
 
-// Coalesced form of one row of the F+1 frames (W a multiple of 32): the
-// wavefront's 64 words are the 2 KiB from byte xs of the row; it loads them
-// as two contiguous KiB spans (lane l: 16 bytes at xs + 16 l and at
-// xs + 1024 + 16 l; spans outside the row read as 0) ...
+// One row of the F+1 frames a wavefront needs: fr[f] is the previous frame of
+// frame f and fr[f+1] its current frame (self-delay form: frames j0-1 ..
+// j0+F-1 of the input channel, the first from the state for j0 = 0; the
+// two-channel form has F = 1: fr[0] from the PREV channel, fr[1] from CUR).
+// Callers clamp y into the frame and point the frames past the batch at its
+// last frame (those results are masked).  The wavefront's 64 words are the
+// 2 KiB from byte xs of the row; it loads them as two contiguous KiB spans
+// (lane l: 16 bytes at xs + 16 l and at xs + 1024 + 16 l; nothing outside the
+// row) ...
+// A row may start at any byte, and the last 16 bytes of a row may reach past
+// its end: into the next row, or behind a channel's or state's last frame
+// into the kFrameSlack bytes allocated there.  Those pixels are masked.
 template <int F>
 __device__ __forceinline__ void load_spans(const uint8_t *const (&fr)[F + 1], int y, int xs, int W,
                                            uint32_t (&raw)[F + 1][8]) {
-  typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
   const int lane = threadIdx.x & 63;
 #pragma unroll
   for (int f = 0; f <= F; ++f)
@@ -158,7 +130,8 @@ __device__ __forceinline__ void load_spans(const uint8_t *const (&fr)[F + 1], in
     for (int h = 0; h < 2; ++h) {
       const int off = xs + 1024 * h + 16 * lane;
       u32x4 v = {0u, 0u, 0u, 0u};
-      if (off >= 0 && off < W) v = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(fr[f] + (int64_t)y * W + off));
+      if (off >= 0 && off < W)
+        v = __builtin_nontemporal_load(reinterpret_cast<const u32x4_any *>(fr[f] + (int64_t)y * W + off));
       raw[f][4 * h + 0] = v.x;
       raw[f][4 * h + 1] = v.y;
       raw[f][4 * h + 2] = v.z;
@@ -171,7 +144,6 @@ __device__ __forceinline__ void load_spans(const uint8_t *const (&fr)[F + 1], in
 // 32 l + 31 of the span) in buf.
 template <int F>
 __device__ __forceinline__ void stage_spans(uint32_t *stg, const uint32_t (&raw)[F + 1][8], uint32_t (&buf)[F + 1][8]) {
-  typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
   const int lane = threadIdx.x & 63;
 #pragma unroll
   for (int f = 0; f <= F; ++f)
@@ -204,7 +176,7 @@ __device__ __forceinline__ int xcd_item(int b, int n_items) {
   return k < n_items ? k : -1;
 }
 
-template <int F, bool FAST>
+template <int F>
 __global__ __launch_bounds__(64) void k_motion_bits(MotionArgs a, int rows, int n_bands, int n_chunks, int n_items) {
   const int lane = threadIdx.x;
   const int blk = xcd_item(blockIdx.x, n_items);
@@ -217,7 +189,6 @@ __global__ __launch_bounds__(64) void k_motion_bits(MotionArgs a, int rows, int 
   const int c = chunk * MW_CHUNK + lane - 1;
   const bool word_in = c >= 0 && c < wpr;
   const bool out_lane = lane >= 1 && lane <= MW_CHUNK && word_in;
-  const int x0 = word_in ? c * 32 : 0;
   const uint32_t valid = (c == wpr - 1 && (W & 31)) ? to_tbits((1u << (W & 31)) - 1u) : 0xFFFFFFFFu;
   const int64_t wh = (int64_t)W * H;
   const short t1s = (short)(a.thr + 1);
@@ -225,7 +196,7 @@ __global__ __launch_bounds__(64) void k_motion_bits(MotionArgs a, int rows, int 
   const int y0 = band * rows, y1 = min(H, y0 + rows);
   uint32_t *__restrict__ bits = a.bits;
 
-  // frame base pointers of the chunk (see load_rows)
+  // frame base pointers of the chunk (see load_spans)
   const uint8_t *fr[F + 1];
   {
     const int64_t Rc = a.cur_idx[0];
@@ -276,38 +247,24 @@ __global__ __launch_bounds__(64) void k_motion_bits(MotionArgs a, int rows, int 
     }
   };
 
-  // two register row buffers: the loads of the next row are in flight while
-  // the current row is processed (rows outside the frame are not loaded)
   uint32_t A[F + 1][8], Bf[F + 1][8];
 #pragma unroll
   for (int f = 0; f <= F; ++f)
 #pragma unroll
     for (int k = 0; k < 8; ++k) A[f][k] = Bf[f][k] = 0;
   const int ylast = y1 + 1;
-  if constexpr (FAST) {
-    // coalesced spans: the next row's loads are in flight (raw) while the
-    // current row, already staged through LDS, is processed
-    __shared__ uint32_t stg[F + 1][512];
-    const int xs = (chunk * MW_CHUNK - 1) * 32;
-    auto clampy = [&](int y) { return min(max(y, 0), H - 1); };
-    load_spans<F>(fr, clampy(y0 - 2), xs, W, Bf);
+  // the next row's loads are in flight (raw) while the current row, already
+  // staged through LDS, is processed
+  __shared__ uint32_t stg[F + 1][512];
+  const int xs = (chunk * MW_CHUNK - 1) * 32;
+  auto clampy = [&](int y) { return min(max(y, 0), H - 1); };
+  load_spans<F>(fr, clampy(y0 - 2), xs, W, Bf);
+  stage_spans<F>(&stg[0][0], Bf, A);
+  for (int y = y0 - 2; y <= ylast; ++y) {
+    if (y + 1 <= ylast) load_spans<F>(fr, clampy(y + 1), xs, W, Bf);
+    process(A, y);
+    if (y + 1 > ylast) break;
     stage_spans<F>(&stg[0][0], Bf, A);
-    for (int y = y0 - 2; y <= ylast; ++y) {
-      if (y + 1 <= ylast) load_spans<F>(fr, clampy(y + 1), xs, W, Bf);
-      process(A, y);
-      if (y + 1 > ylast) break;
-      stage_spans<F>(&stg[0][0], Bf, A);
-    }
-  } else {
-    auto rowload = [&](int y, uint32_t (&buf)[F + 1][8]) { load_rows<F, FAST>(fr, min(max(y, 0), H - 1), x0, W, buf); };
-    rowload(y0 - 2, A);
-    for (int y = y0 - 2; y <= ylast; y += 2) {
-      if (y + 1 <= ylast) rowload(y + 1, Bf);
-      process(A, y);
-      if (y + 1 > ylast) break;
-      if (y + 2 <= ylast) rowload(y + 2, A);
-      process(Bf, y + 1);
-    }
   }
 #pragma unroll
   for (int f = 0; f < F; ++f) {
@@ -323,135 +280,142 @@ __global__ __launch_bounds__(64) void k_motion_bits(MotionArgs a, int rows, int 
 // wavefront store one contiguous 1 KiB span per instruction.
 // The same pass leaves the batch's counts at zero for the next batch (the
 // emit scan has read them) and, with state_src set, copies the batch's last
-// frame to the self-delay state (grid row n: 16 bytes per thread; nothing in
-// this pass reads the frames or the state).
-template <bool FAST>
+// frame to the self-delay state (grid row n: 16 bytes per thread, the last
+// ones into the slack; nothing in this pass reads the frames or the state).
 __global__ __launch_bounds__(256) void k_motion_expand(MotionArgs a) {
   const int64_t j = blockIdx.y;
+  const int W = a.W, H = a.H, wpr = a.words_per_row;
+  const int64_t wh = (int64_t)W * H;
+  const int64_t hw = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (j == a.n) {
-    const int64_t off = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 16;
-    if (off < (int64_t)a.W * a.H) {
-      typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-      const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(a.state_src + off));
-      *reinterpret_cast<u32x4 *>(a.state + off) = v;
+    if (hw * 16 < wh) {
+      const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4_any *>(a.state_src + hw * 16));
+      *reinterpret_cast<u32x4 *>(a.state + hw * 16) = v;
     }
     return;
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) a.count[j] = 0;
   const int64_t slot = a.emit_off[j];
   if (slot < 0) return;                                 // uniform: not emitted
-  const int W = a.W, H = a.H, wpr = a.words_per_row;
-  const int64_t wh = (int64_t)W * H;
-  const int64_t hw = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (blockIdx.x == 0 && threadIdx.x == 0)
-    a.index_out[(a.index_idx[1] + slot) & a.index_mask] = a.frame_base + j;
+  const int64_t *base = a.emit_off + a.n + 1;           // write positions before the batch (masks, indices)
+  if (blockIdx.x == 0 && threadIdx.x == 0) a.index_out[(base[1] + slot) & a.index_mask] = a.frame_base + j;
   if (hw >= 2 * (int64_t)H * wpr) return;
   const int64_t wi = hw >> 1;
   const int half = (int)(hw & 1);
   const int y = (int)(wi / wpr), c = (int)(wi - (int64_t)y * wpr);
   const uint32_t o = a.bits[j * (int64_t)H * wpr + wi] >> (4 * half);
   const int x = c * 32 + 16 * half;
-  uint8_t *dst = a.out + ((a.out_idx[1] + slot) & a.out_mask) * wh + (int64_t)y * W + x;
+  uint8_t *dst = a.out + ((base[0] + slot) & a.out_mask) * wh + (int64_t)y * W + x;
   uint32_t v[4];
 #pragma unroll
   for (int k = 0; k < 4; ++k) v[k] = ((o >> k) & 0x01010101u) * 0xFFu;   // dword k: pixel 4k + j <- bit 8j + k
-  if (FAST) {
-    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+  if (x + 16 <= W) {
     const u32x4 val = {v[0], v[1], v[2], v[3]};
-    __builtin_nontemporal_store(val, reinterpret_cast<u32x4 *>(dst));
+    __builtin_nontemporal_store(val, reinterpret_cast<u32x4_any *>(dst));
   } else {
-    const int n = min(16, W - x);
-    for (int i = 0; i < n; ++i) dst[i] = (uint8_t)(v[i >> 2] >> (8 * (i & 3)));
+    for (int i = 0; i < W - x; ++i) dst[i] = (uint8_t)(v[i >> 2] >> (8 * (i & 3)));
   }
 }
 
-// Exclusive scan of emit flags: emit_off[j] = output slot of firing j or -1,
-// emit_off[n] = number of emitted frames.  One wavefront, ballot-based.
-__global__ __launch_bounds__(64) void k_emit_scan(const int32_t *count, int64_t n, int64_t thresh,
-                                                  int64_t *off) {
+// Exclusive scan of emit flags and batch commit: emit_off[j] = output slot of
+// firing j or -1, emit_off[n] = number of emitted frames, emit_off[n+1..n+2] =
+// write positions of the mask and index channels before the batch (the expand
+// pass, the batch's last, places its tokens from them); then every channel
+// counter advances, and the new write positions go to host memory too, so that
+// the host learns them without a copy.  One wavefront, ballot-based.
+__global__ __launch_bounds__(64) void k_emit_commit(MotionCommitArgs a) {
   const int lane = threadIdx.x;
   const uint64_t below_mask = lane ? (~0ull >> (64 - lane)) : 0ull;
   int64_t carry = 0;
-  for (int64_t c = 0; c < n; c += 64) {
+  for (int64_t c = 0; c < a.n; c += 64) {
     const int64_t j = c + lane;
-    const bool f = j < n && 1000 * (int64_t)count[j] >= thresh;
+    const bool f = j < a.n && 1000 * (int64_t)a.count[j] >= a.thresh;
     const uint64_t bal = __ballot(f);
-    if (j < n) off[j] = f ? carry + __popcll(bal & below_mask) : -1;
+    if (j < a.n) a.emit_off[j] = f ? carry + __popcll(bal & below_mask) : -1;
     carry += __popcll(bal);
   }
-  if (lane == 0) off[n] = carry;
+  if (lane != 0) return;
+  const int64_t out0 = a.out_idx[1], index0 = a.index_idx[1];
+  a.emit_off[a.n] = carry;
+  a.emit_off[a.n + 1] = out0;
+  a.emit_off[a.n + 2] = index0;
+  a.cur_idx[0] += a.n;
+  if (a.prev_idx) a.prev_idx[0] += a.n;
+  a.out_idx[1] = out0 + carry;
+  a.index_idx[1] = index0 + carry;
+  check_chan(a.cur_idx, a.err);
+  if (a.prev_idx) check_chan(a.prev_idx, a.err);
+  check_chan(a.out_idx, a.err);
+  check_chan(a.index_idx, a.err);
+  if (!a.host) return;
+  const uint64_t seq = (uint64_t)a.seq << 32;
+  __hip_atomic_store(&a.host->word[0], seq | (uint32_t)(out0 + carry), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  __hip_atomic_store(&a.host->word[1], seq | (uint32_t)(index0 + carry), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
-
-__global__ void k_motion_commit(const int64_t *emit_off, int64_t n, int64_t *cur_idx, int64_t *prev_idx,
-                                int64_t *out_idx, int64_t *index_idx, int32_t *err) {
-  if (threadIdx.x != 0) return;
-  const int64_t total = emit_off[n];
-  cur_idx[0] += n;
-  if (prev_idx) prev_idx[0] += n;
-  out_idx[1] += total;
-  index_idx[1] += total;
-  check_chan(cur_idx, err);
-  if (prev_idx) check_chan(prev_idx, err);
-  check_chan(out_idx, err);
-  check_chan(index_idx, err);
-}
-
-constexpr int MOTION_ROWS = 32;  // rows per band
 
 template <int F>
 static hipError_t launch_bits(const MotionArgs &a, hipStream_t s, int64_t items, int rows, int n_bands,
                               int n_chunks) {
   if (items > 0x7ffffff0) return hipErrorInvalidValue;
-  const bool fast = (a.W % 32) == 0 && ((int64_t)a.W * a.H) % 16 == 0;
   const dim3 grid((unsigned)((items + 7) / 8 * 8));
-  if (fast)
-    hipLaunchKernelGGL((k_motion_bits<F, true>), grid, dim3(64), 0, s, a, rows, n_bands, n_chunks, (int)items);
-  else
-    hipLaunchKernelGGL((k_motion_bits<F, false>), grid, dim3(64), 0, s, a, rows, n_bands, n_chunks, (int)items);
+  hipLaunchKernelGGL(k_motion_bits<F>, grid, dim3(64), 0, s, a, rows, n_bands, n_chunks, (int)items);
   return hipGetLastError();
 }
 
-// Frames per wavefront in the self-delay form: F + 1 row loads per F
-// frames.  Measured on the 300-frame 1080p workload (bits pass + expand):
-// F = 4 0.308 ms, F = 2 0.341 ms, F = 1 0.405 ms: the extra waves of smaller
-// F do not pay for their extra frame reads.
-constexpr int MOTION_F = 4;
+// Shape of the bits pass: F frames per wavefront in the self-delay form (F + 1
+// row loads per F frames; the two-channel form has F = 1) and bands of `rows`
+// rows (4 rows more are loaded than written).  Large F and bands read less,
+// but a wavefront walks its rows one after the other, so a batch that leaves
+// the 1024 SIMDs short of wavefronts wants smaller ones: the largest F with
+// 32-row bands that still gives 120000 word columns (2000 wavefronts of 60
+// words), else F = 1 and 16, 8 or 4 rows.  Batch body in us by F/rows:
+//   1920x1080  300 frames  4/32 292  2/32 313  1/32 369  4/16 312
+//              120         4/32 161  2/32 136  1/32 148  4/16 140
+//               30         4/32  92  2/32  65  1/16  54  1/8 56
+//                8         4/32  81  1/16  33  1/8   31  1/4 37
+//                1         4/32  43  1/8   20  1/4   18
+//    640x480    64         4/32  81  1/16  41  1/8   37  1/4 44
+//    320x240   256         4/32  87  1/32  61  1/16  48  1/8 51
+//               24         4/32  82  1/16  26  1/8   23  1/4 24
+//   3840x2160   20         4/32 125  2/32 111  1/32 113  1/16 126
+struct BitsShape {
+  int F, rows;
+};
+
+static BitsShape bits_shape(const MotionArgs &a, int n_chunks) {
+  const auto waves = [&](int F, int rows) {
+    return (int64_t)n_chunks * ((a.H + rows - 1) / rows) * ((a.n + F - 1) / F);
+  };
+  const int64_t words = a.words_per_row < MW_CHUNK ? a.words_per_row : MW_CHUNK;
+  for (int F = a.prev ? 1 : 4; F >= 1; F /= 2)
+    if (waves(F, 32) * words >= 120000) return {F, 32};
+  if (waves(1, 16) >= 2000) return {1, 16};
+  return {1, waves(1, 8) >= 500 ? 8 : 4};
+}
 
 hipError_t launch_motion_count(const MotionArgs &a, hipStream_t s) {
   if (a.n <= 0) return hipSuccess;
   const int n_chunks = (a.words_per_row + MW_CHUNK - 1) / MW_CHUNK;
-  const int rows = MOTION_ROWS;
-  const int n_bands = (a.H + rows - 1) / rows;
-  if (a.prev) return launch_bits<1>(a, s, (int64_t)n_chunks * n_bands * a.n, rows, n_bands, n_chunks);
-  return launch_bits<MOTION_F>(a, s, (int64_t)n_chunks * n_bands * ((a.n + MOTION_F - 1) / MOTION_F), rows,
-                               n_bands, n_chunks);
+  const BitsShape sh = bits_shape(a, n_chunks);
+  const int n_bands = (a.H + sh.rows - 1) / sh.rows;
+  const int64_t items = (int64_t)n_chunks * n_bands * ((a.n + sh.F - 1) / sh.F);
+  if (sh.F == 4) return launch_bits<4>(a, s, items, sh.rows, n_bands, n_chunks);
+  if (sh.F == 2) return launch_bits<2>(a, s, items, sh.rows, n_bands, n_chunks);
+  return launch_bits<1>(a, s, items, sh.rows, n_bands, n_chunks);
 }
 
-hipError_t launch_motion_emit_scan(const int32_t *count, int64_t n, int64_t thresh, int64_t *off,
-                                   hipStream_t s) {
-  hipLaunchKernelGGL(k_emit_scan, dim3(1), dim3(64), 0, s, count, n, thresh, off);
+hipError_t launch_motion_emit_commit(const MotionCommitArgs &a, hipStream_t s) {
+  hipLaunchKernelGGL(k_emit_commit, dim3(1), dim3(64), 0, s, a);
   return hipGetLastError();
 }
 
 hipError_t launch_motion_emit(const MotionArgs &a, hipStream_t s) {
   if (a.n <= 0) return hipSuccess;
   const int64_t halves = 2 * (int64_t)a.H * a.words_per_row;
-  const bool fast = (a.W % 32) == 0 && ((int64_t)a.W * a.H) % 16 == 0;
-  // grid row n copies the state: 16 bytes per thread cover the frame when
-  // the width is a multiple of 32 (halves * 16 = W * H)
-  if (a.state_src && !fast) return hipErrorInvalidValue;
+  // grid row n copies the state: 16 bytes per thread cover the frame
+  // (halves * 16 >= W * H)
   dim3 grid((unsigned)((halves + 255) / 256), (unsigned)(a.n + (a.state_src ? 1 : 0)));
-  if (fast)
-    hipLaunchKernelGGL(k_motion_expand<true>, grid, dim3(256), 0, s, a);
-  else
-    hipLaunchKernelGGL(k_motion_expand<false>, grid, dim3(256), 0, s, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_motion_commit(const int64_t *emit_off, int64_t n, int64_t *cur_idx, int64_t *prev_idx,
-                                int64_t *out_idx, int64_t *index_idx, int32_t *err, hipStream_t s) {
-  hipLaunchKernelGGL(k_motion_commit, dim3(1), dim3(64), 0, s, emit_off, n, cur_idx, prev_idx, out_idx,
-                     index_idx, err);
+  hipLaunchKernelGGL(k_motion_expand, grid, dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

@@ -155,6 +155,7 @@ static void free_actor(Actor &a) {
   (void)hipFree(a.count);
   (void)hipFree(a.emit_off);
   (void)hipFree(a.bits);
+  if (a.counts) (void)hipHostFree(a.counts);
   a = Actor();
 }
 
@@ -229,7 +230,7 @@ static df_status make_fifo(df_graph *g, df_dtype dt, int64_t elems_per_token, in
   f.n_initial = n_initial;
   const int id = (int)g->fifos.size();
   f.idx = g->idx_pool + kCtrWords * id;
-  hipError_t e = hipMalloc(&f.ring, (size_t)(slots * f.token_bytes));
+  hipError_t e = hipMalloc(&f.ring, (size_t)(slots * f.token_bytes) + (dt == DF_U8 ? kFrameSlack : 0));
   if (e != hipSuccess) return fail(g, DF_ENOMEM, "channel allocation of %lld bytes failed",
                                    (long long)(slots * f.token_bytes));
   if (n_initial) {
@@ -290,6 +291,20 @@ extern "C" int64_t df_fifo_bytes(df_graph *g, int32_t fifo) {
 }
 
 df_status dfh::refresh_fifo(df_graph *g, Fifo &f) {
+  if (f.counts) {
+    // Wait for the batch's commit only, not for the work enqueued behind it:
+    // its number arrives in host memory with the counter's low half.  The
+    // loop also ends when the stream has nothing left to run (or fails); then
+    // the device is read.
+    for (int64_t spins = 0;; ++spins) {
+      const uint64_t v = __atomic_load_n(&f.counts->word[f.counts_at], __ATOMIC_ACQUIRE);
+      if ((uint32_t)(v >> 32) == f.counts_seq) {
+        f.write_lo = f.write_hi = f.write_lo + (uint32_t)((uint32_t)v - (uint32_t)f.write_lo);
+        return DF_OK;
+      }
+      if (spins % 4096 == 4095 && hipStreamQuery(g->stream) != hipErrorNotReady) break;
+    }
+  }
   HIPCHK(g, hipStreamSynchronize(g->stream));
   int64_t idx[2];
   HIPCHK(g, hipMemcpy(idx, f.idx, sizeof idx, hipMemcpyDeviceToHost));
@@ -385,9 +400,15 @@ extern "C" df_status df_actor_create(df_graph *g, df_actor_kind kind, const void
       return fail(g, DF_EINVAL, "min_changed_permille outside 0..1000");
     if (p.self_delay != 0 && p.self_delay != 1) return fail(g, DF_EINVAL, "self_delay must be 0 or 1");
     a.mp = p;
+    if ((e = hipHostMalloc((void **)&a.counts, sizeof(MotionCounts), hipHostMallocDefault)) != hipSuccess)
+      return fail(g, DF_ENOMEM, "actor allocation failed");
+    *a.counts = MotionCounts{};
     if (p.self_delay) {
       const size_t wh = (size_t)p.width * p.height;
-      if ((e = hipMalloc(&a.state, wh)) != hipSuccess) return fail(g, DF_ENOMEM, "state allocation failed");
+      if ((e = hipMalloc(&a.state, wh + kFrameSlack)) != hipSuccess) {
+        free_actor(a);
+        return fail(g, DF_ENOMEM, "state allocation failed");
+      }
       if ((e = hipMemset(a.state, 0, wh)) != hipSuccess) {
         free_actor(a);
         return fail_hip(g, e, "state init");
@@ -832,13 +853,17 @@ static df_status fire_motion(df_graph *g, Actor &a, int64_t n, int flags, int64_
     HIPCHK(g, hipStreamSynchronize(g->stream));
     const int64_t cap = std::min(next_pow2(want), chunk_max);
     if (grow((void **)&a.count, sizeof(int32_t) * cap) != hipSuccess ||
-        grow((void **)&a.emit_off, sizeof(int64_t) * (cap + 1)) != hipSuccess ||
+        grow((void **)&a.emit_off, sizeof(int64_t) * (cap + 3)) != hipSuccess ||
         grow((void **)&a.bits, (size_t)(frame_bits * cap)) != hipSuccess)
       return fail(g, DF_ENOMEM, "scratch allocation failed");
     a.cnt_cap = cap;
     // counts start at zero; every emit pass leaves the ones it used at zero
     HIPCHK(g, launch_fill_i32(a.count, 0, cap, g->stream));
   }
+  // a captured batch runs when its graph is launched: no number to wait for
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  HIPCHK(g, hipStreamIsCapturing(g->stream, &cs));
+  const bool capturing = cs != hipStreamCaptureStatusNone;
   for (int64_t done = 0; done < n; done += chunk_max) {
     const int64_t k = std::min(chunk_max, n - done);
     MotionArgs ma{};
@@ -866,22 +891,34 @@ static df_status fire_motion(df_graph *g, Actor &a, int64_t n, int flags, int64_
     ma.thr = p.diff_threshold;
     ma.permille = p.min_changed_permille;
     // the batch's last input frame becomes the self-delay state: copied by
-    // the emit pass when the frame is whole 16-byte words per 32-pixel word
-    const bool fast = (p.width % 32) == 0 && wh % 16 == 0;
-    const uint8_t *last_frame = p.self_delay ? (const uint8_t *)fc.ring + ((fc.read_h + k - 1) & fc.mask) * wh : nullptr;
-    ma.state_src = fast ? last_frame : nullptr;
+    // the emit pass
+    ma.state_src = p.self_delay ? (const uint8_t *)fc.ring + ((fc.read_h + k - 1) & fc.mask) * wh : nullptr;
+    MotionCommitArgs ca{};
+    ca.count = a.count;
+    ca.n = k;
+    ca.thresh = (int64_t)p.min_changed_permille * wh;
+    ca.emit_off = a.emit_off;
+    ca.cur_idx = fc.idx;
+    ca.prev_idx = fp ? fp->idx : nullptr;
+    ca.out_idx = fm.idx;
+    ca.index_idx = fi.idx;
+    ca.host = capturing ? nullptr : a.counts;
+    ca.seq = ++a.counts_seq;
+    ca.err = g->err_dev;
     HIPCHK(g, prof_begin(g, (int)(&a - g->actors.data())));
     HIPCHK(g, launch_motion_count(ma, g->stream));
-    HIPCHK(g, launch_motion_emit_scan(a.count, k, (int64_t)p.min_changed_permille * wh, a.emit_off, g->stream));
+    HIPCHK(g, launch_motion_emit_commit(ca, g->stream));
     HIPCHK(g, launch_motion_emit(ma, g->stream));
     HIPCHK(g, prof_end(g));
-    if (last_frame && !fast)
-      HIPCHK(g, hipMemcpyAsync(a.state, last_frame, (size_t)wh, hipMemcpyDeviceToDevice, g->stream));
-    HIPCHK(g, launch_motion_commit(a.emit_off, k, fc.idx, fp ? fp->idx : nullptr, fm.idx, fi.idx, g->err_dev, g->stream));
     fc.read_h += k;
     if (fp) fp->read_h += k;
     fm.write_hi += k;
     fi.write_hi += k;
+    for (Fifo *f : {&fm, &fi}) {
+      f->counts = capturing ? nullptr : a.counts;
+      f->counts_at = f == &fi;
+      f->counts_seq = a.counts_seq;
+    }
     a.fired += k;
   }
   a.last_n = n;
@@ -1232,6 +1269,7 @@ extern "C" df_status df_debug_set_counters(df_graph *g, int32_t fifo, int64_t re
   if (fifo < 0 || fifo >= (int)g->fifos.size()) return fail(g, DF_EINVAL, "bad fifo id %d", fifo);
   Fifo &f = g->fifos[fifo];
   const int64_t v[2] = {read_idx, write_idx};
+  f.counts = nullptr;                                // until its writer's next batch
   HIPCHK(g, hipMemcpyAsync(f.idx, v, sizeof v, hipMemcpyHostToDevice, g->stream));
   HIPCHK(g, hipStreamSynchronize(g->stream));
   return DF_OK;

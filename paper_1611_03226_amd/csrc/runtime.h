@@ -26,6 +26,12 @@ struct Fifo {
   int64_t *idx = nullptr;
   int64_t read_h = 0, write_lo = 0, write_hi = 0;
   int64_t n_initial = 0;
+  // a motion actor's mask or index channel: where the commit of its last batch
+  // (counts_seq) leaves the write counter in host memory (nullptr: read the
+  // device's)
+  const MotionCounts *counts = nullptr;
+  int counts_at = 0;
+  uint32_t counts_seq = 0;
   // the paper's layout (Sec. 3.2): period P (2r, or 3r with a delay token),
   // 0 for a ring; `slots` tokens are allocated (cap, or P + 1 with a delay)
   int64_t period = 0;
@@ -75,6 +81,8 @@ struct Actor {
   int64_t *emit_off = nullptr;
   uint32_t *bits = nullptr;  // bit-packed opened masks of a chunk of firings
   int64_t cnt_cap = 0;
+  MotionCounts *counts = nullptr;   // page-locked host memory, written by each batch's commit
+  uint32_t counts_seq = 0;          // batches so far
   // Gauss / Thres / Med
   df_frame_params fp{};
 };
