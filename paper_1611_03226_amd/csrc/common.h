@@ -319,6 +319,19 @@ hipError_t launch_advance_n(int64_t *const *ptr, int n, int64_t delta, int32_t *
 // Add delta[i] to counter ptr[i] (n <= 8) in one launch.
 hipError_t launch_advance_by(int64_t *const *ptr, const int64_t *delta, int n, int32_t *err, hipStream_t s);
 
+// A push or pop of device memory in one launch: up to two runs of consecutive
+// bytes copied (the second where the channel's slots wrap), and the channel's
+// counter advanced by n tokens with its ring invariant checked.
+struct RingCopyArgs {
+  const uint8_t *src[2];
+  uint8_t *dst[2];
+  int64_t bytes[2];       // bytes[1] = 0: one run
+  int64_t *idx;           // the counter (word 0 or 1 of a channel slot)
+  int64_t n;
+  int32_t *err;
+};
+hipError_t launch_ring_copy(const RingCopyArgs &a, hipStream_t s);
+
 // The predistortion network with materialised branch channels (rows of
 // nf firings of r samples; tables from the offset scan, off in samples).
 struct DpdNetArgs {

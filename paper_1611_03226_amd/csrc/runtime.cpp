@@ -98,6 +98,7 @@ extern "C" df_status df_graph_create(df_graph **out, int device, void *stream) {
   df_graph *g = new (std::nothrow) df_graph();
   if (!g) return fail(nullptr, DF_ENOMEM, "host allocation failed");
   g->device = device;
+  g->many_devices = n > 1;
   if ((e = hipSetDevice(device)) != hipSuccess) {
     delete g;
     return fail(nullptr, DF_EDEVICE, "hipSetDevice: %s", hipGetErrorString(e));
@@ -549,6 +550,47 @@ static hipError_t paper_fixup(df_graph *g, const Fifo &f, int64_t pos, int64_t n
   return hipMemcpyAsync(f.ring, f.ring + f.period * tb, tb, hipMemcpyDeviceToDevice, g->stream);
 }
 
+// Memory of the graph's own device (elsewhere, a runtime copy reaches it).
+static bool on_own_device(const df_graph *g, const void *p) {
+  if (!g->many_devices) return true;
+  hipPointerAttribute_t at;
+  if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return at.type == hipMemoryTypeDevice && at.device == g->device;
+}
+
+// Move n tokens between a channel (position pos) and a flat buffer and
+// advance the channel's counter `idx`.  Device memory: one kernel for the
+// copy and the counter (at most two runs: n is at most the capacity).
+static hipError_t move_tokens(df_graph *g, Fifo &f, int64_t pos, void *flat, int64_t n, bool to_ring,
+                              bool flat_on_device, int64_t *idx) {
+  if (!flat_on_device || !on_own_device(g, flat)) {
+    hipError_t e = ring_copy(g, f, pos, flat, n, to_ring, flat_on_device);
+    if (e == hipSuccess && to_ring) e = paper_fixup(g, f, pos, n);
+    return e == hipSuccess ? launch_advance(idx, n, g->err_dev, g->stream) : e;
+  }
+  const host::SlotMap m = slot_map(f);
+  RingCopyArgs a{};
+  a.idx = idx;
+  a.n = n;
+  a.err = g->err_dev;
+  int64_t done = 0;
+  for (int i = 0; i < 2 && done < n; ++i) {
+    const host::Run run = host::next_run(m, pos + done, n - done, to_ring);
+    uint8_t *r = (uint8_t *)f.ring + run.slot * f.token_bytes, *p = (uint8_t *)flat + done * f.token_bytes;
+    a.src[i] = to_ring ? p : r;
+    a.dst[i] = to_ring ? r : p;
+    a.bytes[i] = run.count * f.token_bytes;
+    done += run.count;
+  }
+  if (done < n) return hipErrorInvalidValue;
+  hipError_t e = launch_ring_copy(a, g->stream);
+  if (e == hipSuccess && to_ring) e = paper_fixup(g, f, pos, n);
+  return e;
+}
+
 extern "C" df_status df_push(df_graph *g, int32_t fifo, const void *src, int64_t n, int src_on_device) {
   ENTER(g);
   if (fifo < 0 || fifo >= (int)g->fifos.size()) return fail(g, DF_EINVAL, "bad fifo id %d", fifo);
@@ -569,9 +611,7 @@ extern "C" df_status df_push(df_graph *g, int32_t fifo, const void *src, int64_t
       if (v[i] < 0 || v[i] > hi)
         return fail(g, DF_EINVAL, "control token %d at %lld outside 0..%d", v[i], (long long)i, hi);
   }
-  HIPCHK(g, ring_copy(g, f, f.write_hi, (void *)src, n, true, src_on_device != 0));
-  HIPCHK(g, paper_fixup(g, f, f.write_hi, n));
-  HIPCHK(g, launch_advance(f.idx + 1, n, g->err_dev, g->stream));
+  HIPCHK(g, move_tokens(g, f, f.write_hi, (void *)src, n, true, src_on_device != 0, f.idx + 1));
   f.write_lo += n;
   f.write_hi += n;
   if (!src_on_device) HIPCHK(g, hipStreamSynchronize(g->stream));
@@ -593,8 +633,7 @@ extern "C" df_status df_pop(df_graph *g, int32_t fifo, void *dst, int64_t max_to
   const int64_t k = std::min(max_tokens, f.write_lo - f.read_h);
   if (k > 0) {
     if (!dst) return fail(g, DF_EINVAL, "null destination");
-    HIPCHK(g, ring_copy(g, f, f.read_h, dst, k, false, dst_on_device != 0));
-    HIPCHK(g, launch_advance(f.idx + 0, k, g->err_dev, g->stream));
+    HIPCHK(g, move_tokens(g, f, f.read_h, dst, k, false, dst_on_device != 0, f.idx + 0));
     f.read_h += k;
     if (!dst_on_device) HIPCHK(g, hipStreamSynchronize(g->stream));
   }
