@@ -8,6 +8,9 @@ namespace dfh {
 
 constexpr int kMaxBranches = 16;
 constexpr int kMaxTaps = 32;
+// Complex coefficients per tap in the tap-major layout the bodies read (the
+// branches of one tap are consecutive).
+constexpr int kCoefRow = kMaxBranches;
 
 // Sticky device error bits (an int32 in device memory per graph).
 enum : int32_t { kErrControl = 1, kErrIndex = 2 };

@@ -55,7 +55,6 @@ __host__ __device__ constexpr int lds_window(int n) { return lds_slot<K>(n) + 1;
 // with a fixed row length, so that the branches of one tap are consecutive
 // (a few wide scalar loads instead of one per branch) at offsets known at
 // compile time.
-constexpr int kCoefRow = kMaxBranches;
 
 // Taps of K consecutive outputs q0..q0+K-1.  Tap m of output q0+k reads
 // window sample k+M-1-m, so iterating the taps in order slides a window of

@@ -138,19 +138,14 @@ extern "C" df_status df_graph_create(df_graph **out, int device, void *stream) {
 }
 
 static void free_actor(Actor &a) {
-  (void)hipFree(a.h);
-  (void)hipFree(a.ht);
-  (void)hipFree(a.hist);
+  (void)hipFree(a.block);
   (void)hipFree(a.order);
   (void)hipFree(a.corr);
-  (void)hipFree(a.ticket);
   (void)hipFree(a.prev);
   (void)hipFree(a.off);
   for (auto &sl : a.scan) {
     (void)hipFree(sl.B);
     (void)hipFree(sl.grp);
-    (void)hipFree(sl.last);
-    (void)hipFree(sl.err);
   }
   (void)hipFree(a.state);
   (void)hipFree(a.count);
@@ -368,25 +363,46 @@ extern "C" df_status df_actor_create(df_graph *g, df_actor_kind kind, const void
     if (!p.coeffs) return fail(g, DF_EINVAL, "null coefficients");
     a.dp = p;
     a.dp.coeffs = nullptr;
-    const size_t hb = sizeof(float2) * p.n_branches_max * p.n_taps;
-    const size_t sb = sizeof(float2) * p.n_branches_max * std::max(p.n_taps - 1, 1);
-    if ((e = hipMalloc(&a.h, hb)) != hipSuccess || (e = hipMalloc(&a.ht, coef_rows_bytes(p.n_taps))) != hipSuccess ||
-        (e = hipMalloc(&a.hist, sb)) != hipSuccess ||
-        (e = hipMalloc(&a.scan[0].last, sizeof(int64_t) * p.n_branches_max)) != hipSuccess ||
-        (e = hipMalloc(&a.scan[1].last, sizeof(int64_t) * p.n_branches_max)) != hipSuccess ||
-        (e = hipMalloc(&a.scan[0].err, sizeof(int32_t))) != hipSuccess ||
-        (e = hipMalloc(&a.scan[1].err, sizeof(int32_t))) != hipSuccess ||
-        (e = hipMalloc(&a.ticket, sizeof(int32_t))) != hipSuccess) {
-      free_actor(a);
-      return fail(g, DF_ENOMEM, "actor allocation failed");
+    // One allocation for the actor's coefficients, history, counters and scan
+    // words; with host coefficients one upload sets all of it.
+    const size_t B = (size_t)p.n_branches_max, M = (size_t)p.n_taps;
+    size_t bytes = 0;
+    const auto region = [&](size_t n) {
+      const size_t at = bytes;
+      bytes += (n + 255) & ~(size_t)255;
+      return at;
+    };
+    const size_t o_h = region(sizeof(float2) * B * M), o_ht = region(coef_rows_bytes(p.n_taps)),
+                 o_hist = region(sizeof(float2) * B * std::max<size_t>(M - 1, 1)),
+                 o_last[2] = {region(sizeof(int64_t) * B), region(sizeof(int64_t) * B)},
+                 o_words = region(3 * sizeof(int32_t));
+    if ((e = hipMalloc((void **)&a.block, bytes)) != hipSuccess) return fail(g, DF_ENOMEM, "actor allocation failed");
+    a.h = (float2 *)(a.block + o_h);
+    a.ht = (float2 *)(a.block + o_ht);
+    a.hist = (float2 *)(a.block + o_hist);
+    for (int i = 0; i < 2; ++i) {
+      a.scan[i].last = (int64_t *)(a.block + o_last[i]);
+      a.scan[i].err = (int32_t *)(a.block + o_words) + i;
     }
-    e = hipMemcpy(a.h, p.coeffs, hb, p.coeffs_on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = launch_coef_rows(a.h, a.ht, p.n_branches_max, p.n_taps, nullptr);
-    if (e == hipSuccess) e = hipMemset(a.hist, 0, sb);
-    if (e == hipSuccess) e = hipMemset(a.ticket, 0, sizeof(int32_t));
-    for (auto &sl : a.scan)
-      if (e == hipSuccess) e = hipMemset(sl.err, 0, sizeof(int32_t));
-    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);   // the graph's stream does not wait for this one
+    a.ticket = (int32_t *)(a.block + o_words) + 2;
+    if (p.coeffs_on_device) {
+      e = hipMemset(a.block, 0, bytes);
+      if (e == hipSuccess) e = hipMemcpy(a.h, p.coeffs, sizeof(float2) * B * M, hipMemcpyDeviceToDevice);
+      if (e == hipSuccess) e = launch_coef_rows(a.h, a.ht, p.n_branches_max, p.n_taps, nullptr);
+      if (e == hipSuccess) e = hipStreamSynchronize(nullptr);   // the graph's stream does not wait for this one
+    } else {
+      alignas(256) char image[16384] = {};               // 12.75 KiB at 16 branches and 32 taps
+      if (bytes > sizeof image) {
+        free_actor(a);
+        return fail(g, DF_EINVAL, "actor state of %zu bytes", bytes);
+      }
+      const float2 *src = (const float2 *)p.coeffs;
+      float2 *ht = (float2 *)(image + o_ht);
+      memcpy(image + o_h, src, sizeof(float2) * B * M);
+      for (size_t b = 0; b < B; ++b)
+        for (size_t m = 0; m < M; ++m) ht[m * kCoefRow + b] = src[b * M + m];
+      e = hipMemcpy(a.block, image, bytes, hipMemcpyHostToDevice);
+    }
     if (e != hipSuccess) {
       free_actor(a);
       return fail_hip(g, e, "actor init");

@@ -52,6 +52,7 @@ struct Actor {
   int64_t last_n = 0;    // size of the last batch
   // predistortion
   df_dpd_params dp{};
+  char *block = nullptr;     // one allocation: h, ht, hist, ticket, scan[].last and .err
   float2 *h = nullptr;       // [B_max][M]
   float2 *ht = nullptr;      // the same, tap-major (launch_coef_rows)
   float2 *hist = nullptr;    // [B_max][M-1] carried branch histories
