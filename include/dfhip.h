@@ -479,6 +479,23 @@ df_status df_mp_input_adjoint(void *stream, const void *u, const void *a,
                               const void *g, void *Gu, int64_t n_streams,
                               int64_t len, int32_t K, int32_t Q);
 
+/* Squared error of the memory polynomial and its gradient, for coefficient
+ * adaptation: with v = the polynomial of u as above and e = v - x, *loss (one
+ * device float) = sum |e|^2 over all rows, summed in a fixed order (fp64 above
+ * four samples), and e (complex64 [n_streams][len], may be NULL) receives e.
+ * `work` is a device buffer of df_mp_loss_work_bytes() bytes.
+ * df_mp_loss_adjoint writes Gu = dL/dRe u + i dL/dIm u for an upstream
+ * gradient *gloss (one device float) of the loss: the input adjoint above with
+ * g = 2 *gloss e.  len >= Q - 1 as for df_dpd_forward.
+ * Errors: DF_EINVAL (sizes, null pointers, work too small), DF_EDEVICE. */
+int64_t df_mp_loss_work_bytes(void);
+df_status df_mp_loss(void *stream, const void *u, const void *a, const void *x,
+                     void *e, float *loss, int64_t n_streams, int64_t len,
+                     int32_t K, int32_t Q, void *work, int64_t work_bytes);
+df_status df_mp_loss_adjoint(void *stream, const void *u, const void *a,
+                             const void *e, const float *gloss, void *Gu,
+                             int64_t n_streams, int64_t len, int32_t K, int32_t Q);
+
 /* Measurement helper (no operation of the method): copies `bytes` bytes from
  * device buffer src to device buffer dst on `stream` (NULL: the null stream)
  * with a plain 16-byte-vector stream-copy kernel.  It is the reference

@@ -76,9 +76,35 @@ class PAFunction(torch.autograd.Function):
         return gu, None
 
 
+class PALossFunction(torch.autograd.Function):
+    """sum |PA_a(u) - x|^2 for fixed a and x, and its gradient for u: the
+    model, the error and the sum in one kernel, and the backward reads the
+    stored error (the same as PAFunction followed by torch's arithmetic, which
+    makes about twenty passes over the signals)."""
+
+    @staticmethod
+    def forward(ctx, u, a, x):
+        u, a, x = u.contiguous(), a.detach().contiguous(), x.contiguous()
+        e = torch.empty_like(u) if ctx.needs_input_grad[0] else None
+        loss = torch.empty((), dtype=torch.float32, device=u.device)
+        work = torch.empty(D.df_mp_loss_work_bytes(), dtype=torch.uint8, device=u.device)
+        D.df_mp_loss(u, a, x, e, loss, work, stream=_stream())
+        if e is not None:
+            ctx.save_for_backward(u, a, e)
+        return loss
+
+    @staticmethod
+    def backward(ctx, gloss):
+        u, a, e = ctx.saved_tensors
+        gu = torch.empty_like(u)
+        D.df_mp_loss_adjoint(u, a, e, gloss.contiguous(), gu, stream=_stream())
+        return gu, None, None
+
+
 def adaptation_loss(x, h, a, r):
     """L = sum |PA(DPD_h(x)) - x|^2."""
     u = DPDFunction.apply(x, h, r)
-    v = PAFunction.apply(u, a)
-    e = v - x
+    if not x.requires_grad:
+        return PALossFunction.apply(u, a, x)
+    e = PAFunction.apply(u, a) - x               # x is a variable too: torch differentiates the error
     return (e.real * e.real + e.imag * e.imag).sum()

@@ -379,7 +379,19 @@ hipError_t launch_stream_copy(const void *src, void *dst, int64_t bytes, hipStre
 // Bandwidth reference of one access mix: 0 copy, 1 read only, 2 write only,
 // 3 two reads one write (src holds 2*bytes).
 hipError_t launch_hbm_ref(int mode, const void *src, void *dst, int64_t bytes, hipStream_t s);
-hipError_t launch_mp_adj(const float2 *u, const float2 *a, const float2 *g, float2 *Gu, int64_t n_streams,
-                         int64_t len, int K, int Q, hipStream_t s);
+// Memory-polynomial amplifier model over rows [S][len], a [K][Q].
+struct MpArgs {
+  const float2 *u;
+  const float2 *a;
+  const float2 *x;        // loss: the target; adjoint: the upstream gradient
+  float2 *out;            // loss: e = v - x, or nullptr; adjoint: Gu
+  const float *scale;     // adjoint: the gradient is 2 * scale[0] * x (nullptr: x)
+  double *partial;        // loss: kMpLossBlocks sums
+  int64_t S, len;
+  int K, Q;
+};
+constexpr int kMpLossBlocks = 2048;
+hipError_t launch_mp_loss(const MpArgs &m, float *loss, hipStream_t s);
+hipError_t launch_mp_adj(const MpArgs &m, hipStream_t s);
 
 }  // namespace dfh

@@ -16,7 +16,10 @@
 // d phi/du* = k p^(k-1) u^2 (p = |u|^2),
 //   Gu[n] = sum_q g[n+q] conj(A_q) + conj(g[n+q]) Bw_q u^2,
 //   A_q = sum_k a[k][q] (k+1) p^k,  Bw_q = sum_{k>=1} a[k][q] k p^(k-1).
+#include <algorithm>
+
 #include "common.h"
+#include "dpd_tile.h"
 
 namespace dfh {
 
@@ -278,49 +281,237 @@ hipError_t launch_adj(const AdjArgs &a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// ------------------------------------------------------------------ PA input adjoint
-__global__ __launch_bounds__(256) void k_mp_adj(const float2 *u, const float2 *a, const float2 *gin, float2 *Gu,
-                                                int64_t n_streams, int64_t len, int K, int Q) {
-  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (t >= n_streams * len) return;
-  const int64_t s = t / len, n = t - s * len;
-  const float2 uv = u[t];
-  const float p = uv.x * uv.x + uv.y * uv.y;
-  const float u2r = uv.x * uv.x - uv.y * uv.y, u2i = 2.f * uv.x * uv.y;
-  float Gr = 0.f, Gi = 0.f;
-  for (int q = 0; q < Q; ++q) {
-    if (n + q >= len) break;
-    const float2 gq = gin[s * len + n + q];
-    float Ar = 0.f, Ai = 0.f, Br = 0.f, Bi = 0.f;
-    float pk = 1.f, pkm1 = 1.f;                    // p^k, p^(k-1)
-    for (int k = 0; k < K; ++k) {
-      const float2 c = a[k * Q + q];
-      Ar += c.x * (k + 1) * pk;
-      Ai += c.y * (k + 1) * pk;
-      if (k >= 1) {
-        Br += c.x * k * pkm1;
-        Bi += c.y * k * pkm1;
-        pkm1 *= p;
-      }
-      pk *= p;
-    }
-    // gq conj(A)
-    Gr += gq.x * Ar + gq.y * Ai;
-    Gi += gq.y * Ar - gq.x * Ai;
-    // conj(gq) Bw u^2
-    const float wr = Br * u2r - Bi * u2i, wi = Br * u2i + Bi * u2r;
-    Gr += gq.x * wr + gq.y * wi;
-    Gi += gq.x * wi - gq.y * wr;
-  }
-  Gu[t] = make_float2(Gr, Gi);
+// ------------------------------------------------------------------ amplifier model
+//
+// Forward with loss and input adjoint of the memory polynomial.  A workgroup
+// takes a run of one row, a thread four consecutive samples of it: with four
+// orders and four taps (the model in use) the thread's window sits in
+// registers, the sixteen coefficients in scalar registers, and everything
+// moves in 16-byte accesses; other sizes, and the samples whose taps cross
+// the row's end, go sample by sample.  HBM-bound at 2^22 samples: the loss
+// reads u and x and writes e (100 MB, 22 us), the adjoint reads u and g and
+// writes Gu (100 MB, 22 us, 32 us with a thread per sample that reloaded
+// its coefficients and formed the powers per tap).
+typedef float f4_any __attribute__((ext_vector_type(4), aligned(8)));
+
+__device__ __forceinline__ void load4(const float2 *p, float2 (&v)[4]) {
+  const f4_any a = *(const f4_any *)p, b = *(const f4_any *)(p + 2);
+  v[0] = make_float2(a.x, a.y), v[1] = make_float2(a.z, a.w);
+  v[2] = make_float2(b.x, b.y), v[3] = make_float2(b.z, b.w);
 }
 
-hipError_t launch_mp_adj(const float2 *u, const float2 *a, const float2 *g, float2 *Gu, int64_t n_streams,
-                         int64_t len, int K, int Q, hipStream_t s) {
-  const int64_t total = n_streams * len;
-  if (total <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_mp_adj, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, u, a, g, Gu, n_streams,
-                     len, K, Q);
+__device__ __forceinline__ void store4(float2 *p, const float2 (&v)[4]) {
+  *(f4_any *)p = f4_any{v[0].x, v[0].y, v[1].x, v[1].y};
+  *(f4_any *)(p + 2) = f4_any{v[2].x, v[2].y, v[3].x, v[3].y};
+}
+
+// Tap q's polynomial at p: P = sum_k a[k][q] p^k, and with DERIV its
+// derivative D = sum_{k>=1} k a[k][q] p^(k-1) (Horner for both).
+template <bool DERIV>
+__device__ __forceinline__ void tap_poly(cfloat2p a, int K, int Q, int q, float p, float2 &P, float2 &D) {
+  P = ldc(a, (K - 1) * Q + q);
+  D = make_float2(0.f, 0.f);
+  for (int k = K - 2; k >= 0; --k) {
+    const float2 c = ldc(a, k * Q + q);
+    if (DERIV) D = make_float2(fmaf(D.x, p, P.x), fmaf(D.y, p, P.y));
+    P = make_float2(fmaf(P.x, p, c.x), fmaf(P.y, p, c.y));
+  }
+}
+
+__device__ __forceinline__ float norm2(float2 v) { return fmaf(v.x, v.x, v.y * v.y); }
+
+__device__ __forceinline__ void add_product(float2 &s, float2 x, float2 y) {   // s += x y
+  s.x = fmaf(x.x, y.x, fmaf(-x.y, y.y, s.x));
+  s.y = fmaf(x.x, y.y, fmaf(x.y, y.x, s.y));
+}
+
+// v[n] of a row.
+__device__ __forceinline__ float2 mp_value(const float2 *u, cfloat2p a, int64_t n, int K, int Q) {
+  float2 v = make_float2(0.f, 0.f), P, D;
+  for (int q = 0; q < Q && q <= n; ++q) {
+    const float2 w = u[n - q];
+    tap_poly<false>(a, K, Q, q, norm2(w), P, D);
+    add_product(v, w, P);
+  }
+  return v;
+}
+
+// One tap's part of Gu: g conj(A) + conj(g) D u^2 with A = P + p D.
+__device__ __forceinline__ void add_adjoint(float2 &G, float2 g, float2 P, float2 D, float p, float2 u2) {
+  const float2 A = make_float2(fmaf(p, D.x, P.x), fmaf(p, D.y, P.y));
+  float2 w = make_float2(0.f, 0.f);
+  add_product(w, D, u2);
+  G.x = fmaf(g.x, A.x, fmaf(g.y, A.y, G.x));
+  G.y = fmaf(g.y, A.x, fmaf(-g.x, A.y, G.y));
+  G.x = fmaf(g.x, w.x, fmaf(g.y, w.y, G.x));
+  G.y = fmaf(g.x, w.y, fmaf(-g.y, w.x, G.y));
+}
+
+__device__ __forceinline__ float2 square(float2 u) { return make_float2(u.x * u.x - u.y * u.y, 2.f * u.x * u.y); }
+
+// Gu[n] of a row, without the scale of g.
+__device__ __forceinline__ float2 mp_adjoint(float2 uv, const float2 *g, cfloat2p a, int64_t n, int64_t len, int K,
+                                             int Q) {
+  float2 G = make_float2(0.f, 0.f), P, D;
+  const float p = norm2(uv);
+  const float2 u2 = square(uv);
+  for (int q = 0; q < Q && n + q < len; ++q) {
+    tap_poly<true>(a, K, Q, q, p, P, D);
+    add_adjoint(G, g[n + q], P, D, p, u2);
+  }
+  return G;
+}
+
+// Runs of 4 * blockDim samples: run i is run i % runs_per_row of row
+// i / runs_per_row; workgroups stride over them.
+// k_mp_loss: e = v - x (stored when e is given) and per workgroup the sum of
+// |e|^2 (each thread's in fp32 over its four samples, the rest in fp64).
+template <bool FOUR>
+__global__ __launch_bounds__(256) void k_mp_loss(MpArgs m, int64_t runs, int64_t runs_per_row) {
+  __shared__ double ws[4];
+  const cfloat2p a = as_const(m.a);
+  double sum = 0.0;
+  for (int64_t i = blockIdx.x; i < runs; i += gridDim.x) {
+    const int64_t row = i / runs_per_row;
+    const int64_t n0 = ((i - row * runs_per_row) * blockDim.x + threadIdx.x) * 4;
+    const float2 *u = m.u + row * m.len, *x = m.x + row * m.len;
+    float2 *e = m.out ? m.out + row * m.len : nullptr;
+    float part = 0.f;
+    if (FOUR && n0 >= 4 && n0 + 4 <= m.len) {
+      float2 h[4], c[4], w[7], xv[4];
+      load4(u + n0 - 4, h);
+      load4(u + n0, c);
+      load4(x + n0, xv);
+#pragma unroll
+      for (int j = 0; j < 7; ++j) w[j] = j < 3 ? h[j + 1] : c[j - 3];     // sample n0 - 3 + j
+      float2 v[4], P, D;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k] = make_float2(-xv[k].x, -xv[k].y);
+#pragma unroll
+      for (int j = 0; j < 7; ++j) {
+        const float p = norm2(w[j]);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int k = j - 3 + q;                                         // output n0 + k
+          if (k < 0 || k > 3) continue;
+          tap_poly<false>(a, 4, 4, q, p, P, D);
+          add_product(v[k], w[j], P);
+        }
+      }
+      if (e) store4(e + n0, v);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) part = fmaf(v[k].x, v[k].x, fmaf(v[k].y, v[k].y, part));
+    } else {
+      for (int64_t n = n0; n < n0 + 4 && n < m.len; ++n) {
+        float2 v = mp_value(u, a, n, m.K, m.Q);
+        v = make_float2(v.x - x[n].x, v.y - x[n].y);
+        if (e) e[n] = v;
+        part = fmaf(v.x, v.x, fmaf(v.y, v.y, part));
+      }
+    }
+    sum += (double)part;
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+  if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = sum;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < (int)(blockDim.x >> 6); ++w) sum += ws[w];
+    m.partial[blockIdx.x] = sum;
+  }
+}
+
+// The workgroups' sums in a fixed order.
+__global__ __launch_bounds__(256) void k_mp_loss_sum(const double *partial, int n, float *loss) {
+  __shared__ double ws[4];
+  double sum = 0.0;
+  for (int k = threadIdx.x; k < n; k += 256) sum += partial[k];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+  if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = sum;
+  __syncthreads();
+  if (threadIdx.x == 0) *loss = (float)(((ws[0] + ws[1]) + ws[2]) + ws[3]);
+}
+
+// Gu from u and the upstream gradient g, or (m.scale) 2 * scale[0] * g.
+template <bool FOUR>
+__global__ __launch_bounds__(256) void k_mp_adj(MpArgs m, int64_t runs, int64_t runs_per_row) {
+  const cfloat2p a = as_const(m.a);
+  const float sc = m.scale ? 2.f * m.scale[0] : 1.f;
+  for (int64_t i = blockIdx.x; i < runs; i += gridDim.x) {
+    const int64_t row = i / runs_per_row;
+    const int64_t n0 = ((i - row * runs_per_row) * blockDim.x + threadIdx.x) * 4;
+    const float2 *u = m.u + row * m.len, *g = m.x + row * m.len;
+    float2 *out = m.out + row * m.len;
+    if (FOUR && n0 + 8 <= m.len) {
+      float2 uv[4], g0[4], g1[4], G[4], P, D;
+      load4(u + n0, uv);
+      load4(g + n0, g0);
+      load4(g + n0 + 4, g1);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const float p = norm2(uv[k]);
+        const float2 u2 = square(uv[k]);
+        G[k] = make_float2(0.f, 0.f);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          tap_poly<true>(a, 4, 4, q, p, P, D);
+          add_adjoint(G[k], k + q < 4 ? g0[(k + q) & 3] : g1[(k + q) & 3], P, D, p, u2);
+        }
+        G[k] = make_float2(sc * G[k].x, sc * G[k].y);
+      }
+      store4(out + n0, G);
+    } else {
+      for (int64_t n = n0; n < n0 + 4 && n < m.len; ++n) {
+        const float2 G = mp_adjoint(u[n], g, a, n, m.len, m.K, m.Q);
+        out[n] = make_float2(sc * G.x, sc * G.y);
+      }
+    }
+  }
+}
+
+namespace {
+
+struct MpGrid {
+  int threads;
+  int64_t runs, runs_per_row;
+};
+
+MpGrid mp_grid(const MpArgs &m) {
+  const int64_t t = (m.len + 3) / 4;                     // threads a row needs
+  MpGrid g;
+  g.threads = (int)std::min<int64_t>(256, (t + 63) / 64 * 64);
+  g.runs_per_row = (t + g.threads - 1) / g.threads;
+  g.runs = m.S * g.runs_per_row;
+  return g;
+}
+
+}  // namespace
+
+hipError_t launch_mp_loss(const MpArgs &m, float *loss, hipStream_t s) {
+  int blocks = 0;
+  if (m.S > 0 && m.len > 0) {
+    const MpGrid g = mp_grid(m);
+    blocks = (int)std::min<int64_t>(g.runs, kMpLossBlocks);
+    if (m.K == 4 && m.Q == 4)
+      hipLaunchKernelGGL(k_mp_loss<true>, dim3(blocks), dim3(g.threads), 0, s, m, g.runs, g.runs_per_row);
+    else
+      hipLaunchKernelGGL(k_mp_loss<false>, dim3(blocks), dim3(g.threads), 0, s, m, g.runs, g.runs_per_row);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(k_mp_loss_sum, dim3(1), dim3(256), 0, s, m.partial, blocks, loss);
+  return hipGetLastError();
+}
+
+hipError_t launch_mp_adj(const MpArgs &m, hipStream_t s) {
+  if (m.S <= 0 || m.len <= 0) return hipSuccess;
+  const MpGrid g = mp_grid(m);
+  const unsigned blocks = (unsigned)std::min<int64_t>(g.runs, 1 << 20);
+  if (m.K == 4 && m.Q == 4)
+    hipLaunchKernelGGL(k_mp_adj<true>, dim3(blocks), dim3(g.threads), 0, s, m, g.runs, g.runs_per_row);
+  else
+    hipLaunchKernelGGL(k_mp_adj<false>, dim3(blocks), dim3(g.threads), 0, s, m, g.runs, g.runs_per_row);
   return hipGetLastError();
 }
 

@@ -305,9 +305,61 @@ extern "C" df_status df_mp_input_adjoint(void *stream, const void *u, const void
   if (K < 1 || K > kMaxBranches || Q < 1 || Q > kMaxTaps) return fail(nullptr, DF_EINVAL, "bad K or Q");
   if (S == 0 || len == 0) return DF_OK;
   if (!u || !a || !g || !Gu) return fail(nullptr, DF_EINVAL, "null pointer");
-  hipError_t e = launch_mp_adj((const float2 *)u, (const float2 *)a, (const float2 *)g, (float2 *)Gu, S, len, K, Q,
-                               (hipStream_t)stream);
+  MpArgs m{};
+  m.u = (const float2 *)u;
+  m.a = (const float2 *)a;
+  m.x = (const float2 *)g;
+  m.out = (float2 *)Gu;
+  m.S = S;
+  m.len = len;
+  m.K = K;
+  m.Q = Q;
+  hipError_t e = launch_mp_adj(m, (hipStream_t)stream);
   if (e != hipSuccess) return fail_hip(nullptr, e, "df_mp_input_adjoint");
+  return DF_OK;
+}
+
+extern "C" int64_t df_mp_loss_work_bytes(void) { return kMpLossBlocks * (int64_t)sizeof(double); }
+
+extern "C" df_status df_mp_loss(void *stream, const void *u, const void *a, const void *x, void *e_out, float *loss,
+                                int64_t S, int64_t len, int32_t K, int32_t Q, void *work, int64_t work_bytes) {
+  df_status st = check_dpd_shape(S, len, len, K, Q, DF_HIST_BRANCH);
+  if (st) return st;
+  if (!loss || !work || work_bytes < df_mp_loss_work_bytes()) return fail(nullptr, DF_EINVAL, "null loss or small work");
+  if ((S > 0 && len > 0) && (!u || !a || !x)) return fail(nullptr, DF_EINVAL, "null pointer");
+  MpArgs m{};
+  m.u = (const float2 *)u;
+  m.a = (const float2 *)a;
+  m.x = (const float2 *)x;
+  m.out = (float2 *)e_out;
+  m.partial = (double *)work;
+  m.S = S;
+  m.len = len;
+  m.K = K;
+  m.Q = Q;
+  hipError_t e = launch_mp_loss(m, loss, (hipStream_t)stream);
+  if (e != hipSuccess) return fail_hip(nullptr, e, "df_mp_loss");
+  return DF_OK;
+}
+
+extern "C" df_status df_mp_loss_adjoint(void *stream, const void *u, const void *a, const void *e_in,
+                                        const float *gloss, void *Gu, int64_t S, int64_t len, int32_t K, int32_t Q) {
+  df_status st = check_dpd_shape(S, len, len, K, Q, DF_HIST_BRANCH);
+  if (st) return st;
+  if (S == 0) return DF_OK;
+  if (!u || !a || !e_in || !gloss || !Gu) return fail(nullptr, DF_EINVAL, "null pointer");
+  MpArgs m{};
+  m.u = (const float2 *)u;
+  m.a = (const float2 *)a;
+  m.x = (const float2 *)e_in;
+  m.out = (float2 *)Gu;
+  m.scale = gloss;
+  m.S = S;
+  m.len = len;
+  m.K = K;
+  m.Q = Q;
+  hipError_t e = launch_mp_adj(m, (hipStream_t)stream);
+  if (e != hipSuccess) return fail_hip(nullptr, e, "df_mp_loss_adjoint");
   return DF_OK;
 }
 

@@ -90,6 +90,9 @@ _SIGS = {
     "df_dpd_coeff_adjoint": ([_P, _P, _P, _P, _P, _I64, _I64, _I64, _I32, _I32, _I32, _P, _I64], _I32),
     "df_dpd_coeff_adjoint_work_bytes": ([_I64, _I64, _I64, _I32, _I32], _I64),
     "df_mp_input_adjoint": ([_P, _P, _P, _P, _P, _I64, _I64, _I32, _I32], _I32),
+    "df_mp_loss_work_bytes": ([], _I64),
+    "df_mp_loss": ([_P, _P, _P, _P, _P, _P, _I64, _I64, _I32, _I32, _P, _I64], _I32),
+    "df_mp_loss_adjoint": ([_P, _P, _P, _P, _P, _P, _I64, _I64, _I32, _I32], _I32),
     "df_stream_copy": ([_P, _P, _P, _I64], _I32),
     "df_hbm_ref": ([_P, _I32, _P, _P, _I64], _I32),
     "df_paper_channel_bytes": ([_I64, _I64, _I32], _I64),
@@ -509,6 +512,47 @@ def df_mp_input_adjoint(u, a, g, Gu, stream=None) -> None:
     K, Q = a.shape
     _check(_lib.df_mp_input_adjoint(_stream_ptr(stream), _dev_ptr(u), _dev_ptr(a), _dev_ptr(g), _dev_ptr(Gu),
                                     S, L, K, Q))
+
+
+def _check_mp(a, **rows) -> None:
+    shape = None
+    for name, t in rows.items():
+        if not _tensor_dtype_ok(t, DF_C64):
+            raise ValueError(f"{name} must be complex64, got {t.dtype}")
+        if t.dim() != 2 or (shape is not None and tuple(t.shape) != shape):
+            raise ValueError(f"{', '.join(rows)} must be [S, L] of equal shape")
+        shape = tuple(t.shape)
+    if a.dim() != 2 or not _tensor_dtype_ok(a, DF_C64):
+        raise ValueError("a must be a complex64 [K, Q] tensor")
+
+
+def _check_scalar(t, name: str) -> None:
+    if t.numel() != 1 or str(t.dtype) != "torch.float32":
+        raise ValueError(f"{name} must be one float32")
+
+
+def df_mp_loss_work_bytes() -> int:
+    return int(_lib.df_mp_loss_work_bytes())
+
+
+def df_mp_loss(u, a, x, e, loss, work, stream=None) -> None:
+    """loss = sum |PA(u) - x|^2 (one float32); e (or None) receives PA(u) - x."""
+    _check_mp(a, u=u, x=x, **({} if e is None else {"e": e}))
+    _check_scalar(loss, "loss")
+    S, L = u.shape
+    K, Q = a.shape
+    _check(_lib.df_mp_loss(_stream_ptr(stream), _dev_ptr(u), _dev_ptr(a), _dev_ptr(x), None if e is None else _dev_ptr(e),
+                           _dev_ptr(loss), S, L, K, Q, _dev_ptr(work), work.numel() * work.element_size()))
+
+
+def df_mp_loss_adjoint(u, a, e, gloss, Gu, stream=None) -> None:
+    """Gu for e of df_mp_loss and the upstream gradient gloss (one float32)."""
+    _check_mp(a, u=u, e=e, Gu=Gu)
+    _check_scalar(gloss, "gloss")
+    S, L = u.shape
+    K, Q = a.shape
+    _check(_lib.df_mp_loss_adjoint(_stream_ptr(stream), _dev_ptr(u), _dev_ptr(a), _dev_ptr(e), _dev_ptr(gloss),
+                                   _dev_ptr(Gu), S, L, K, Q))
 
 
 def df_stream_copy(src, dst, nbytes: int, stream=None) -> None:
