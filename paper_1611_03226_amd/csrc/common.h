@@ -360,6 +360,11 @@ hipError_t launch_mask_tables(const int32_t *ctrl, int32_t *B, int64_t *off, con
 size_t coef_rows_bytes(int M);
 hipError_t launch_coef_rows(const float2 *h, float2 *ht, int B_max, int M, hipStream_t s);
 hipError_t launch_dpd_heads(const DpdArgs &a, hipStream_t s);
+// One batch of at most 64 firings of an actor (x_idx, y_idx, hist, ticket and
+// commit set; c as for launch_scan of the batch): control intake, tables, head
+// corrections, body and commit in one launch.
+hipError_t launch_dpd_small(const DpdArgs &a, const ScanArgs &c, hipStream_t s, int tile, int outputs_per_thread,
+                            const KTiming *timing = nullptr);
 // Body form for M = 16 from the environment: the VALU form, or the
 // matrix-core form with DFHIP_BODY=mx (measured slower on MI355X: the
 // complex products and row combination it leaves on the VALU cost nearly

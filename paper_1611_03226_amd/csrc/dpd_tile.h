@@ -203,6 +203,20 @@ __device__ __forceinline__ void head_taps(cfloat2p hg, int b, float psr, float p
   if constexpr (m + 1 < M) head_taps<M, m + 1>(hg, b, psr, psi, sr, si);
 }
 
+// The same with the lane's branch's own coefficients (LDS or memory, hb[m]).
+template <int M, int m>
+__device__ __forceinline__ void row_taps(const float2 *hb, float psr, float psi, float &sr, float &si) {
+  if constexpr (m < M) {
+    const float2 c = hb[m];
+    const float vr = row_shl<M - 1 - m>(psr), vi = row_shl<M - 1 - m>(psi);
+    sr = fmaf(c.x, vr, sr);
+    sr = fmaf(-c.y, vi, sr);
+    si = fmaf(c.x, vi, si);
+    si = fmaf(c.y, vr, si);
+    row_taps<M, m + 1>(hb, psr, psi, sr, si);
+  }
+}
+
 // Head corrections of up to four firings of one actor (one wavefront; lane
 // 16*row + i serves firing `row`, history sample / output i).  Outputs
 // q < M-1 of a firing reach back before its first sample, where branch b
@@ -327,6 +341,7 @@ struct Job {
   int B;                  // its Horner length (highest active branch + 1)
   int first;              // first tile of its firing (0/1): no samples before it
   int head;               // ... whose outputs take head corrections (0/1)
+  int g;                  // firing (workgroups that form their own head corrections)
 };
 
 // Where a run of n consecutive ring samples from position p starts, and
@@ -349,7 +364,8 @@ struct TileRegs {
 // Indices are clamped into the window, and below a firing's start onto its
 // first sample (commit_tile writes 0 there), so that no load is conditional
 // and none is waited for here.
-template <int K>
+// CORR: head corrections come from memory (else the workgroup forms them).
+template <int K, bool CORR = true>
 __device__ __forceinline__ void load_tile(TileRegs<K> &r, const Job &j, int M) {
   const int tid = threadIdx.x, nt = blockDim.x, lo = j.first ? M - 1 : 0, hi = j.nout + M - 2;
   int64_t slot;
@@ -364,21 +380,21 @@ __device__ __forceinline__ void load_tile(TileRegs<K> &r, const Job &j, int M) {
     for (int u = 0; u < K; ++u) r.win[u] = j.x[(slot + min(max(tid + u * nt, lo), hi)) & j.x_mask];
     if (tid < M - 1) r.win[K] = j.x[(slot + min(K * nt + tid, hi)) & j.x_mask];
   }
-  if (j.head && tid < M - 1) r.cv = j.corr[tid];
+  if (CORR && j.head && tid < M - 1) r.cv = j.corr[tid];
 }
 
 // Waits for the loads of load_tile.  The workgroup does so before it stores a
 // tile's outputs: loads and stores count on one counter in issue order, and a
 // wait at the next commit would be for the stores too.
-template <int K>
+template <int K, bool CORR = true>
 __device__ __forceinline__ void settle(TileRegs<K> &r) {
 #pragma unroll
   for (int u = 0; u < K + 1; ++u) asm volatile("" : "+v"(r.win[u].x), "+v"(r.win[u].y));
-  asm volatile("" : "+v"(r.cv.x), "+v"(r.cv.y));
+  if (CORR) asm volatile("" : "+v"(r.cv.x), "+v"(r.cv.y));
 }
 
 // nt is a multiple of K, so a thread's slots are equally spaced.
-template <int K>
+template <int K, bool CORR = true>
 __device__ __forceinline__ void commit_tile(float2 *sx, float2 *sc, const TileRegs<K> &r, const Job &j, int M) {
   const int tid = threadIdx.x, step = lds_slot<K>(blockDim.x);
   float2 *p = sx + lds_slot<K>(tid);
@@ -387,7 +403,7 @@ __device__ __forceinline__ void commit_tile(float2 *sx, float2 *sc, const TileRe
   for (int u = 1; u < K; ++u) p[u * step] = r.win[u];
   if (tid < M - 1) {
     p[K * step] = r.win[K];
-    if (j.head) sc[tid] = r.cv;
+    if (CORR && j.head) sc[tid] = r.cv;
   }
 }
 
@@ -484,27 +500,33 @@ struct Walk {
 
 // The whole pipelined loop over a workgroup's tiles.
 // src.fetch(k) loads tile k's raw descriptor two tiles ahead; src.expand(raw,
-// job) turns it into the uniform Job when the tile's loads are issued.
+// job) turns it into the uniform Job when the tile's loads are issued.  A
+// source with kOwnHeads forms a first tile's head corrections itself
+// (src.heads, the whole workgroup, into sc).
 // MT: the compiled tap count, or 0 (any count, Mr).
 template <int MT, int K, int BC, bool MASKED, class Src>
 __device__ __forceinline__ void run_tiles(float2 *sx, float2 *sc, int64_t n_items, Src &src, int Mr) {
+  constexpr bool CORR = !Src::kOwnHeads;
   const int M = MT ? MT : Mr;
   Walk w;
   if (!w.start(n_items)) return;                     // uniform
   Job cur, nxt;
   src.expand(src.fetch(w.item), cur);
   TileRegs<K> regs;
-  load_tile<K>(regs, cur, M);
+  load_tile<K, CORR>(regs, cur, M);
   if (w.left > 1) src.expand(src.fetch(w.item + w.step), nxt);
   for (;;) {
-    commit_tile<K>(sx, sc, regs, cur, M);
+    commit_tile<K, CORR>(sx, sc, regs, cur, M);
+    if constexpr (Src::kOwnHeads) {
+      if (cur.head) src.heads(sc, cur, M);
+    }
     __syncthreads();
-    if (w.left > 1) load_tile<K>(regs, nxt, M);
+    if (w.left > 1) load_tile<K, CORR>(regs, nxt, M);
     typename Src::Raw nn{};
     if (w.left > 2) nn = src.fetch(w.item + 2 * w.step);
     float ar[K], ai[K];
     tile_compute<MT, K, BC, MASKED>(sx, as_const(cur.h), cur, M, ar, ai);
-    if (w.left > 1) settle<K>(regs);
+    if (w.left > 1) settle<K, CORR>(regs);
     tile_store<K>(sc, cur, M, ar, ai);
     if (w.left == 1) break;
     __syncthreads();

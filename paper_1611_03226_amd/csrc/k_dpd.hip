@@ -59,13 +59,15 @@ hipError_t launch_coef_rows(const float2 *h, float2 *ht, int B_max, int M, hipSt
 // Advance the channel indices by the batch's token counts and carry each
 // branch's history: the last M-1 input samples of its last feeding firing.
 // One workgroup (the body's last).
-__device__ __forceinline__ void dpd_commit_block(const DpdCommitArgs &a) {
+// last_of(b): the last feeding firing of branch b, -1 for none.
+template <class LastOf>
+__device__ __forceinline__ void dpd_commit_block(const DpdCommitArgs &a, LastOf last_of) {
   const int64_t Rx = a.x_idx[0];
   __syncthreads();
   const int L = a.M - 1;
   for (int t = threadIdx.x; t < a.B_max * L; t += blockDim.x) {
     const int b = t / L, k = t - b * L;
-    const int64_t lf = a.last[b];
+    const int64_t lf = last_of(b);
     if (lf >= 0) a.hist[b * L + k] = a.x[(Rx + lf * a.r + a.r - L + k) & a.x_mask];
   }
   __syncthreads();
@@ -193,6 +195,7 @@ __global__ __launch_bounds__(256) void k_dpd_heads(DpdArgs a) {
 // (k / tpf)-th firing in processing order (pairs (firing, branch set) from
 // the scan, or firing order).
 struct SingleSrc {
+  static constexpr bool kOwnHeads = false;
   const DpdArgs &a;
   int64_t Rx, Wy;
   __device__ SingleSrc(const DpdArgs &a_)
@@ -248,9 +251,160 @@ __global__ __launch_bounds__(256) void k_dpd_tiled(DpdArgs a) {
                  (int)gridDim.x - 1;
   __syncthreads();
   if (last_block) {
-    dpd_commit_block(a.commit);
+    dpd_commit_block(a.commit, [&](int b) { return a.commit.last[b]; });
     if (threadIdx.x == 0) *a.ticket = 0;              // ready for the next batch
   }
+}
+
+// ------------------------------------------------------------------ small batches
+//
+// A batch of at most 64 firings in one launch: every wavefront reads the
+// batch's control tokens (lane = firing), so a ballot per branch gives every
+// history source, table entry and last feeder; the workgroup of a firing's
+// first tile forms its head corrections, the last workgroup commits.  A small
+// batch is bound by launches and latency: 64 firings of 256 samples took scan,
+// head pass and body 5 + 6 + 7 us and two kernel boundaries, here 10 us (a
+// pass with push and pop 27 and 20.5 us).
+struct SmallSrc {
+  static constexpr bool kOwnHeads = true;
+  const DpdArgs &a;
+  int64_t Rx, Wy;
+  uint32_t sets;          // lane g: branch set of firing g
+  bool shared_hist;
+  float2 *part;           // LDS [16][32]: a branch's part of each correction
+  const float2 *hs;       // LDS [B_max][M] coefficients
+  struct Raw {
+    uint32_t g, tile;
+  };
+  __device__ Raw fetch(int64_t it) const {
+    const uint32_t k = (uint32_t)it / (uint32_t)a.tiles_per_firing;
+    return {k, (uint32_t)it - k * (uint32_t)a.tiles_per_firing};
+  }
+  __device__ void expand(const Raw &q, Job &j) const {
+    const uint32_t set = (uint32_t)__builtin_amdgcn_readlane((int)sets, (int)q.g);
+    const int64_t t0 = (int64_t)q.tile * a.tile;
+    j.x = a.x;
+    j.y = a.y;
+    j.h = a.ht;
+    j.corr = nullptr;
+    j.x_mask = a.x_mask;
+    j.y_mask = a.y_mask;
+    j.xb = Rx + (int64_t)q.g * a.r + t0;
+    j.yb = Wy + (int64_t)q.g * a.r + t0;
+    j.nout = (int)min((int64_t)a.tile, a.r - t0);
+    j.set = set;
+    j.B = set_len(set);
+    j.first = t0 == 0;
+    j.head = t0 == 0 && set != 0u;
+    j.g = (int)q.g;
+  }
+  // Firings (bits) that feed branch b.
+  __device__ uint64_t fed(int b) const {
+    const int lane = threadIdx.x & 63;
+    return __ballot(lane < (int)a.n_firings && (shared_hist || in_set(sets, b)));
+  }
+  // Head corrections of firing j.g, as the head pass forms them (the same
+  // sums in the same order): branch b by a row of lanes (16, or 32 for tap
+  // counts that are not compiled in), lane i its history sample and output.
+  template <int MT>
+  __device__ void form(float2 *sc, const Job &j, int Mr) const {
+    constexpr int RL = MT ? 16 : 32, ROWS = 64 / RL;
+    const int M = MT ? MT : Mr, L = M - 1;
+    const int lane = threadIdx.x & 63, row = lane / RL, i = lane % RL;
+    const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    const uint64_t before = (1ull << j.g) - 1;
+    for (int b0 = 0; b0 < j.B; b0 += nw * ROWS) {        // uniform
+      const int b = b0 + w * ROWS + row;
+      int pf = -1;
+      for (int c = 0; c < j.B; ++c) {
+        const uint64_t below = fed(c) & before;
+        if (c == b) pf = below ? 63 - __clzll((long long)below) : -1;
+      }
+      float2 xv = make_float2(0.f, 0.f);
+      if (b < j.B && in_set(j.set, b) && i < L)
+        xv = pf >= 0 ? a.x[(Rx + (int64_t)pf * a.r + a.r - L + i) & a.x_mask] : a.hist[b * L + i];
+      const float pp = fmaf(xv.x, xv.x, xv.y * xv.y);
+      float pb = 1.f;
+      for (int e = 0; e < j.B; ++e) pb = e < b ? pb * pp : pb;
+      const float pr = pb * xv.x, pi = pb * xv.y;
+      const float2 *hb = hs + (b < j.B ? b : 0) * M;
+      float sr = 0.f, si = 0.f;
+      if constexpr (MT != 0) {
+        row_taps<MT, 1>(hb, pr, pi, sr, si);
+      } else {
+        for (int m = 1; m < M; ++m) {
+          const int from = RL * row + ((L + i - m) & (RL - 1));
+          const float vr = __shfl(pr, from), vi = __shfl(pi, from);
+          if (m > i) {
+            const float2 c = hb[m];
+            sr = fmaf(c.x, vr, sr);
+            sr = fmaf(-c.y, vi, sr);
+            si = fmaf(c.x, vi, si);
+            si = fmaf(c.y, vr, si);
+          }
+        }
+      }
+      if (b < j.B) part[b * 32 + i] = make_float2(sr, si);
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < L) {
+      float cr = 0.f, ci = 0.f;
+      for (int b = 0; b < j.B; ++b)
+        if (in_set(j.set, b)) {
+          cr += part[b * 32 + threadIdx.x].x;
+          ci += part[b * 32 + threadIdx.x].y;
+        }
+      sc[threadIdx.x] = make_float2(cr, ci);
+    }
+  }
+};
+
+template <int MT>
+struct SmallTiles : SmallSrc {
+  __device__ void heads(float2 *sc, const Job &j, int M) const { form<MT>(sc, j, M); }
+};
+
+template <int MT, int K, int BC, bool MASKED>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_dpd_small(DpdArgs a, ScanArgs c) {
+  extern __shared__ float2 lds[];   // [M-1] head corrections, window, [16][32] parts, [B_max][M] coefficients
+  const int M = MT ? MT : a.M;
+  float2 *sc = lds, *sx = sc + lds_corr(M), *part = sx + lds_window<K>(a.tile + M - 1), *hs = part + 16 * 32;
+  const int lane = threadIdx.x & 63, n = (int)a.n_firings;
+  bool bad = false;
+  uint32_t set = 0u;
+  if (lane < n) set = token_set(c.ctrl[(c.ctrl_pos + lane) & c.ctrl_mask], c.ctrl_mode, a.B_max, &bad);
+  SmallTiles<MT> src{{a, as_const(a.x_idx)[0], as_const(a.y_idx)[1], set, c.hist_mode == 1, part, hs}};
+  for (int t = threadIdx.x; t < a.B_max * M; t += blockDim.x) hs[t] = a.h[t];
+  if (threadIdx.x < 64) {
+    if (blockIdx.x == 0 && __ballot(bad) && lane == 0) atomicOr(c.err, (int32_t)kErrControl);
+    for (int g = blockIdx.x; g < n; g += gridDim.x) {    // the tables of firing g (as the head pass writes them)
+      const uint64_t before = (1ull << g) - 1;
+      for (int b = 0; b < a.B_max; ++b) {
+        const uint64_t below = src.fed(b) & before;
+        if (lane == b) {
+          c.prev_out[(int64_t)b * c.stride + g] = below ? 63 - __clzll((long long)below) : -1;
+          c.off_out[(int64_t)b * c.stride + g] = a.r * __popcll(below);
+        }
+      }
+      if (lane == g) c.B_out[g] = (int32_t)set;
+    }
+  }
+  __syncthreads();
+  run_tiles<MT, K, BC, MASKED>(sx, sc, a.n_firings * a.tiles_per_firing, src, a.M);
+  __shared__ int last_block, last[kMaxBranches];         // commit by the last workgroup, as k_dpd_tiled
+  __syncthreads();
+  if (threadIdx.x == 0)
+    last_block = __hip_atomic_fetch_add(a.ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
+  __syncthreads();
+  if (!last_block) return;
+  if (threadIdx.x < 64)
+    for (int b = 0; b < a.B_max; ++b) {
+      const uint64_t f = src.fed(b);
+      if (lane == 0) last[b] = f ? 63 - __clzll((long long)f) : -1;
+    }
+  __syncthreads();
+  dpd_commit_block(a.commit, [&](int b) { return (int64_t)last[b]; });
+  if (threadIdx.x == 0) *a.ticket = 0;
 }
 
 // The same loop with matrix-core tiles (M = 16).
@@ -268,7 +422,7 @@ __global__ __launch_bounds__(256) void k_dpd_tiled_mx(DpdArgs a) {
                  (int)gridDim.x - 1;
   __syncthreads();
   if (last_block) {
-    dpd_commit_block(a.commit);
+    dpd_commit_block(a.commit, [&](int b) { return a.commit.last[b]; });
     if (threadIdx.x == 0) *a.ticket = 0;
   }
 }
@@ -315,6 +469,24 @@ static hipError_t launch_tiled(const DpdArgs &a0, hipStream_t s, int tile, const
 // runs the kernels whose taps are a loop.
 static bool compiled_taps(int M) { return M == 4 || M == 8 || M == 16; }
 
+template <int MT, int K, int BC, bool MASKED>
+static hipError_t launch_small(const DpdArgs &a0, const ScanArgs &c, hipStream_t s, int tile, const KTiming *t) {
+  DpdArgs a = a0;
+  a.tile = tile;
+  a.tiles_per_firing = (int32_t)((a.r + tile - 1) / tile);
+  const int threads = tile / K;
+  const size_t lds = (size_t)(lds_window<K>(tile + a.M - 1) + lds_corr(a.M) + 16 * 32 + a.B_max * a.M) * sizeof(float2);
+  const int64_t items = a.n_firings * a.tiles_per_firing;
+  const int64_t resident = resident_blocks((const void *)k_dpd_small<MT, K, BC, MASKED>, threads, lds);
+  const int64_t blocks = items < resident ? items : resident;
+  if (t)
+    hipExtLaunchKernelGGL((k_dpd_small<MT, K, BC, MASKED>), dim3((unsigned)blocks), dim3(threads), lds, s, t->start,
+                          t->stop, 0, a, c);
+  else
+    hipLaunchKernelGGL((k_dpd_small<MT, K, BC, MASKED>), dim3((unsigned)blocks), dim3(threads), lds, s, a, c);
+  return hipGetLastError();
+}
+
 bool dpd_body_mx_env() {
   const char *v = getenv("DFHIP_BODY");
   return v && strcmp(v, "mx") == 0;
@@ -341,9 +513,11 @@ hipError_t launch_dpd_heads(const DpdArgs &a, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_dpd_body(const DpdArgs &a, hipStream_t s, int tile, int outputs_per_thread, const KTiming *t) {
-  if (a.n_firings <= 0) return hipSuccess;
-  if (!a.ht || a.M < 1 || a.M > kMaxTaps) return hipErrorInvalidValue;
+struct TileShape {
+  int K, tile;
+};
+
+static TileShape tile_shape(const DpdArgs &a, int tile, int outputs_per_thread) {
   // Shape: 2048 outputs with eight per thread where firings fill such tiles
   // and there is one for each of the 256 compute units (fewer scalar loads,
   // LDS reads and |x|^2 per output; ms against 1024 with four: 32 firings of
@@ -351,8 +525,8 @@ hipError_t launch_dpd_body(const DpdArgs &a, hipStream_t s, int tile, int output
   // 4096 0.108 / 0.107; 128 of 4096 0.014 / 0.014), else 1024 with four (777
   // firings of 1000: 0.019 / 0.023).  A caller's own choice of either value
   // stands (df_set_tile).
-  // Tile: a multiple of 64*K outputs, at most 256 threads, no larger than
-  // needed for one firing.
+  // The tile is a multiple of 64*K outputs, at most 256 threads, no larger
+  // than needed for one firing.
   const bool big = tile <= 0 && a.r >= 2048 && a.n_firings * a.r >= 256 * 2048;
   const int K = outputs_per_thread == 8 || (outputs_per_thread == 0 && big) ? 8 : 4;
   int tl = tile > 0 ? tile : (outputs_per_thread == 0 && big ? 2048 : 1024);
@@ -361,6 +535,32 @@ hipError_t launch_dpd_body(const DpdArgs &a, hipStream_t s, int tile, int output
   tl = (tl / (64 * K)) * (64 * K);
   if (tl < 64 * K) tl = 64 * K;
   if (tl / K > 256) tl = 256 * K;
+  return {K, tl};
+}
+
+hipError_t launch_dpd_small(const DpdArgs &a, const ScanArgs &c, hipStream_t s, int tile, int outputs_per_thread,
+                            const KTiming *t) {
+  if (a.n_firings < 1 || a.n_firings > 64 || !a.ht || !a.h || !a.hist || !a.x_idx || !a.y_idx || !a.ticket || !c.ctrl ||
+      !c.B_out || !c.prev_out || !c.off_out || !c.err || a.M < 1 || a.M > kMaxTaps)
+    return hipErrorInvalidValue;
+  const TileShape sh = tile_shape(a, tile, outputs_per_thread);
+  const bool small = a.B_max <= 10;
+#define DF_SMALL(m, k)                                                                       \
+  if ((m == 0 || a.M == m) && sh.K == k)                                                     \
+    return a.masked ? launch_small<m, k, 16, true>(a, c, s, sh.tile, t)                      \
+                    : (small ? launch_small<m, k, 10, false>(a, c, s, sh.tile, t)            \
+                             : launch_small<m, k, 16, false>(a, c, s, sh.tile, t));
+  DF_SMALL(16, 4) DF_SMALL(16, 8) DF_SMALL(8, 4) DF_SMALL(8, 8) DF_SMALL(4, 4) DF_SMALL(4, 8)
+  DF_SMALL(0, 4) DF_SMALL(0, 8)
+#undef DF_SMALL
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_dpd_body(const DpdArgs &a, hipStream_t s, int tile, int outputs_per_thread, const KTiming *t) {
+  if (a.n_firings <= 0) return hipSuccess;
+  if (!a.ht || a.M < 1 || a.M > kMaxTaps) return hipErrorInvalidValue;
+  const TileShape sh = tile_shape(a, tile, outputs_per_thread);
+  const int K = sh.K, tl = sh.tile;
   // compiled paths: Horner lengths up to 10 or up to 16; branch sets that are
   // not prefixes (bit-mask tokens) take the masked paths up to 16
   const bool small = a.B_max <= 10;

@@ -243,6 +243,7 @@ __device__ __forceinline__ void pers_items(const PersArgs &a, int64_t blk, int64
 struct ItemSrc {
   const PersArgs &a;
   static constexpr int kWords = (int)(sizeof(PItem) / 4);
+  static constexpr bool kOwnHeads = false;
   struct Raw {
     uint32_t dv;          // lane-distributed words
   };

@@ -780,7 +780,8 @@ df_status dfh::dpd_enqueue(df_graph *g, Actor &a, int64_t n, bool may_run_ahead)
     a.ahead = -1;
   }
   Actor::ScanSlot &sl = a.scan[s];
-  if (!scanned)
+  const bool small = n <= 64 && !(g->body_mx && M == 16);   // one launch does it all
+  if (!scanned && !small)
     HIPCHK(g, launch_scan(scan_args(g, a, sl, pos, n, ordered, g->err_dev), g->stream, false, false));
   ScanArgs sa{};                                     // where the scan left its tables
   sa.n_segs = 1;
@@ -829,7 +830,7 @@ df_status dfh::dpd_enqueue(df_graph *g, Actor &a, int64_t n, bool may_run_ahead)
     da.ahead = scan_args(g, a, a.scan[t], pos + n, n, ordered, a.scan[t].err);
     da.ahead_blocks = (int32_t)((scan_groups(1, n) + 3) / 4);
   }
-  HIPCHK(g, launch_dpd_heads(da, g->stream));
+  if (!small) HIPCHK(g, launch_dpd_heads(da, g->stream));
   DpdCommitArgs ca{};
   ca.x = (const float2 *)fx.ring;
   ca.x_idx = fx.idx;
@@ -847,7 +848,11 @@ df_status dfh::dpd_enqueue(df_graph *g, Actor &a, int64_t n, bool may_run_ahead)
   da.commit = ca;
   KTiming kt;
   HIPCHK(g, prof_pair(g, &kt, (int)(&a - g->actors.data())));
-  HIPCHK(g, launch_dpd_body(da, g->stream, g->tile, g->outputs_per_thread, g->prof ? &kt : nullptr));
+  if (small)
+    HIPCHK(g, launch_dpd_small(da, scan_args(g, a, sl, pos, n, false, g->err_dev), g->stream, g->tile,
+                               g->outputs_per_thread, g->prof ? &kt : nullptr));
+  else
+    HIPCHK(g, launch_dpd_body(da, g->stream, g->tile, g->outputs_per_thread, g->prof ? &kt : nullptr));
 
   fc.read_h += n;
   fx.read_h += n * r;
