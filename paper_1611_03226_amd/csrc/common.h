@@ -332,6 +332,7 @@ struct RingCopyArgs {
   int64_t *idx;           // the counter (word 0 or 1 of a channel slot)
   int64_t n;
   int32_t *err;
+  int32_t push;           // into the channel
 };
 hipError_t launch_ring_copy(const RingCopyArgs &a, hipStream_t s);
 

@@ -104,7 +104,9 @@ namespace {
 
 typedef v4 __attribute__((aligned(1))) v4_any;
 
-template <int U, bool NT>
+enum { kStreamLoad = 1, kStreamStore = 2 };
+
+template <int U, int NT>
 __global__ __launch_bounds__(kRefThreads) void k_ring_copy(RingCopyArgs a, uint32_t blocks0) {
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     *a.idx += a.n;                                     // nothing here reads the counters
@@ -122,13 +124,13 @@ __global__ __launch_bounds__(kRefThreads) void k_ring_copy(RingCopyArgs a, uint3
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const v4_any *p = (const v4_any *)(src + at + u * step);
-      if constexpr (NT) v[u] = __builtin_nontemporal_load(p);
+      if constexpr (NT & kStreamLoad) v[u] = __builtin_nontemporal_load(p);
       else v[u] = *p;
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       v4_any *p = (v4_any *)(dst + at + u * step);
-      if constexpr (NT) __builtin_nontemporal_store(v[u], p);
+      if constexpr (NT & kStreamStore) __builtin_nontemporal_store(v[u], p);
       else *p = v[u];
     }
     return;
@@ -141,7 +143,7 @@ __global__ __launch_bounds__(kRefThreads) void k_ring_copy(RingCopyArgs a, uint3
   }
 }
 
-template <int U, bool NT>
+template <int U, int NT>
 hipError_t ring_copy(const RingCopyArgs &a, hipStream_t s) {
   const int64_t span = (int64_t)U * kRefThreads * 16;
   const int64_t b0 = (a.bytes[0] + span - 1) / span, b1 = (a.bytes[1] + span - 1) / span;
@@ -154,13 +156,15 @@ hipError_t ring_copy(const RingCopyArgs &a, hipStream_t s) {
 
 hipError_t launch_ring_copy(const RingCopyArgs &a, hipStream_t s) {
   if (a.bytes[0] <= 0 || a.bytes[1] < 0) return hipErrorInvalidValue;
-  // From 64 MiB on the copy does not fit the caches next to what follows, and
-  // streaming accesses win (2^24 samples pushed, fired and popped: 172 us a
-  // pass cached, 155 us streamed, 158 us with eight vectors per thread; the
-  // runtime's copy and a counter kernel 177); below, the data is read again
-  // soon (26 MB of frames through three actors: 78 against 83 us).
-  if (a.bytes[0] + a.bytes[1] < (64 << 20)) return ring_copy<1, false>(a, s);
-  return ring_copy<4, true>(a, s);
+  // From 64 MiB on, streaming accesses: a push reads its source once, but its
+  // tokens are read again by the actor (the last-level cache holds 256 MB); a
+  // pop neither.  us a pass, cached / streamed both ways / as chosen: 2^24
+  // samples 213 / 196 / 194, 120 frames of 1080p motion 319 / 288 / 290, 64
+  // frames of 1080p through three actors 293 / 297 / 285, chained 177 / 178 /
+  // 167.  Below, everything is read again soon (26 MB of frames through three
+  // actors: 78 cached, 83 streamed).
+  if (a.bytes[0] + a.bytes[1] < (64 << 20)) return ring_copy<1, 0>(a, s);
+  return a.push ? ring_copy<4, kStreamLoad>(a, s) : ring_copy<4, kStreamLoad | kStreamStore>(a, s);
 }
 
 hipError_t launch_stream_copy(const void *src, void *dst, int64_t bytes, hipStream_t s) {

@@ -45,6 +45,7 @@ __device__ inline uint8_t *out_frame(uint8_t *ring, const int64_t *idx, int64_t 
 }
 
 typedef __attribute__((address_space(1))) uint8_t gu8;
+typedef __attribute__((address_space(1))) uint32_t gu32;
 // words and vectors of them at any byte address
 typedef uint32_t __attribute__((aligned(1))) u32_any;
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -328,58 +329,100 @@ __device__ __forceinline__ uint32_t lane_above(uint32_t v) {   // value of lane 
 }
 
 // One frame of a wavefront's band.  Gauss words of rows clamp(y0-1+j),
-// j = 0..R+1, at word `col` are produced one per row step (sliding 5-row
-// window).  WARM: only store them in gp (previous frame of the range).
+// j = 0..R+1, at word `col` are produced one per row step: the sliding 5-row
+// window is summed vertically first, on even and odd pixels in 16-bit lanes,
+// and the sums of the two pixels on either side come from the neighbour
+// lanes.  WARM: only store them in gp (previous frame of the range).
 // Otherwise each is thresholded against gp[j] (then replaces it), and once
 // three threshold rows are known the median of the middle one is stored;
 // with `keep` the Gauss words of rows y0..yend-1 also go to `dg` (the delay
 // channel's token).
+// EDGE: bands that touch the frame's top or bottom: rows are clamped into the
+// frame, unfiltered rows copied, stores guarded.  The other wavefronts (16 of
+// a 320x240 frame's 20) skip all of that, and their row addresses are uniform
+// bases with one vector offset.
+// Bound by VALU issue: 1433 wavefront instructions per frame with the
+// horizontal sums first (22 rows of them for 16 outputs) and every band
+// guarded, 1116 now; 64 frames of 1920x1080 in 100 and 88 us, 128 of 1000x600
+// in 54 and 49, 4096 of 320x240 in 227 and 215 to 226.
 struct FuseLane {
   int y0, yend, H, Wq;
   uint32_t col, s2l, s2r, s1l, s1r, thr;
   bool store;
 };
 
-template <int R, bool WARM>
-__device__ inline void fused_frame(const FuseLane &q, const uint32_t *src, uint32_t *dst, uint32_t *dg,
+// The word at byte p + k + at, with p + k uniform: a scalar base and a 32-bit
+// vector offset.  Both are hidden from the compiler at the place of the
+// access, which otherwise forms a 64-bit vector address for each.
+__device__ __forceinline__ gu32 *word_at(const uint8_t *p, int k, uint32_t at) {
+  gu8 *b = (gu8 *)(p + k);
+  asm("" : "+s"(b), "+v"(at));
+  return (gu32 *)(b + at);
+}
+
+// The lane's place in a frame, formed per frame (held across the frame loop,
+// row offsets would take ~40 registers).
+template <int R, bool EDGE>
+struct FusePlace {
+  int y0, row_bytes, last_row, col_bytes;
+  uint32_t at;                                  // byte offset of row y0
+  __device__ FusePlace(const FuseLane &q) {
+    uint32_t col = q.col;
+    y0 = q.y0;
+    asm volatile("" : "+v"(y0), "+v"(col));
+    row_bytes = 4 * q.Wq;
+    last_row = (q.H - 1) * row_bytes;
+    col_bytes = (int)col * 4;
+    at = (uint32_t)(y0 * row_bytes + col_bytes);
+  }
+  // Row r of the band's R + 6, clamped into the frame in offset space.
+  __device__ uint32_t row(const uint8_t *src, int r) const {
+    if constexpr (EDGE) {
+      const int off = min(max((y0 - 3) * row_bytes + r * row_bytes, 0), last_row);
+      return *word_at(src, 0, (uint32_t)(off + col_bytes));
+    } else {
+      return *word_at(src, (r - 3) * row_bytes, at);
+    }
+  }
+};
+
+// Every row of the band is in flight at once.  (Loading the next frame's rows
+// during this one, all of them or the first eight, measured within 3 % either
+// way.)
+template <int R, bool WARM, bool EDGE>
+__device__ inline void fused_frame(const FuseLane &q, const uint8_t *src, uint8_t *dst, uint8_t *dg,
                                    uint32_t (&gpE)[R + 2], uint32_t (&gpO)[R + 2]) {
-  uint32_t he[5] = {}, ho[5] = {}, mid[5] = {};
+  uint32_t E[5] = {}, O[5] = {};
   uint32_t t_up = 0, t_c = 0;
-  // recompute the row offsets per frame instead of holding them across the
-  // frame loop (they would take ~40 registers)
-  int y0 = q.y0;
-  uint32_t col = q.col;
-  asm volatile("" : "+v"(y0), "+v"(col));
-  // every row of the band in flight at once: byte offsets from the
-  // wavefront-uniform frame base, stepped by one row and clamped into the
-  // frame in offset space (no multiply per row)
-  const int row_bytes = 4 * q.Wq, last_row = (q.H - 1) * row_bytes;
-  const int col_bytes = (int)col * 4;
-  int off = (y0 - 3) * row_bytes;
+  const FusePlace<R, EDGE> pl(q);
+  const int y0 = pl.y0, row_bytes = pl.row_bytes;
+  const uint32_t at = pl.at;
   uint32_t rows[R + 6];
 #pragma unroll
-  for (int r = 0; r < R + 6; ++r, off += row_bytes)
-    rows[r] = *(const uint32_t *)((const char *)src + (uint32_t)(min(max(off, 0), last_row) + col_bytes));
-  int out_off = y0 * row_bytes + col_bytes;         // byte offset of output row y0
+  for (int r = 0; r < R + 6; ++r) rows[r] = pl.row(src, r);
 #pragma unroll
   for (int r = 0; r < R + 6; ++r) {
-    const uint32_t w = rows[r];
-    const uint32_t wl = lane_below(w), wr = lane_above(w);
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      he[k] = he[k + 1];
-      ho[k] = ho[k + 1];
-      mid[k] = mid[k + 1];
+      E[k] = E[k + 1];
+      O[k] = O[k + 1];
     }
-    swar::hsum5(swar::perm(w, wl, q.s2l), swar::perm(wr, w, q.s2r), &he[4], &ho[4]);
-    mid[4] = w;
+    E[4] = rows[r] & swar::kLo;
+    O[4] = swar::perm(rows[r], rows[r], 0x0C030C01u);
     if (r < 4) continue;
     const int j = r - 4;                          // Gauss / threshold row index
     const int t = y0 - 1 + j;                     // its frame row (clamped when used)
     // Gauss words kept split: even pixels in gE, odd pixels in gO
-    const bool filtered = t >= 2 && t < q.H - 2;
-    const uint32_t gE = filtered ? swar::vround5(he[0], he[1], he[2], he[3], he[4]) : mid[2] & swar::kLo;
-    const uint32_t gO = filtered ? swar::vround5(ho[0], ho[1], ho[2], ho[3], ho[4]) : (mid[2] >> 8) & swar::kLo;
+    const uint32_t vE = swar::vsum5(E[0], E[1], E[2], E[3], E[4]), vO = swar::vsum5(O[0], O[1], O[2], O[3], O[4]);
+    const uint32_t l = swar::perm(vE, lane_below(swar::pair_hi(vE, vO)), q.s2l);
+    const uint32_t rr = swar::perm(vO, lane_above(swar::pair_lo(vE, vO)), q.s2r);
+    uint32_t gE, gO;
+    swar::hround5(vE, vO, l, rr, &gE, &gO);
+    if constexpr (EDGE) {
+      const bool filtered = t >= 2 && t < q.H - 2;
+      gE = filtered ? gE : E[2];
+      gO = filtered ? gO : O[2];
+    }
     if (WARM) {
       gpE[j] = gE;
       gpO[j] = gO;
@@ -389,19 +432,44 @@ __device__ inline void fused_frame(const FuseLane &q, const uint32_t *src, uint3
     gpE[j] = gE;
     gpO[j] = gO;
     // frame row t = y0 + j - 1 is output row j - 1 of the band
-    if (dg && j >= 1 && j <= R && t < q.yend && q.store)
-      *(uint32_t *)((char *)dg + (uint32_t)(out_off + (j - 1) * row_bytes)) = swar::interleave(gE, gO);
+    if (dg && j >= 1 && j <= R && (!EDGE || t < q.yend) && q.store)
+      *word_at(dg, (j - 1) * row_bytes, at) = swar::interleave(gE, gO);
     if (j >= 2) {
-      // median of threshold row j-1 (frame row y0 + j - 2); its inputs are
-      // 0x00/0xFF masks, so the median is the bitwise majority
+      // median of threshold row j-1 (frame row y0 + j - 2)
       const uint32_t L = swar::perm(t_c, lane_below(t_c), q.s1l), Rt = swar::perm(lane_above(t_c), t_c, q.s1r);
-      const int y = y0 + j - 2;
-      if (q.store && y < q.yend)
-        __builtin_nontemporal_store(swar::med5_masks(t_c, t_up, t_dn, L, Rt),
-                                    (uint32_t *)((char *)dst + (uint32_t)(out_off + (j - 2) * row_bytes)));
+      if (q.store && (!EDGE || y0 + j - 2 < q.yend))
+        __builtin_nontemporal_store(swar::med5_ones(t_c, t_up, t_dn, L, Rt),
+                                    word_at(dst, (j - 2) * row_bytes, at));
     }
     t_up = t_c;
     t_c = t_dn;
+  }
+}
+
+// The frames [f_begin, f_end) of a wavefront.
+template <int R, bool EDGE>
+__device__ inline void fused_range(const MdpFusedArgs &a, const FuseLane &q, int64_t f_begin, int64_t f_end) {
+  const int64_t WH = (int64_t)a.W * a.H;
+  const int64_t in0 = a.in_idx[0], out0 = a.out_idx[1], d_read = a.delay_idx[0], d_write = a.delay_idx[1];
+  const auto frame = [&](int64_t f) { return a.in + read_slot(in0 + f, a.in_mask) * WH; };
+  // Gauss words of the previous frame, rows clamp(y0-1+j), split into even
+  // and odd pixels
+  uint32_t gpE[R + 2], gpO[R + 2];
+  if (f_begin == 0) {
+    const uint32_t *pg = (const uint32_t *)(a.delay + read_slot(d_read, a.delay_mask) * WH);
+#pragma unroll
+    for (int j = 0; j < R + 2; ++j) {
+      const uint32_t w = pg[(uint32_t)(min(max(q.y0 - 1 + j, 0), a.H - 1) * q.Wq) + q.col];
+      gpE[j] = w & swar::kLo;
+      gpO[j] = (w >> 8) & swar::kLo;
+    }
+  } else {
+    fused_frame<R, true, EDGE>(q, frame(f_begin - 1), nullptr, nullptr, gpE, gpO);
+  }
+  for (int64_t f = f_begin; f < f_end; ++f) {
+    // the delay channel keeps the last frame's Gauss output as its one token
+    uint8_t *dg = f == a.n_frames - 1 ? a.delay + write_slot(d_write + a.n_frames - 1, a.delay_mask) * WH : nullptr;
+    fused_frame<R, false, EDGE>(q, frame(f), a.out + write_slot(out0 + f, a.out_mask) * WH, dg, gpE, gpO);
   }
 }
 
@@ -424,38 +492,18 @@ __global__ __launch_bounds__(256) void k_mdp_fused(MdpFusedArgs a, int32_t waves
   q.y0 = (ic / q.Wq) * R;
   q.yend = min(q.y0 + R, a.H);
   q.col = (uint32_t)cx;
-  q.s2l = swar::win2_left(cx == 0);
-  q.s2r = swar::win2_right(cx == q.Wq - 1);
+  q.s2l = swar::pair_left(cx == 0);
+  q.s2r = swar::pair_right(cx == q.Wq - 1);
   q.s1l = swar::win1_left(cx == 0);
   q.s1r = swar::win1_right(cx == q.Wq - 1);
   q.thr = (uint32_t)a.thr;
-  const int64_t WH = (int64_t)a.W * a.H;
   const int64_t f_begin = (int64_t)cp.frame * frames_per_chunk;
   const int64_t f_end = min(f_begin + frames_per_chunk, a.n_frames);
-  const int64_t in0 = a.in_idx[0], out0 = a.out_idx[1], d_read = a.delay_idx[0], d_write = a.delay_idx[1];
-
-  // Gauss words of the previous frame, rows clamp(y0-1+j), split into even
-  // and odd pixels
-  uint32_t gpE[R + 2], gpO[R + 2];
-  if (f_begin == 0) {
-    const uint32_t *pg = (const uint32_t *)(a.delay + read_slot(d_read, a.delay_mask) * WH);
-#pragma unroll
-    for (int j = 0; j < R + 2; ++j) {
-      const uint32_t w = pg[(uint32_t)(min(max(q.y0 - 1 + j, 0), a.H - 1) * q.Wq) + q.col];
-      gpE[j] = w & swar::kLo;
-      gpO[j] = (w >> 8) & swar::kLo;
-    }
-  } else {
-    fused_frame<R, true>(q, (const uint32_t *)(a.in + read_slot(in0 + f_begin - 1, a.in_mask) * WH), nullptr, nullptr,
-                         gpE, gpO);
-  }
-  for (int64_t f = f_begin; f < f_end; ++f) {
-    // the delay channel keeps the last frame's Gauss output as its one token
-    uint32_t *dg = f == a.n_frames - 1 ? (uint32_t *)(a.delay + write_slot(d_write + a.n_frames - 1, a.delay_mask) * WH)
-                                       : nullptr;
-    fused_frame<R, false>(q, (const uint32_t *)(a.in + read_slot(in0 + f, a.in_mask) * WH),
-                          (uint32_t *)(a.out + write_slot(out0 + f, a.out_mask) * WH), dg, gpE, gpO);
-  }
+  // rows y0 - 3 .. y0 + R + 2 inside the frame and rows y0 - 1 .. y0 + R
+  // filtered, for every lane
+  const bool edge = q.y0 == 0 || q.y0 + R + 2 >= a.H;
+  if (__any(edge)) fused_range<R, true>(a, q, f_begin, f_end);
+  else fused_range<R, false>(a, q, f_begin, f_end);
 }
 
 // ------------------------------------------------------------------ launch

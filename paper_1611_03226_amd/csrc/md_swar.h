@@ -91,6 +91,37 @@ __host__ __device__ inline uint32_t vround5(uint32_t a, uint32_t b, uint32_t c, 
   return (s >> 8) & kLo;
 }
 
+// The same filter with the vertical pass first: per 16-bit lane the
+// unrounded 5-tap sum of five pixels (at most 255 * 16 = 4080) ...
+__host__ __device__ inline uint32_t vsum5(uint32_t a, uint32_t b, uint32_t c, uint32_t d, uint32_t e) {
+  return (a + e) + ((b + d + c) << 2) + (c << 1);
+}
+
+// ... and the horizontal pass over vertical sums v0..v3 of a word's pixels,
+// E = (v0, v2) and O = (v1, v3), with l = (v-2, v-1) and r = (v4, v5) of the
+// neighbours: rounded (s + 128) >> 8, the bytes of pixels 0, 2 in *even and
+// of 1, 3 in *odd.  Lanes stay below 65536 as in vround5.
+__host__ __device__ inline void hround5(uint32_t E, uint32_t O, uint32_t l, uint32_t r, uint32_t *even, uint32_t *odd) {
+  const uint32_t A = perm(E, l, 0x05040100u);   // (v-2, v0)
+  const uint32_t B = perm(O, l, 0x05040302u);   // (v-1, v1)
+  const uint32_t F = perm(r, E, 0x05040302u);   // (v2, v4)
+  const uint32_t G = perm(r, O, 0x07060302u);   // (v3, v5)
+  const uint32_t se = (A + F + 0x00800080u) + ((B + O + E) << 2) + (E << 1);
+  const uint32_t so = (B + G + 0x00800080u) + ((E + F + O) << 2) + (O << 1);
+  *even = perm(se, se, 0x0C030C01u);
+  *odd = perm(so, so, 0x0C030C01u);
+}
+
+// A word's own pairs as its neighbours take them: (v2, v3) for the word on
+// the right, (v0, v1) for the one on the left; and the selectors that keep
+// such a pair p, or at a frame edge repeat the edge pixel's sum instead:
+//   perm(E, p, pair_left(edge))  = l above, (v0, v0) at the left edge
+//   perm(O, p, pair_right(edge)) = r above, (v3, v3) at the right edge
+__host__ __device__ inline uint32_t pair_hi(uint32_t E, uint32_t O) { return perm(O, E, 0x07060302u); }
+__host__ __device__ inline uint32_t pair_lo(uint32_t E, uint32_t O) { return perm(O, E, 0x05040100u); }
+__host__ __device__ inline uint32_t pair_left(bool edge) { return edge ? 0x05040504u : 0x03020100u; }
+__host__ __device__ inline uint32_t pair_right(bool edge) { return edge ? 0x07060706u : 0x03020100u; }
+
 // Re-interleave even-pixel and odd-pixel lanes into one word of 4 pixels.
 __host__ __device__ inline uint32_t interleave(uint32_t even, uint32_t odd) { return even | (odd << 8); }
 
@@ -129,25 +160,24 @@ __host__ __device__ inline u16x2 med5(u16x2 a, u16x2 b, u16x2 c, u16x2 d, u16x2 
 }
 
 // Threshold of pixels given in split form (even pixels 0, 2 in the 16-bit
-// lanes of *E, odd pixels 1, 3 in *O, values 0..255): 0xFF in every byte
+// lanes of *E, odd pixels 1, 3 in *O, values 0..255): 0x01 in every byte
 // where |cur - prev| > t (t in 0..255), else 0.  |d| + (255 - t) stays below
 // 512, so bit 8 of each lane is the comparison.
 __host__ __device__ inline uint32_t thres_split(uint32_t cE, uint32_t cO, uint32_t pE, uint32_t pO, uint32_t t) {
   const uint32_t bias = (255u - t) * 0x00010001u;
   const u16x2 ce = as_u16x2(cE), co = as_u16x2(cO), pe = as_u16x2(pE), po = as_u16x2(pO);
-  const uint32_t dE = from_u16x2(vmax(ce, pe) - vmin(ce, pe));
-  const uint32_t dO = from_u16x2(vmax(co, po) - vmin(co, po));
-  const uint32_t bE = ((dE + bias) >> 8) & 0x00010001u, bO = ((dO + bias) >> 8) & 0x00010001u;
-  const uint32_t ones = bE | (bO << 8);     // 0x00 / 0x01 per byte
-  return (ones << 8) - ones;                // x 255, modulo 2^32
+  const uint32_t dE = from_u16x2(vmax(ce, pe) - vmin(ce, pe)) + bias;
+  const uint32_t dO = from_u16x2(vmax(co, po) - vmin(co, po)) + bias;
+  return ((dE >> 8) & 0x00010001u) | (dO & 0x01000100u);
 }
 
-// Median of five 0x00/0xFF byte masks, per byte: with only two values the
-// median is the majority, and the min/max network becomes AND/OR.
-__host__ __device__ inline uint32_t med5_masks(uint32_t a, uint32_t b, uint32_t c, uint32_t d, uint32_t e) {
-  const uint32_t f = (a & b) | (c & d);
-  const uint32_t g = (a | b) & (c | d);
-  return (e & f) | ((e | f) & g);
+// Median of five words of 0x00/0x01 bytes, as 0x00/0xFF: with only two values
+// the median is the majority, and a byte's sum of five (at most 5) plus 5
+// reaches 8 exactly from three on.
+__host__ __device__ inline uint32_t med5_ones(uint32_t a, uint32_t b, uint32_t c, uint32_t d, uint32_t e) {
+  const uint32_t s = (a + b + c) + d + e;
+  const uint32_t y = ((s + 0x05050505u) >> 3) & 0x01010101u;
+  return (y << 8) - y;                      // x 255, modulo 2^32
 }
 
 // Median of five words of four pixels each, per pixel.

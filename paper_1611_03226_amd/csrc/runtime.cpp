@@ -592,6 +592,7 @@ static hipError_t move_tokens(df_graph *g, Fifo &f, int64_t pos, void *flat, int
   a.idx = idx;
   a.n = n;
   a.err = g->err_dev;
+  a.push = to_ring;
   int64_t done = 0;
   for (int i = 0; i < 2 && done < n; ++i) {
     const host::Run run = host::next_run(m, pos + done, n - done, to_ring);
