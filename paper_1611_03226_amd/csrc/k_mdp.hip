@@ -344,7 +344,8 @@ __device__ __forceinline__ uint32_t lane_above(uint32_t v) {   // value of lane 
 // Bound by VALU issue: 1433 wavefront instructions per frame with the
 // horizontal sums first (22 rows of them for 16 outputs) and every band
 // guarded, 1116 now; 64 frames of 1920x1080 in 100 and 88 us, 128 of 1000x600
-// in 54 and 49, 4096 of 320x240 in 227 and 215 to 226.
+// in 54 and 49, 4096 of 320x240 in 227 and (with ordinary stores, see
+// launch_mdp_fused) 196.
 struct FuseLane {
   int y0, yend, H, Wq;
   uint32_t col, s2l, s2r, s1l, s1r, thr;
@@ -389,7 +390,13 @@ struct FusePlace {
 // Every row of the band is in flight at once.  (Loading the next frame's rows
 // during this one, all of them or the first eight, measured within 3 % either
 // way.)
-template <int R, bool WARM, bool EDGE>
+template <bool NT>
+__device__ __forceinline__ void store_word(gu32 *p, uint32_t v) {
+  if constexpr (NT) __builtin_nontemporal_store(v, p);
+  else *p = v;
+}
+
+template <int R, bool NT, bool WARM, bool EDGE>
 __device__ inline void fused_frame(const FuseLane &q, const uint8_t *src, uint8_t *dst, uint8_t *dg,
                                    uint32_t (&gpE)[R + 2], uint32_t (&gpO)[R + 2]) {
   uint32_t E[5] = {}, O[5] = {};
@@ -438,8 +445,7 @@ __device__ inline void fused_frame(const FuseLane &q, const uint8_t *src, uint8_
       // median of threshold row j-1 (frame row y0 + j - 2)
       const uint32_t L = swar::perm(t_c, lane_below(t_c), q.s1l), Rt = swar::perm(lane_above(t_c), t_c, q.s1r);
       if (q.store && (!EDGE || y0 + j - 2 < q.yend))
-        __builtin_nontemporal_store(swar::med5_ones(t_c, t_up, t_dn, L, Rt),
-                                    word_at(dst, (j - 2) * row_bytes, at));
+        store_word<NT>(word_at(dst, (j - 2) * row_bytes, at), swar::med5_ones(t_c, t_up, t_dn, L, Rt));
     }
     t_up = t_c;
     t_c = t_dn;
@@ -447,7 +453,7 @@ __device__ inline void fused_frame(const FuseLane &q, const uint8_t *src, uint8_
 }
 
 // The frames [f_begin, f_end) of a wavefront.
-template <int R, bool EDGE>
+template <int R, bool NT, bool EDGE>
 __device__ inline void fused_range(const MdpFusedArgs &a, const FuseLane &q, int64_t f_begin, int64_t f_end) {
   const int64_t WH = (int64_t)a.W * a.H;
   const int64_t in0 = a.in_idx[0], out0 = a.out_idx[1], d_read = a.delay_idx[0], d_write = a.delay_idx[1];
@@ -464,16 +470,16 @@ __device__ inline void fused_range(const MdpFusedArgs &a, const FuseLane &q, int
       gpO[j] = (w >> 8) & swar::kLo;
     }
   } else {
-    fused_frame<R, true, EDGE>(q, frame(f_begin - 1), nullptr, nullptr, gpE, gpO);
+    fused_frame<R, NT, true, EDGE>(q, frame(f_begin - 1), nullptr, nullptr, gpE, gpO);
   }
   for (int64_t f = f_begin; f < f_end; ++f) {
     // the delay channel keeps the last frame's Gauss output as its one token
     uint8_t *dg = f == a.n_frames - 1 ? a.delay + write_slot(d_write + a.n_frames - 1, a.delay_mask) * WH : nullptr;
-    fused_frame<R, false, EDGE>(q, frame(f), a.out + write_slot(out0 + f, a.out_mask) * WH, dg, gpE, gpO);
+    fused_frame<R, NT, false, EDGE>(q, frame(f), a.out + write_slot(out0 + f, a.out_mask) * WH, dg, gpE, gpO);
   }
 }
 
-template <int R>
+template <int R, bool NT>
 __global__ __launch_bounds__(256) void k_mdp_fused(MdpFusedArgs a, int32_t waves_per_chunk, int32_t bpc,
                                                    int32_t frames_per_chunk) {
   const FramePart cp = frame_part(blockIdx.x, (uint32_t)bpc);   // (frame chunk, block of the chunk)
@@ -502,8 +508,8 @@ __global__ __launch_bounds__(256) void k_mdp_fused(MdpFusedArgs a, int32_t waves
   // rows y0 - 3 .. y0 + R + 2 inside the frame and rows y0 - 1 .. y0 + R
   // filtered, for every lane
   const bool edge = q.y0 == 0 || q.y0 + R + 2 >= a.H;
-  if (__any(edge)) fused_range<R, true>(a, q, f_begin, f_end);
-  else fused_range<R, false>(a, q, f_begin, f_end);
+  if (__any(edge)) fused_range<R, NT, true>(a, q, f_begin, f_end);
+  else fused_range<R, NT, false>(a, q, f_begin, f_end);
 }
 
 // ------------------------------------------------------------------ launch
@@ -617,27 +623,39 @@ hipError_t launch_advance_n(int64_t *const *ptr, int n, int64_t delta, int32_t *
 
 bool mdp_fused_supported(int32_t W, int32_t H) { return W % 4 == 0 && W >= 4 && H >= 1; }
 
-hipError_t launch_mdp_fused(const MdpFusedArgs &a, hipStream_t s, const KTiming *t) {
-  if (!mdp_fused_supported(a.W, a.H)) return hipErrorInvalidValue;
-  if (a.n_frames <= 0) return hipSuccess;
+template <bool NT>
+static hipError_t launch_fused(const MdpFusedArgs &a, hipStream_t s, const KTiming *t) {
   const int64_t n_bands = (a.H + kFuseRun - 1) / kFuseRun;
   const int64_t words = n_bands * (a.W / 4);
   const int32_t waves = (int32_t)((words + kFuseOut - 1) / kFuseOut);
   const int32_t bpc = (waves + 3) / 4;
   // frame ranges as short as possible while the whole grid stays resident
   // (one round of workgroups: no tail of a partly filled second round)
-  const int64_t resident = resident_blocks((const void *)k_mdp_fused<kFuseRun>, 256, 0);
+  const int64_t resident = resident_blocks((const void *)k_mdp_fused<kFuseRun, NT>, 256, 0);
   const int64_t max_chunks = resident / bpc > 0 ? resident / bpc : 1;
   const int64_t fpc = (a.n_frames + max_chunks - 1) / max_chunks;
   const int64_t chunks = (a.n_frames + fpc - 1) / fpc;
   if (chunks * bpc > kMaxBlocks) return hipErrorInvalidValue;   // > 2^23 workgroups: not supported
   const dim3 grid((unsigned)(chunks * bpc));
   if (t)
-    hipExtLaunchKernelGGL(k_mdp_fused<kFuseRun>, grid, dim3(256), 0, s, t->start, t->stop, 0, a, waves, bpc,
+    hipExtLaunchKernelGGL((k_mdp_fused<kFuseRun, NT>), grid, dim3(256), 0, s, t->start, t->stop, 0, a, waves, bpc,
                           (int32_t)fpc);
   else
-    hipLaunchKernelGGL(k_mdp_fused<kFuseRun>, grid, dim3(256), 0, s, a, waves, bpc, (int32_t)fpc);
+    hipLaunchKernelGGL((k_mdp_fused<kFuseRun, NT>), grid, dim3(256), 0, s, a, waves, bpc, (int32_t)fpc);
   return hipGetLastError();
+}
+
+hipError_t launch_mdp_fused(const MdpFusedArgs &a, hipStream_t s, const KTiming *t) {
+  if (!mdp_fused_supported(a.W, a.H)) return hipErrorInvalidValue;
+  if (a.n_frames <= 0) return hipSuccess;
+  // A wavefront stores 248-byte row pieces, whose ends share 64-byte words of
+  // memory with their neighbours'.  Up to the last-level cache's 256 MB the
+  // streamed pieces merge there and leave room for the input; beyond it they
+  // reach memory in parts, and stores that merge in the L2 win.  us, streamed
+  // / ordinary: 3072 frames of 320x240 (236 MB) 142 / 148, 4096 225 / 196,
+  // 8192 473 / 391; 1080p 128 frames (265 MB) 164 / 167, 152 205 / 189.
+  const bool stream = a.n_frames * (int64_t)a.W * a.H <= (256ll << 20);
+  return stream ? launch_fused<true>(a, s, t) : launch_fused<false>(a, s, t);
 }
 
 }  // namespace dfh
