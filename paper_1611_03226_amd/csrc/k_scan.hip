@@ -69,6 +69,43 @@ __global__ __launch_bounds__(256) void k_scan_tables(ScanArgs a, int64_t n_group
   }
 }
 
+// Short segments in one launch: a workgroup per segment, a wavefront per
+// branch that walks the segment's firings 64 at a time with its running count
+// and last feeder, so nothing passes between wavefronts and no ticket has to
+// be cleared.  Bound by latency: 6 segments of 40 firings take 3 us, against
+// 2 + 5 + 3 us and two kernel boundaries for the three launches above; the
+// walk is serial, so long segments keep those (kRowFirings).
+constexpr int64_t kRowFirings = 512;
+
+__global__ __launch_bounds__(1024) void k_scan_rows(ScanArgs a) {
+  const int64_t seg = blockIdx.x, g0 = seg * a.seg_firings;
+  const int b = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int64_t R = a.ctrl_idx ? a.ctrl_idx[0] : a.ctrl_pos;
+  const uint64_t below_mask = lane ? (~0ull >> (64 - lane)) : 0ull;
+  int64_t cnt = 0, last = -1;
+  for (int64_t c = 0; c < a.seg_firings; c += 64) {
+    const int64_t j = c + lane;
+    const bool in = j < a.seg_firings;
+    const int32_t tok = in ? a.ctrl[(R + g0 + j) & a.ctrl_mask] : 0;
+    bool bad;
+    const uint32_t set = token_set(tok, a.ctrl_mode, a.B_max, &bad);
+    if (b == 0) {
+      if (__ballot(in && bad) && lane == 0 && a.err) atomicOr(a.err, (int32_t)kErrControl);
+      if (in) a.B_out[g0 + j] = (int32_t)set;
+    }
+    const uint64_t bal = __ballot(in && (a.hist_mode == 1 || in_set(set, b)));
+    const uint64_t below = bal & below_mask;
+    if (in) {
+      const int64_t o = (int64_t)b * a.stride + g0 + j;
+      a.prev_out[o] = below ? g0 + c + 63 - __clzll((long long)below) : last;
+      if (a.off_out) a.off_out[o] = a.r * (cnt + __popcll(below));
+    }
+    cnt += __popcll(bal);
+    if (bal) last = g0 + c + 63 - __clzll((long long)bal);
+  }
+  if (a.last_out && lane == 0) a.last_out[seg * a.B_max + b] = last;
+}
+
 int64_t scan_groups(int64_t n_segs, int64_t seg_firings) { return n_segs * ((seg_firings + 63) / 64); }
 
 static size_t al256(size_t b) { return (b + 255) & ~(size_t)255; }
@@ -121,6 +158,10 @@ hipError_t launch_scan(const ScanArgs &a, hipStream_t s, bool tables, bool zero_
   if (a.n_segs <= 0 || a.seg_firings <= 0) return hipSuccess;
   if (a.B_max < 1 || a.B_max > kMaxBranches || !a.grp || !a.ticket) return hipErrorInvalidValue;
   if (a.seg_firings > INT32_MAX || (a.lgrp && a.n_segs != 1)) return hipErrorInvalidValue;
+  if (tables && !a.lgrp && a.seg_firings <= kRowFirings) {
+    hipLaunchKernelGGL(k_scan_rows, dim3((unsigned)a.n_segs), dim3(64 * a.B_max), 0, s, a);
+    return hipGetLastError();
+  }
   if (zero_tickets) {
     hipError_t e = launch_fill_i32(a.ticket, 0, a.n_segs, s);
     if (e != hipSuccess) return e;
