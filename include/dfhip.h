@@ -256,6 +256,10 @@ df_status df_fifo_status(df_graph *g, int32_t fifo, int64_t *read_idx,
 df_status df_fifo_info(df_graph *g, int32_t fifo, int32_t *dtype,
                        int64_t *elems_per_token, int64_t *token_bytes);
 
+/* The same as one value, for a binding's checks on every push and pop:
+ * elems_per_token * 256 + dtype, or -1 (null graph or bad id).  Host only. */
+int64_t df_fifo_token(const df_graph *g, int32_t fifo);
+
 /* ------------------------------------------------------------------ actors */
 
 /* Create an actor of `kind` with a parameter struct (df_dpd_params or
@@ -440,6 +444,30 @@ int64_t df_dpd_forward_noalloc_max_bytes(void);
 df_status df_dpd_forward(void *stream, const void *x, const int32_t *ctrl,
                          const void *h, void *y, int64_t n_streams, int64_t len,
                          int64_t r, int32_t B_max, int32_t M, int32_t hist);
+
+/* df_dpd_forward with the caller's scratch, for programs with an allocator of
+ * their own (the autograd binding): identical results, no allocation.
+ * `tables` (df_dpd_tables_bytes() bytes, only with ctrl, else NULL) receives
+ * the firings' branch sets and history sources; kept unchanged with the same
+ * x, it serves df_dpd_coeff_adjoint_tables, which is df_dpd_coeff_adjoint of
+ * the same call (same results) without reading the control tokens again.
+ * `work` (df_dpd_forward_work_bytes() bytes) is free once the stream has
+ * passed the call.  Both are device buffers aligned to 8 bytes; calls that
+ * share none of them are independent.
+ * Errors: DF_EINVAL (sizes, buffers), DF_EDEVICE. */
+int64_t df_dpd_tables_bytes(int64_t n_streams, int64_t len, int64_t r, int32_t B_max);
+int64_t df_dpd_forward_work_bytes(int64_t n_streams, int64_t len, int64_t r,
+                                  int32_t B_max, int32_t M, int32_t with_ctrl);
+df_status df_dpd_forward_work(void *stream, const void *x, const int32_t *ctrl,
+                              const void *h, void *y, int64_t n_streams, int64_t len,
+                              int64_t r, int32_t B_max, int32_t M, int32_t hist,
+                              void *tables, int64_t tables_bytes,
+                              void *work, int64_t work_bytes);
+df_status df_dpd_coeff_adjoint_tables(void *stream, const void *x, const void *tables,
+                                      int64_t tables_bytes, const void *G, void *grad_h,
+                                      int64_t n_streams, int64_t len, int64_t r,
+                                      int32_t B_max, int32_t M, void *work,
+                                      int64_t work_bytes);
 
 /* The same y computed by the network of Sec. 4.2 as drawn: a Poly kernel
  * writing psi_b(x) of every firing to branch channel b (only for the

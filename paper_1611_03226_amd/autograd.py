@@ -23,6 +23,20 @@ def _stream():
     return torch.cuda.current_stream()
 
 
+def _forward(x, ctrl, h, y, r, hist):
+    """y = DPD_h(x) with torch's allocations as scratch (cached, and ordered on
+    torch's stream); returns the firings' tables, None without ctrl."""
+    D.check_dpd_tensors(x, ctrl, h, y, r)
+    (S, L), (B, M) = x.shape, h.shape
+    tables = None
+    if ctrl is not None:
+        tables = torch.empty(max(D.df_dpd_tables_bytes(S, L, r, B), 8), dtype=torch.uint8, device=x.device)
+    work = torch.empty(max(D.df_dpd_forward_work_bytes(S, L, r, B, M, ctrl is not None), 8), dtype=torch.uint8,
+                       device=x.device)
+    D.df_dpd_forward_work(x, ctrl, h, y, r, tables, work, hist, stream=_stream())
+    return tables
+
+
 class DPDFunction(torch.autograd.Function):
     """y = DPD_h(x) for x [S, L], h [B, M]; ctrl [S, L/r] int32 or None (all
     branches active).  Backward: coefficient adjoint only (x is data)."""
@@ -32,16 +46,18 @@ class DPDFunction(torch.autograd.Function):
         x = x.contiguous()
         hc = h.detach().contiguous()
         y = torch.empty_like(x)
-        D.df_dpd_forward(x, ctrl, hc, y, r, hist, stream=_stream())
-        ctx.save_for_backward(x, ctrl if ctrl is not None else torch.empty(0))
-        ctx.has_ctrl = ctrl is not None
-        ctx.r, ctx.hist, ctx.hshape = r, hist, h.shape
+        tables = _forward(x, ctrl, hc, y, r, hist)
+        none = torch.empty(0)
+        # the tables are the control tokens as the backward needs them; the
+        # tokens are saved too, so that a change in between is an error
+        ctx.save_for_backward(x, none if ctrl is None else ctrl, none if tables is None else tables)
+        ctx.has_ctrl = tables is not None
+        ctx.r, ctx.hshape = r, h.shape
         return y
 
     @staticmethod
     def backward(ctx, gy):
-        x, ctrl = ctx.saved_tensors
-        ctrl = ctrl if ctx.has_ctrl else None
+        x, _, tables = ctx.saved_tensors
         B, M = ctx.hshape
         S, L = x.shape
         grad_h = None
@@ -49,7 +65,10 @@ class DPDFunction(torch.autograd.Function):
             grad_h = torch.empty((B, M), dtype=torch.complex64, device=x.device)
             nb = D.df_dpd_coeff_adjoint_work_bytes(S, L, ctx.r, B, M)
             work = torch.empty(max(nb, 8), dtype=torch.uint8, device=x.device)
-            D.df_dpd_coeff_adjoint(x, ctrl, gy.contiguous(), grad_h, ctx.r, work, ctx.hist, stream=_stream())
+            if ctx.has_ctrl:
+                D.df_dpd_coeff_adjoint_tables(x, tables, gy.contiguous(), grad_h, ctx.r, work, stream=_stream())
+            else:
+                D.df_dpd_coeff_adjoint(x, None, gy.contiguous(), grad_h, ctx.r, work, stream=_stream())
         return None, grad_h, None, None, None
 
 
@@ -64,7 +83,7 @@ class PAFunction(torch.autograd.Function):
         a = a.detach().contiguous()
         v = torch.empty_like(u)
         S, L = u.shape
-        D.df_dpd_forward(u, None, a, v, L, D.DF_HIST_BRANCH, stream=_stream())
+        _forward(u, None, a, v, L, D.DF_HIST_BRANCH)
         ctx.save_for_backward(u, a)
         return v
 

@@ -335,6 +335,12 @@ extern "C" df_status df_fifo_info(df_graph *g, int32_t fifo, int32_t *dtype, int
   return DF_OK;
 }
 
+extern "C" int64_t df_fifo_token(const df_graph *g, int32_t fifo) {
+  if (!g || fifo < 0 || fifo >= (int)g->fifos.size()) return -1;
+  const Fifo &f = g->fifos[fifo];
+  return f.elems_per_token * 256 + (int64_t)f.dt;
+}
+
 // ------------------------------------------------------------------ actors
 
 extern "C" df_status df_actor_create(df_graph *g, df_actor_kind kind, const void *params, size_t params_size,

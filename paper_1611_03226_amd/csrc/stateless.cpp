@@ -187,6 +187,49 @@ extern "C" df_status df_dpd_forward(void *stream, const void *x, const int32_t *
   return DF_OK;
 }
 
+// Regions of a caller's buffers, 256-byte aligned: the tables (branch sets,
+// then history sources) and the rest of the forward's scratch.
+static size_t al256(size_t v) { return (v + 255) & ~(size_t)255; }
+
+extern "C" int64_t df_dpd_tables_bytes(int64_t S, int64_t len, int64_t r, int32_t B_max) {
+  if (S <= 0 || len <= 0 || r <= 0 || B_max <= 0) return 0;
+  const FwdScratchSize z = dpd_forward_scratch_size(S, len, r, B_max, 1, true);
+  return (int64_t)(al256(z.B) + al256(z.prev));
+}
+
+extern "C" int64_t df_dpd_forward_work_bytes(int64_t S, int64_t len, int64_t r, int32_t B_max, int32_t M,
+                                             int32_t with_ctrl) {
+  if (S <= 0 || len <= 0 || r <= 0 || B_max <= 0 || M <= 0) return 0;
+  const FwdScratchSize z = dpd_forward_scratch_size(S, len, r, B_max, M, with_ctrl != 0);
+  return (int64_t)(al256(z.ht) + (with_ctrl ? al256(z.corr) + al256(z.grp) : 0));
+}
+
+extern "C" df_status df_dpd_forward_work(void *stream, const void *x, const int32_t *ctrl, const void *h, void *y,
+                                         int64_t S, int64_t len, int64_t r, int32_t B_max, int32_t M, int32_t hist,
+                                         void *tables, int64_t tables_bytes, void *work, int64_t work_bytes) {
+  bool nothing = false;
+  df_status st = check_dpd_forward_args(x, h, y, S, len, r, B_max, M, hist, &nothing);
+  if (st || nothing) return st;
+  if (!work || work_bytes < df_dpd_forward_work_bytes(S, len, r, B_max, M, ctrl != nullptr))
+    return fail(nullptr, DF_EINVAL, "work buffer too small");
+  if (ctrl && (!tables || tables_bytes < df_dpd_tables_bytes(S, len, r, B_max)))
+    return fail(nullptr, DF_EINVAL, "table buffer too small");
+  if ((((uintptr_t)tables | (uintptr_t)work) & 7) != 0) return fail(nullptr, DF_EINVAL, "buffers must be 8-byte aligned");
+  const FwdScratchSize z = dpd_forward_scratch_size(S, len, r, B_max, M, ctrl != nullptr);
+  FwdScratch sc{};
+  char *p = (char *)work;
+  sc.ht = (float2 *)p;
+  if (ctrl) {
+    sc.B = (int32_t *)tables;
+    sc.prev = (int64_t *)((char *)tables + al256(z.B));
+    sc.corr = (float2 *)(p + al256(z.ht));
+    sc.grp = p + al256(z.ht) + al256(z.corr);
+  }
+  hipError_t e = dpd_forward_enqueue(sc, (hipStream_t)stream, x, ctrl, h, y, S, len, r, B_max, M, hist);
+  if (e != hipSuccess) return fail_hip(nullptr, e, "df_dpd_forward_work");
+  return DF_OK;
+}
+
 extern "C" df_status df_dpd_forward_network(void *stream, const void *x, const int32_t *ctrl, const void *h, void *y,
                                             int64_t S, int64_t len, int64_t r, int32_t B_max, int32_t M,
                                             int32_t ctrl_mode) {
@@ -248,9 +291,11 @@ extern "C" int64_t df_dpd_coeff_adjoint_work_bytes(int64_t S, int64_t len, int64
   return std::max(blocks_ctrl, blocks_all) * B_max * M * (int64_t)sizeof(float2);
 }
 
-extern "C" df_status df_dpd_coeff_adjoint(void *stream, const void *x, const int32_t *ctrl, const void *G,
-                                         void *grad_h, int64_t S, int64_t len, int64_t r, int32_t B_max, int32_t M,
-                                         int32_t hist, void *work, int64_t work_bytes) {
+// The coefficient adjoint; with control tokens either from tables that a
+// forward call left, or (tables == nullptr) from tables made here.
+static df_status coeff_adjoint(const char *what, hipStream_t s, const void *x, const int32_t *ctrl, const void *tables,
+                               const void *G, void *grad_h, int64_t S, int64_t len, int64_t r, int32_t B_max, int32_t M,
+                               int32_t hist, void *work, int64_t work_bytes) {
   df_status st = check_dpd_shape(S, len, r, B_max, M, hist);
   if (st) return st;
   if (!grad_h) return fail(nullptr, DF_EINVAL, "null grad_h");
@@ -258,7 +303,6 @@ extern "C" df_status df_dpd_coeff_adjoint(void *stream, const void *x, const int
   const int64_t need = df_dpd_coeff_adjoint_work_bytes(S, len, r, B_max, M);
   if (need > 0 && (!work || work_bytes < need))
     return fail(nullptr, DF_EINVAL, "work buffer of %lld bytes needed", (long long)need);
-  hipStream_t s = (hipStream_t)stream;
   AdjArgs a{};
   a.x = (const float2 *)x;
   a.G = (const float2 *)G;
@@ -266,13 +310,12 @@ extern "C" df_status df_dpd_coeff_adjoint(void *stream, const void *x, const int
   a.M = M;
   a.partial = (float2 *)work;
   a.grad = (float2 *)grad_h;
-  Tables t;
   hipError_t e = hipSuccess;
   if (S == 0 || len == 0) {
     a.n_firings = 0;
     a.blocks_per_firing = 1;
     e = launch_adj(a, s);
-  } else if (!ctrl) {
+  } else if (!ctrl && !tables) {
     a.seg_firings = 1;
     a.n_firings = S;
     a.r = len;
@@ -281,11 +324,18 @@ extern "C" df_status df_dpd_coeff_adjoint(void *stream, const void *x, const int
     e = launch_adj(a, s);
   } else {
     const int64_t nf = len / r;
-    e = make_tables(ctrl, S, nf, r, B_max, hist, s, &t);
-    if (e == hipSuccess) {
+    Tables t;
+    if (tables) {
+      a.B = (const int32_t *)tables;
+      a.prev = (const int64_t *)((const char *)tables + al256(sizeof(int32_t) * (size_t)(S * nf)));
+      a.prev_stride = S * nf;
+    } else {
+      e = make_tables(ctrl, S, nf, r, B_max, hist, s, &t);
       a.B = t.B;
       a.prev = t.prev;
       a.prev_stride = t.n;
+    }
+    if (e == hipSuccess) {
       a.seg_firings = nf;
       a.n_firings = S * nf;
       a.r = r;
@@ -293,10 +343,27 @@ extern "C" df_status df_dpd_coeff_adjoint(void *stream, const void *x, const int
       a.blocks_per_firing = (int32_t)((r + a.span - 1) / a.span);
       e = launch_adj(a, s);
     }
-    free_tables(&t, s);
+    if (!tables) free_tables(&t, s);
   }
-  if (e != hipSuccess) return fail_hip(nullptr, e, "df_dpd_coeff_adjoint");
+  if (e != hipSuccess) return fail_hip(nullptr, e, what);
   return DF_OK;
+}
+
+extern "C" df_status df_dpd_coeff_adjoint(void *stream, const void *x, const int32_t *ctrl, const void *G,
+                                         void *grad_h, int64_t S, int64_t len, int64_t r, int32_t B_max, int32_t M,
+                                         int32_t hist, void *work, int64_t work_bytes) {
+  return coeff_adjoint("df_dpd_coeff_adjoint", (hipStream_t)stream, x, ctrl, nullptr, G, grad_h, S, len, r, B_max, M,
+                       hist, work, work_bytes);
+}
+
+extern "C" df_status df_dpd_coeff_adjoint_tables(void *stream, const void *x, const void *tables, int64_t tables_bytes,
+                                                 const void *G, void *grad_h, int64_t S, int64_t len, int64_t r,
+                                                 int32_t B_max, int32_t M, void *work, int64_t work_bytes) {
+  if (S > 0 && len > 0 && r > 0 &&
+      (!tables || ((uintptr_t)tables & 7) || tables_bytes < df_dpd_tables_bytes(S, len, r, B_max)))
+    return fail(nullptr, DF_EINVAL, "table buffer too small or misaligned");
+  return coeff_adjoint("df_dpd_coeff_adjoint_tables", (hipStream_t)stream, x, nullptr, tables, G, grad_h, S, len, r,
+                       B_max, M, DF_HIST_BRANCH, work, work_bytes);
 }
 
 extern "C" df_status df_mp_input_adjoint(void *stream, const void *u, const void *a, const void *g, void *Gu,

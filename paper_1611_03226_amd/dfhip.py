@@ -90,6 +90,11 @@ _SIGS = {
     "df_dpd_coeff_adjoint": ([_P, _P, _P, _P, _P, _I64, _I64, _I64, _I32, _I32, _I32, _P, _I64], _I32),
     "df_dpd_coeff_adjoint_work_bytes": ([_I64, _I64, _I64, _I32, _I32], _I64),
     "df_mp_input_adjoint": ([_P, _P, _P, _P, _P, _I64, _I64, _I32, _I32], _I32),
+    "df_dpd_tables_bytes": ([_I64, _I64, _I64, _I32], _I64),
+    "df_dpd_forward_work_bytes": ([_I64, _I64, _I64, _I32, _I32, _I32], _I64),
+    "df_dpd_forward_work": ([_P, _P, _P, _P, _P, _I64, _I64, _I64, _I32, _I32, _I32, _P, _I64, _P, _I64], _I32),
+    "df_dpd_coeff_adjoint_tables": ([_P, _P, _P, _I64, _P, _P, _I64, _I64, _I64, _I32, _I32, _P, _I64], _I32),
+    "df_fifo_token": ([_P, _I32], _I64),
     "df_mp_loss_work_bytes": ([], _I64),
     "df_mp_loss": ([_P, _P, _P, _P, _P, _P, _I64, _I64, _I32, _I32, _P, _I64], _I32),
     "df_mp_loss_adjoint": ([_P, _P, _P, _P, _P, _P, _I64, _I64, _I32, _I32], _I32),
@@ -317,6 +322,14 @@ def df_fifo_info(g, fifo: int):
     return dt.value, e.value, b.value
 
 
+def _token_type(g, fifo: int):
+    """(dtype, elems_per_token) of a channel."""
+    v = _lib.df_fifo_token(g, fifo)
+    if v < 0:
+        return df_fifo_info(g, fifo)[:2]         # raises
+    return v & 255, v >> 8
+
+
 def df_port_rate(g, actor: int, port: int) -> int:
     out = C.c_int64()
     _check(_lib.df_port_rate(g, actor, port, C.byref(out)), g)
@@ -326,7 +339,7 @@ def df_port_rate(g, actor: int, port: int) -> int:
 def df_push(g, fifo: int, data, n_tokens: int | None = None) -> None:
     """Push host (numpy) or device (torch) data; n_tokens defaults to the
     whole tokens data holds.  dtype and size are checked against the channel."""
-    dt, ept, _ = df_fifo_info(g, fifo)
+    dt, ept = _token_type(g, fifo)
     if _is_tensor(data):
         n = device_tokens(data, dt, ept, n_tokens)
         _check(_lib.df_push(g, fifo, _dev_ptr(data), n, 1), g)
@@ -338,7 +351,7 @@ def df_push(g, fifo: int, data, n_tokens: int | None = None) -> None:
 def df_pop(g, fifo: int, dst, max_tokens: int | None = None) -> int:
     """Pop into host (numpy) or device (torch) dst; returns tokens moved.
     max_tokens defaults to the whole tokens dst has room for."""
-    dt, ept, _ = df_fifo_info(g, fifo)
+    dt, ept = _token_type(g, fifo)
     out = C.c_int64()
     if _is_tensor(dst):
         n = device_tokens(dst, dt, ept, max_tokens)
@@ -456,6 +469,39 @@ def df_dpd_forward(x, ctrl, h, y, r: int, hist: int = DF_HIST_BRANCH, stream=Non
     B, M = h.shape
     _check(_lib.df_dpd_forward(_stream_ptr(stream), _dev_ptr(x), None if ctrl is None else _dev_ptr(ctrl),
                                _dev_ptr(h), _dev_ptr(y), S, L, r, B, M, hist))
+
+
+def df_dpd_tables_bytes(S: int, L: int, r: int, B: int) -> int:
+    return int(_lib.df_dpd_tables_bytes(S, L, r, B))
+
+
+def df_dpd_forward_work_bytes(S: int, L: int, r: int, B: int, M: int, with_ctrl: bool) -> int:
+    return int(_lib.df_dpd_forward_work_bytes(S, L, r, B, M, 1 if with_ctrl else 0))
+
+
+def _bytes(t) -> int:
+    return 0 if t is None else t.numel() * t.element_size()
+
+
+def df_dpd_forward_work(x, ctrl, h, y, r: int, tables, work, hist: int = DF_HIST_BRANCH, stream=None) -> None:
+    """df_dpd_forward in the caller's scratch; tables (None without ctrl) also
+    serves df_dpd_coeff_adjoint_tables."""
+    check_dpd_tensors(x, ctrl, h, y, r)
+    S, L = x.shape
+    B, M = h.shape
+    _check(_lib.df_dpd_forward_work(_stream_ptr(stream), _dev_ptr(x), None if ctrl is None else _dev_ptr(ctrl),
+                                    _dev_ptr(h), _dev_ptr(y), S, L, r, B, M, hist,
+                                    None if tables is None else _dev_ptr(tables), _bytes(tables), _dev_ptr(work),
+                                    _bytes(work)))
+
+
+def df_dpd_coeff_adjoint_tables(x, tables, G, grad_h, r: int, work, stream=None) -> None:
+    """df_dpd_coeff_adjoint of the forward call that left `tables`."""
+    check_dpd_tensors(x, None, grad_h, G, r, coeff_name="grad_h")
+    S, L = x.shape
+    B, M = grad_h.shape
+    _check(_lib.df_dpd_coeff_adjoint_tables(_stream_ptr(stream), _dev_ptr(x), _dev_ptr(tables), _bytes(tables),
+                                            _dev_ptr(G), _dev_ptr(grad_h), S, L, r, B, M, _dev_ptr(work), _bytes(work)))
 
 
 def df_dpd_forward_noalloc(x, ctrl, h, y, r: int, hist: int = DF_HIST_BRANCH, stream=None) -> None:
