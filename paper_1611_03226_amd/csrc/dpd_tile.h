@@ -318,7 +318,7 @@ __device__ __forceinline__ void head_correction_any(cfloat2p hg, int M, BOf B_of
 // and head corrections of tile i+1 are loaded while tile i is computed.
 // Bound by VALU issue (16 taps, 2^24 samples, mean length 5.5: 55 M wavefront
 // instructions of arithmetic, 90 us of the chip's issue); the body takes
-// 108 us there, 131 us before the taps were fenced (loads ahead of a tap, one
+// 108 us there, 122 us before the taps were fenced (loads ahead of a tap, one
 // wait behind it), the stores moved behind the wait for the next window, the
 // window slots spread over all banks and the addresses made uniform bases
 // with 32-bit offsets.  The run-time tap loop takes 22 us for 2^21 samples of
@@ -430,10 +430,27 @@ __device__ __forceinline__ void tile_compute(const float2 *sx, cfloat2p ht, cons
   }
 }
 
+// Where pair k of lane's outputs lies in a wavefront's part of the store
+// buffer, in bytes: the pairs of the lanes whose outputs start on the same
+// banks are exchanged against each other.
+template <int K>
+__device__ __forceinline__ uint32_t store_slot(uint32_t lane, int k) {
+  constexpr uint32_t P = K / 2;
+  return (lane * P + (lane / (16 / P)) % P) * 16 ^ (uint32_t)k * 16;
+}
+
 // Store this thread's outputs; in a firing's first tile, outputs q < M-1
 // first add their head correction (staged in sc).
+// A wavefront whose 64 K outputs are all there and start on 16 bytes passes
+// them through its part of `so` (LDS, K * threads samples; null: not given), so
+// that every store instruction writes one run of 1 KiB; stored from where they
+// are formed, 16 bytes of each 8 K bytes at a time, they take the L2 K / 2
+// requests for each run of 8 K bytes.  2^24 samples, 10 branches: 4 taps 73 and 65 us, 8 taps
+// 78 and 72, 16 taps 109 and 108 (VALU-bound; the pass with push and pop 168
+// and 161; 32 firings of 65536 with 10 taps 27.2 and 26.0).
 template <int K>
-__device__ __forceinline__ void tile_store(const float2 *sc, const Job &j, int M, float (&ar)[K], float (&ai)[K]) {
+__device__ __forceinline__ void tile_store(float4 *so, const float2 *sc, const Job &j, int M, float (&ar)[K],
+                                           float (&ai)[K]) {
   const int q0 = threadIdx.x * K;
   if (q0 >= j.nout) return;
   if (j.head && q0 < M - 1) {
@@ -449,6 +466,24 @@ __device__ __forceinline__ void tile_store(const float2 *sc, const Job &j, int M
   int64_t slot;
   if (!ring_run(j.yb, j.y_mask, j.nout, &slot)) {
     char *p = (char *)(j.y + slot);
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (so && (w + 1) * 64 * K <= j.nout && ((uintptr_t)p & 15) == 0) {   // uniform
+      char *b = (char *)so + w * 512 * K, *q = p + (uint32_t)w * (512u * K);
+      uint32_t l = threadIdx.x & 63;
+      asm volatile("" : "+v"(l));                        // the offsets are formed here, not held across the tile
+#pragma unroll
+      for (int k = 0; k < K / 2; ++k)
+        *(float4 *)(b + store_slot<K>(l, k)) = make_float4(ar[2 * k], ai[2 * k], ar[2 * k + 1], ai[2 * k + 1]);
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // read by other lanes of the wavefront
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      // pair 64 c + l is pair l % (K/2) of lane (64 c + l) / (K/2)
+      const uint32_t from = store_slot<K>(l / (K / 2), l % (K / 2));
+#pragma unroll
+      for (int c = 0; c < K / 2; ++c)
+        *(float4 *)(q + 16u * l + 1024u * c) = *(const float4 *)(b + from + 1024 * c);
+      return;
+    }
     const uint32_t off = (uint32_t)q0 * 8u;              // a multiple of 32
     if (q0 + K <= j.nout) {
       if (((uintptr_t)p & 15) == 0) {                    // uniform: pairs of outputs in 16-byte stores
@@ -505,7 +540,7 @@ struct Walk {
 // (src.heads, the whole workgroup, into sc).
 // MT: the compiled tap count, or 0 (any count, Mr).
 template <int MT, int K, int BC, bool MASKED, class Src>
-__device__ __forceinline__ void run_tiles(float2 *sx, float2 *sc, int64_t n_items, Src &src, int Mr) {
+__device__ __forceinline__ void run_tiles(float2 *sx, float2 *sc, float4 *so, int64_t n_items, Src &src, int Mr) {
   constexpr bool CORR = !Src::kOwnHeads;
   const int M = MT ? MT : Mr;
   Walk w;
@@ -527,7 +562,7 @@ __device__ __forceinline__ void run_tiles(float2 *sx, float2 *sc, int64_t n_item
     float ar[K], ai[K];
     tile_compute<MT, K, BC, MASKED>(sx, as_const(cur.h), cur, M, ar, ai);
     if (w.left > 1) settle<K, CORR>(regs);
-    tile_store<K>(sc, cur, M, ar, ai);
+    tile_store<K>(so, sc, cur, M, ar, ai);
     if (w.left == 1) break;
     __syncthreads();
     w.item += w.step;

@@ -234,11 +234,11 @@ struct SingleSrc {
 // pipelined as run_tiles describes.  MT: the compiled tap count (4, 8, 16),
 // or 0: any count, the taps a loop.
 template <int MT, int K, int BC, bool MASKED>
-__global__ __launch_bounds__(256) void k_dpd_tiled(DpdArgs a) {
-  extern __shared__ float2 lds[];   // [M-1] head corrections, window
-  float2 *sc = lds, *sx = sc + lds_corr(MT ? MT : a.M);
+__global__ __launch_bounds__(256, MT == 0 && BC == 10 ? 4 : 1) void k_dpd_tiled(DpdArgs a) {
+  extern __shared__ float4 lds4[];  // outputs on their way to memory, [M-1] head corrections, window
+  float2 *sc = (float2 *)lds4 + a.tile, *sx = sc + lds_corr(MT ? MT : a.M);
   SingleSrc src(a);
-  run_tiles<MT, K, BC, MASKED>(sx, sc, a.n_firings * a.tiles_per_firing, src, a.M);
+  run_tiles<MT, K, BC, MASKED>(sx, sc, lds4, a.n_firings * a.tiles_per_firing, src, a.M);
   if (!a.ticket) return;
   // The last workgroup to finish commits the batch: every other workgroup
   // has read the channel indices by then (it read them before finishing),
@@ -366,9 +366,10 @@ struct SmallTiles : SmallSrc {
 
 template <int MT, int K, int BC, bool MASKED>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_dpd_small(DpdArgs a, ScanArgs c) {
-  extern __shared__ float2 lds[];   // [M-1] head corrections, window, [16][32] parts, [B_max][M] coefficients
+  extern __shared__ float4 lds4[];  // outputs on their way to memory, [M-1] head corrections, window, [16][32] parts,
+                                    // [B_max][M] coefficients
   const int M = MT ? MT : a.M;
-  float2 *sc = lds, *sx = sc + lds_corr(M), *part = sx + lds_window<K>(a.tile + M - 1), *hs = part + 16 * 32;
+  float2 *sc = (float2 *)lds4 + a.tile, *sx = sc + lds_corr(M), *part = sx + lds_window<K>(a.tile + M - 1), *hs = part + 16 * 32;
   const int lane = threadIdx.x & 63, n = (int)a.n_firings;
   bool bad = false;
   uint32_t set = 0u;
@@ -390,7 +391,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     }
   }
   __syncthreads();
-  run_tiles<MT, K, BC, MASKED>(sx, sc, a.n_firings * a.tiles_per_firing, src, a.M);
+  run_tiles<MT, K, BC, MASKED>(sx, sc, lds4, a.n_firings * a.tiles_per_firing, src, a.M);
   __shared__ int last_block, last[kMaxBranches];         // commit by the last workgroup, as k_dpd_tiled
   __syncthreads();
   if (threadIdx.x == 0)
@@ -452,7 +453,7 @@ static hipError_t launch_tiled(const DpdArgs &a0, hipStream_t s, int tile, const
   a.tile = tile;
   a.tiles_per_firing = (int32_t)((a.r + tile - 1) / tile);
   const int threads = tile / K;
-  const size_t lds = (size_t)(lds_window<K>(tile + a.M - 1) + lds_corr(a.M)) * sizeof(float2);
+  const size_t lds = (size_t)(tile + lds_window<K>(tile + a.M - 1) + lds_corr(a.M)) * sizeof(float2);
   const int64_t items = a.n_firings * a.tiles_per_firing;
   if (items <= 0) return hipSuccess;
   const int64_t resident = resident_blocks((const void *)k_dpd_tiled<MT, K, BC, MASKED>, threads, lds);
@@ -475,7 +476,7 @@ static hipError_t launch_small(const DpdArgs &a0, const ScanArgs &c, hipStream_t
   a.tile = tile;
   a.tiles_per_firing = (int32_t)((a.r + tile - 1) / tile);
   const int threads = tile / K;
-  const size_t lds = (size_t)(lds_window<K>(tile + a.M - 1) + lds_corr(a.M) + 16 * 32 + a.B_max * a.M) * sizeof(float2);
+  const size_t lds = (size_t)(tile + lds_window<K>(tile + a.M - 1) + lds_corr(a.M) + 16 * 32 + a.B_max * a.M) * sizeof(float2);
   const int64_t items = a.n_firings * a.tiles_per_firing;
   const int64_t resident = resident_blocks((const void *)k_dpd_small<MT, K, BC, MASKED>, threads, lds);
   const int64_t blocks = items < resident ? items : resident;

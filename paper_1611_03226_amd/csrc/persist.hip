@@ -320,13 +320,19 @@ __device__ __forceinline__ void pers_head(const PersArgs &a, int64_t w) {
   if (head_live<M, 4>(B_of(row))) a.corr_all[(f0 + row) * (M - 1) + q] = make_float2(cr, ci);
 }
 
+// Tiles whose outputs pass through LDS on their way to memory (tile_store):
+// with 4096 outputs that buffer and the window would be more than the 64 KiB
+// of LDS a workgroup has without asking.
+__host__ __device__ constexpr int staged_outputs(int tile) { return tile <= 2048 ? tile : 0; }
+
 // Persistent body: a grid-stride walk over the work items (run_tiles).
 template <int M, int K, int BC, bool MASKED>
 __global__ __launch_bounds__(512) void k_pers_body(PersArgs a) {
-  extern __shared__ float2 lds[];   // [M-1] head corrections, window
-  float2 *sc = lds, *sx = sc + lds_corr(M);
+  extern __shared__ float4 lds4[];  // outputs on their way to memory, [M-1] head corrections, window
+  const int staged = staged_outputs(a.tile);
+  float2 *sc = (float2 *)lds4 + staged, *sx = sc + lds_corr(M);
   ItemSrc src{a};
-  run_tiles<M, K, BC, MASKED>(sx, sc, as_const(a.tile_base)[a.n_inst], src, a.M);
+  run_tiles<M, K, BC, MASKED>(sx, sc, staged ? lds4 : nullptr, as_const(a.tile_base)[a.n_inst], src, a.M);
 }
 
 // The same walk with matrix-core tiles (M = 16).
@@ -415,7 +421,7 @@ void destroy_persistent(df_graph *g) {
 
 template <int M, int K, int BC, bool MASKED>
 static hipError_t launch_pers_body(const PersArgs &a, int threads, int blocks, hipStream_t s, const KTiming *t) {
-  const size_t lds = (size_t)(lds_window<K>(a.tile + M - 1) + lds_corr(M)) * sizeof(float2);
+  const size_t lds = (size_t)(staged_outputs(a.tile) + lds_window<K>(a.tile + M - 1) + lds_corr(M)) * sizeof(float2);
   if (t)
     hipExtLaunchKernelGGL((k_pers_body<M, K, BC, MASKED>), dim3(blocks), dim3(threads), lds, s, t->start, t->stop, 0, a);
   else
