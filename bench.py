@@ -692,15 +692,15 @@ def _md(b, k):
 COUNTER_GROUPS = {
     "dpd_scale": dict(
         file="k_dpd_tiled_dpd_scale_2p24_traffic.md", only="",
-        title="k_dpd_tiled<16,4,10>, 2^24-sample workload (4096 firings of 4096, B 1..10, M 16)",
-        kernels=[("body", "k_dpd_tiled<16, 4, 10, false>",
+        title="k_dpd_tiled<16,8,10>, 2^24-sample workload (4096 firings of 4096, B 1..10, M 16)",
+        kernels=[("body", "k_dpd_tiled<16, 8, 10, false>",
                   lambda b: (b["roofline"]["algorithmic_bytes_per_launch"],
                              b["roofline"]["algorithmic_flops_per_launch"]))]),
     "motion": dict(
         file="k_motion_bits_expand_motion_300x1080p_counters.md", only="motion",
         title="motion actor passes, 300 frames of 1920x1080 per launch (self-delay form)",
-        kernels=[("bits", "k_motion_bits<4, true>", lambda b: (b["motion"]["kernels"]["bits"]["algorithmic_bytes"], 0.0)),
-                 ("expand", "k_motion_expand<true>",
+        kernels=[("bits", "k_motion_bits<4>", lambda b: (b["motion"]["kernels"]["bits"]["algorithmic_bytes"], 0.0)),
+                 ("expand", "k_motion_expand",
                   lambda b: (b["motion"]["kernels"]["expand"]["algorithmic_bytes"], 0.0))]),
     "instances": dict(
         file="k_pers_body_instances_1024_counters.md", only="instances",
@@ -719,7 +719,7 @@ COUNTER_GROUPS = {
         kernels=[("gauss", "k_gauss5_w<4, true, true>", lambda b: _md(b, "gauss")),
                  ("thres", "k_thres_v", lambda b: _md(b, "thres")),
                  ("med", "k_med5_w<4, true>", lambda b: _md(b, "med")),
-                 ("fused", "k_mdp_fused<16>", lambda b: _md(b, "fused"))]),
+                 ("fused", "k_mdp_fused<16", lambda b: _md(b, "fused"))]),
 }
 
 
@@ -937,7 +937,7 @@ def main():
         "roofline": {"bound": "alu", "achieved": round(achieved, 2), "peak": round(FP32_PEAK / 1e12, 1),
                      "unit": "TFLOP/s", "frac": round(achieved * 1e12 / FP32_PEAK, 4), "traffic": measured_traffic(),
                      "algorithmic_bytes_per_launch": m["bytes"], "kernel_sources_sha256": kernel_sources_sha256(),
-                     "kernel": "k_dpd_tiled<16,4,10>", "kernel_ms": round(m["body_ms"], 4),
+                     "kernel": "k_dpd_tiled<16,8,10>", "kernel_ms": round(m["body_ms"], 4),
                      "algorithmic_flops_per_launch": m["flops"],
                      "frac_of_nonpacked_issue": round(achieved * 1e12 / VALU_PEAK, 4),
                      "hbm_frac": round(m["bytes"] / body_s / HBM_PEAK, 4)},
