@@ -927,10 +927,12 @@ static df_status fire_motion(df_graph *g, Actor &a, int64_t n, int flags, int64_
     // counts start at zero; every emit pass leaves the ones it used at zero
     HIPCHK(g, launch_fill_i32(a.count, 0, cap, g->stream));
   }
-  // a captured batch runs when its graph is launched: no number to wait for
+  // A captured batch runs whenever its graph is launched, and moves the
+  // counters each time: from the first capture on, only the device knows them.
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   HIPCHK(g, hipStreamIsCapturing(g->stream, &cs));
-  const bool capturing = cs != hipStreamCaptureStatusNone;
+  if (cs != hipStreamCaptureStatusNone) a.captured = true;
+  MotionCounts *counts = a.captured ? nullptr : a.counts;
   for (int64_t done = 0; done < n; done += chunk_max) {
     const int64_t k = std::min(chunk_max, n - done);
     MotionArgs ma{};
@@ -969,7 +971,7 @@ static df_status fire_motion(df_graph *g, Actor &a, int64_t n, int flags, int64_
     ca.prev_idx = fp ? fp->idx : nullptr;
     ca.out_idx = fm.idx;
     ca.index_idx = fi.idx;
-    ca.host = capturing ? nullptr : a.counts;
+    ca.host = counts;
     ca.seq = ++a.counts_seq;
     ca.err = g->err_dev;
     HIPCHK(g, prof_begin(g, (int)(&a - g->actors.data())));
@@ -982,7 +984,7 @@ static df_status fire_motion(df_graph *g, Actor &a, int64_t n, int flags, int64_
     fm.write_hi += k;
     fi.write_hi += k;
     for (Fifo *f : {&fm, &fi}) {
-      f->counts = capturing ? nullptr : a.counts;
+      f->counts = counts;
       f->counts_at = f == &fi;
       f->counts_seq = a.counts_seq;
     }

@@ -84,6 +84,7 @@ struct Actor {
   int64_t cnt_cap = 0;
   MotionCounts *counts = nullptr;   // page-locked host memory, written by each batch's commit
   uint32_t counts_seq = 0;          // batches so far
+  bool captured = false;            // a batch was captured in a HIP graph
   // Gauss / Thres / Med
   df_frame_params fp{};
 };
