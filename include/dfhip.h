@@ -300,7 +300,9 @@ df_status df_push(df_graph *g, int32_t fifo, const void *src, int64_t n_tokens,
 /* Remove up to max_tokens tokens from a channel the host reads into dst
  * (host, or device when dst_on_device); *n_popped receives the number
  * moved.  A host pop has completed when the call returns; a device pop is
- * stream-ordered.  Errors: DF_ESTATE (an actor reads this channel). */
+ * stream-ordered: behind a data-dependent producer it waits until that
+ * producer's count is known, not for the stream (df_fifo_status does).
+ * Errors: DF_ESTATE (an actor reads this channel). */
 df_status df_pop(df_graph *g, int32_t fifo, void *dst, int64_t max_tokens,
                  int dst_on_device, int64_t *n_popped);
 

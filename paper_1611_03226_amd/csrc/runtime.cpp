@@ -299,8 +299,14 @@ df_status dfh::refresh_fifo(df_graph *g, Fifo &f) {
         return DF_OK;
       }
       if (spins % 4096 == 4095 && hipStreamQuery(g->stream) != hipErrorNotReady) break;
+      __builtin_ia32_pause();
     }
   }
+  return read_fifo(g, f);
+}
+
+df_status dfh::read_fifo(df_graph *g, Fifo &f) {
+  f.counts = nullptr;                                // until its writer's next batch
   HIPCHK(g, hipStreamSynchronize(g->stream));
   int64_t idx[2];
   HIPCHK(g, hipMemcpy(idx, f.idx, sizeof idx, hipMemcpyDeviceToHost));
@@ -314,8 +320,9 @@ extern "C" df_status df_fifo_status(df_graph *g, int32_t fifo, int64_t *read_idx
   ENTER(g);
   if (fifo < 0 || fifo >= (int)g->fifos.size()) return fail(g, DF_EINVAL, "bad fifo id %d", fifo);
   Fifo &f = g->fifos[fifo];
-  if (f.write_lo != f.write_hi) {
-    df_status st = refresh_fifo(g, f);
+  // synchronises, also where a pop has learned the count without
+  if (f.write_lo != f.write_hi || f.counts) {
+    df_status st = read_fifo(g, f);
     if (st) return st;
   }
   if (read_idx) *read_idx = f.read_h;

@@ -125,7 +125,10 @@ struct df_graph {
 namespace dfh {
 df_status fail(df_graph *g, df_status st, const char *fmt, ...);
 df_status fail_hip(df_graph *g, hipError_t e, const char *what);
+// Learn a data-dependent producer's counts: refresh_fifo waits for its last
+// batch's commit, read_fifo for the whole stream.
 df_status refresh_fifo(df_graph *g, Fifo &f);
+df_status read_fifo(df_graph *g, Fifo &f);
 // Synchronise and turn the sticky device error word into a status.
 df_status sync_errors(df_graph *g);
 // Result of a token-moving call: with DFHIP_CHECK_INDICES set, a successful
