@@ -67,5 +67,13 @@ inline int64_t reused_batch(int64_t last, int64_t cap, int64_t base, int64_t n) 
   return p < base ? -1 : (p - base) / n;
 }
 
+// Firings of a motion batch one launch may cover: its passes have a grid row
+// per firing, at most 65535, and with a self-delay the last pass one more for
+// the state; and at most 512 MiB of staged mask bits.
+inline int64_t motion_chunk(int64_t frame_bits, bool self_delay) {
+  const int64_t rows = 65535 - (self_delay ? 1 : 0), staged = (512ll << 20) / frame_bits;
+  return staged < 1 ? 1 : staged < rows ? staged : rows;
+}
+
 }  // namespace host
 }  // namespace dfh

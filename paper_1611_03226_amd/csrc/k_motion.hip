@@ -395,6 +395,7 @@ static BitsShape bits_shape(const MotionArgs &a, int n_chunks) {
 
 hipError_t launch_motion_count(const MotionArgs &a, hipStream_t s) {
   if (a.n <= 0) return hipSuccess;
+  if (a.n + (a.state_src ? 1 : 0) > 65535) return hipErrorInvalidValue;   // grid rows of the expand pass
   const int n_chunks = (a.words_per_row + MW_CHUNK - 1) / MW_CHUNK;
   const BitsShape sh = bits_shape(a, n_chunks);
   const int n_bands = (a.H + sh.rows - 1) / sh.rows;

@@ -920,8 +920,7 @@ static df_status fire_motion(df_graph *g, Actor &a, int64_t n, int flags, int64_
   const int64_t wh = (int64_t)p.width * p.height;
   const int32_t wpr = (p.width + 31) / 32;
   const int64_t frame_bits = (int64_t)wpr * p.height * 4;
-  // firings per chunk: grid limit of one launch, and <= 512 MiB of staged bits
-  const int64_t chunk_max = std::max<int64_t>(1, std::min<int64_t>(65535, (512ll << 20) / frame_bits));
+  const int64_t chunk_max = host::motion_chunk(frame_bits, p.self_delay != 0);
   const int64_t want = std::min(n, chunk_max);
   if (want > a.cnt_cap) {
     HIPCHK(g, hipStreamSynchronize(g->stream));

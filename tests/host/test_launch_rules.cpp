@@ -1,0 +1,34 @@
+// Host unit test of the rules that size a launch (csrc/host_logic.h): what
+// they give stays inside the device's grid limits over the whole range of
+// accepted sizes.
+#include "host_logic.h"
+
+#include <cstdio>
+#include <cstdlib>
+
+using namespace dfh::host;
+
+#define CHECK(c)                                              \
+  do {                                                        \
+    if (!(c)) {                                               \
+      std::fprintf(stderr, "line %d: %s\n", __LINE__, #c);    \
+      std::exit(1);                                           \
+    }                                                         \
+  } while (0)
+
+// Motion: a grid row per firing, and one for the self-delay state.
+static void motion() {
+  for (int64_t w = 1; w <= 65536; w = w * 5 / 4 + 1)
+    for (int64_t h = 1; h <= 65536; h = h * 5 / 4 + 1)
+      for (int delay = 0; delay < 2; ++delay) {
+        const int64_t bits = (w + 31) / 32 * h * 4, n = motion_chunk(bits, delay);
+        CHECK(n >= 1 && n + delay <= 65535);
+        CHECK(n == 1 || n * bits <= (512ll << 20));
+      }
+}
+
+int main() {
+  motion();
+  std::puts("launch rules: ok");
+  return 0;
+}

@@ -69,3 +69,36 @@ def test_status_synchronises():
             assert G.status(mc.mask)[1] == (k if pop_first else k // 2)
             assert s.query()
         G.sync()
+
+
+@pytest.mark.parametrize("self_delay", [True, False])
+def test_batch_beyond_one_launch(self_delay):
+    """More firings than one launch's grid rows, in one batch and in batches of
+    a few thousand: the same masks and indices, and the right state behind."""
+    import torch
+    from paper_1611_03226_amd.graph import Graph
+    n, H, W = 65600, 5, 9
+    say(f"motion batch of {n} firings, self_delay={self_delay}")
+    frames = np.repeat(np.random.default_rng(3).integers(0, 256, (1, H, W)), n, 0).astype(np.uint8)
+    frames[1::7, 1:4, 2:6] ^= 0x80
+    frames[65533:65537] = np.random.default_rng(4).integers(0, 256, (4, H, W)) // 128 * 255
+    out = []
+    for step in (n, 4100):
+        with Graph(0) as G:
+            mc = G.motion_chain(W, H, self_delay=self_delay, cap_in=1 << 17, cap_out=1 << 17)
+            G.push(mc.cur, frames)
+            if not self_delay:
+                G.push(mc.prev, frames)
+            for k in range(0, n, step):
+                assert G.fire(mc.actor, min(step, n - k)) == min(step, n - k)
+            m, i = np.zeros((n, H, W), np.uint8), np.zeros(n, np.int64)
+            got = G.pop(mc.mask, m)
+            assert G.pop(mc.index, i) == got
+            G.sync()
+            out.append((m[:got], i[:got]))
+    assert np.array_equal(out[0][1], out[1][1]) and np.array_equal(out[0][0], out[1][0])
+    lo = 65520
+    ref_m, ref_i = omo.run_motion(frames[lo:])           # its first frame sees the zero frame
+    late = out[0][1] > lo
+    assert np.array_equal(out[0][1][late], ref_i[ref_i > 0] + lo)
+    assert np.array_equal(out[0][0][late], ref_m[ref_i > 0])
