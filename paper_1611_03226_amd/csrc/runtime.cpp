@@ -98,7 +98,6 @@ extern "C" df_status df_graph_create(df_graph **out, int device, void *stream) {
   df_graph *g = new (std::nothrow) df_graph();
   if (!g) return fail(nullptr, DF_ENOMEM, "host allocation failed");
   g->device = device;
-  g->many_devices = n > 1;
   if ((e = hipSetDevice(device)) != hipSuccess) {
     delete g;
     return fail(nullptr, DF_EDEVICE, "hipSetDevice: %s", hipGetErrorString(e));
@@ -579,15 +578,21 @@ static hipError_t paper_fixup(df_graph *g, const Fifo &f, int64_t pos, int64_t n
   return hipMemcpyAsync(f.ring, f.ring + f.period * tb, tb, hipMemcpyDeviceToDevice, g->stream);
 }
 
-// Memory of the graph's own device (elsewhere, a runtime copy reaches it).
-static bool on_own_device(const df_graph *g, const void *p) {
-  if (!g->many_devices) return true;
+// Whether [p, p + bytes) is one allocation's memory on the graph's own device.
+// Anything else (host or managed memory, a peer's, a buffer that ends before
+// the tokens do) is the runtime copy's to reach or to refuse: a kernel would
+// fault there.
+static bool own_device_range(const df_graph *g, const void *p, int64_t bytes) {
   hipPointerAttribute_t at;
-  if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+  hipDeviceptr_t base = nullptr;
+  size_t size = 0;
+  if (hipPointerGetAttributes(&at, p) != hipSuccess ||
+      (at.type == hipMemoryTypeDevice && hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)p) != hipSuccess)) {
     (void)hipGetLastError();
     return false;
   }
-  return at.type == hipMemoryTypeDevice && at.device == g->device;
+  return at.type == hipMemoryTypeDevice && at.device == g->device && (const char *)p - (const char *)base >= 0 &&
+         (const char *)p + bytes <= (const char *)base + size;
 }
 
 // Move n tokens between a channel (position pos) and a flat buffer and
@@ -595,7 +600,7 @@ static bool on_own_device(const df_graph *g, const void *p) {
 // copy and the counter (at most two runs: n is at most the capacity).
 static hipError_t move_tokens(df_graph *g, Fifo &f, int64_t pos, void *flat, int64_t n, bool to_ring,
                               bool flat_on_device, int64_t *idx) {
-  if (!flat_on_device || !on_own_device(g, flat)) {
+  if (!flat_on_device || !own_device_range(g, flat, n * f.token_bytes)) {
     hipError_t e = ring_copy(g, f, pos, flat, n, to_ring, flat_on_device);
     if (e == hipSuccess && to_ring) e = paper_fixup(g, f, pos, n);
     return e == hipSuccess ? launch_advance(idx, n, g->err_dev, g->stream) : e;

@@ -100,7 +100,6 @@ struct df_graph {
   bool no_scan_ahead = false;        // DFHIP_SCAN_AHEAD=0: no scan of the next batch in the head pass
   bool own_stream = false;
   bool poisoned = false;
-  bool many_devices = false;         // the process sees other GPUs too
   std::string last_error;
   std::vector<dfh::Fifo> fifos;
   std::vector<dfh::Actor> actors;
