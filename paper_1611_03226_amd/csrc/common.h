@@ -175,6 +175,7 @@ struct DpdArgs {
   // (control tokens only): its first ahead_blocks workgroups do it.
   ScanArgs ahead;
   int32_t ahead_blocks;
+  int64_t head_block0;    // first workgroup of this launch of the head pass
 };
 
 // ---------------------------------------------------------------- motion

@@ -75,5 +75,15 @@ inline int64_t motion_chunk(int64_t frame_bits, bool self_delay) {
   return staged < 1 ? 1 : staged < rows ? staged : rows;
 }
 
+// A launch has fewer than 2^32 threads; half of that is the most asked for.
+constexpr int64_t kMaxThreads = 1ll << 31;
+
+// Segments short enough for the one-launch scan (a wavefront per branch walks
+// a segment 64 firings at a time), and few enough for its grid.
+constexpr int64_t kRowFirings = 512;
+inline bool scan_in_rows(int64_t n_segs, int64_t seg_firings, int B_max) {
+  return seg_firings <= kRowFirings && n_segs <= kMaxThreads / (64 * B_max);
+}
+
 }  // namespace host
 }  // namespace dfh

@@ -11,11 +11,13 @@
 // state); those terms are added by a per-branch correction.
 #include <hip/hip_ext.h>
 
+#include <algorithm>
 #include <cstdlib>
 #include <cstring>
 
 #include "common.h"
 #include "dpd_tile.h"
+#include "host_logic.h"
 #include "scan_dev.h"
 
 namespace dfh {
@@ -107,7 +109,7 @@ __global__ __launch_bounds__(256) void k_dpd_heads(DpdArgs a) {
       return;
     }
   }
-  const int64_t hb = (int64_t)blockIdx.x - a.ahead_blocks;
+  const int64_t hb = a.head_block0 + (int64_t)blockIdx.x - a.ahead_blocks;
   if (a.err_ahead && hb == 0 && threadIdx.x == 0) {
     const int32_t e = *a.err_ahead;
     if (e) {
@@ -501,17 +503,23 @@ hipError_t launch_dpd_heads(const DpdArgs &a, hipStream_t s) {
                                                a.ahead_blocks != (scan_groups(1, a.ahead.seg_firings) + 3) / 4)))
     return hipErrorInvalidValue;
   const int nr = compiled_taps(a.M) ? 4 : 2;           // firings per workgroup
-  const dim3 grid((unsigned)((a.n_firings + nr - 1) / nr + a.ahead_blocks));
+  // in pieces that a grid can hold beside the scan's workgroups
+  const int64_t blocks = (a.n_firings + nr - 1) / nr, most = host::kMaxThreads / 512;
+  for (DpdArgs p = a; p.head_block0 < blocks; p.head_block0 += most, p.ahead_blocks = 0) {
+    const dim3 grid((unsigned)(std::min(blocks - p.head_block0, most) + p.ahead_blocks));
 #define DF_HEADS(m)                                                                     \
   if (m == 0 || a.M == m) {                                                             \
     if (a.grp)                                                                          \
-      hipLaunchKernelGGL((k_dpd_heads<m, true>), grid, dim3(256), 0, s, a);             \
+      hipLaunchKernelGGL((k_dpd_heads<m, true>), grid, dim3(256), 0, s, p);             \
     else                                                                                \
-      hipLaunchKernelGGL((k_dpd_heads<m, false>), grid, dim3(256), 0, s, a);            \
+      hipLaunchKernelGGL((k_dpd_heads<m, false>), grid, dim3(256), 0, s, p);            \
   }
-  DF_HEADS(16) else DF_HEADS(8) else DF_HEADS(4) else DF_HEADS(0)
+    DF_HEADS(16) else DF_HEADS(8) else DF_HEADS(4) else DF_HEADS(0)
 #undef DF_HEADS
-  return hipGetLastError();
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 struct TileShape {

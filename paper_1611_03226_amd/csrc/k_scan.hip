@@ -34,6 +34,7 @@
 #include <algorithm>
 #include <mutex>
 
+#include "host_logic.h"
 #include "scan_dev.h"
 
 namespace dfh {
@@ -74,9 +75,7 @@ __global__ __launch_bounds__(256) void k_scan_tables(ScanArgs a, int64_t n_group
 // and last feeder, so nothing passes between wavefronts and no ticket has to
 // be cleared.  Bound by latency: 6 segments of 40 firings take 3 us, against
 // 2 + 5 + 3 us and two kernel boundaries for the three launches above; the
-// walk is serial, so long segments keep those (kRowFirings).
-constexpr int64_t kRowFirings = 512;
-
+// walk is serial, so long segments keep those (host::scan_in_rows).
 __global__ __launch_bounds__(1024) void k_scan_rows(ScanArgs a) {
   const int64_t seg = blockIdx.x, g0 = seg * a.seg_firings;
   const int b = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -158,7 +157,7 @@ hipError_t launch_scan(const ScanArgs &a, hipStream_t s, bool tables, bool zero_
   if (a.n_segs <= 0 || a.seg_firings <= 0) return hipSuccess;
   if (a.B_max < 1 || a.B_max > kMaxBranches || !a.grp || !a.ticket) return hipErrorInvalidValue;
   if (a.seg_firings > INT32_MAX || (a.lgrp && a.n_segs != 1)) return hipErrorInvalidValue;
-  if (tables && !a.lgrp && a.seg_firings <= kRowFirings) {
+  if (tables && !a.lgrp && host::scan_in_rows(a.n_segs, a.seg_firings, a.B_max)) {
     hipLaunchKernelGGL(k_scan_rows, dim3((unsigned)a.n_segs), dim3(64 * a.B_max), 0, s, a);
     return hipGetLastError();
   }

@@ -5,6 +5,7 @@
 
 #include <cstdio>
 #include <cstdlib>
+#include <initializer_list>
 
 using namespace dfh::host;
 
@@ -27,8 +28,20 @@ static void motion() {
       }
 }
 
+// One-launch scan: a workgroup per segment, a wavefront per branch.
+static void scan_rows() {
+  for (int B = 1; B <= 16; ++B)
+    for (int64_t segs = 1; segs < 1ll << 34; segs = segs * 3 / 2 + 1)
+      for (int64_t firings : {1, 64, 512, 513}) {
+        const bool rows = scan_in_rows(segs, firings, B);
+        CHECK(!rows || (firings <= 512 && segs * 64 * B < 1ll << 32));
+        CHECK(rows || firings > 512 || segs * 64 * B > 1ll << 30);
+      }
+}
+
 int main() {
   motion();
+  scan_rows();
   std::puts("launch rules: ok");
   return 0;
 }
