@@ -114,6 +114,8 @@ class PALossFunction(torch.autograd.Function):
 
     @staticmethod
     def backward(ctx, gloss):
+        if not ctx.needs_input_grad[0]:          # only a or x asks, and both are fixed
+            return None, None, None
         u, a, e = ctx.saved_tensors
         gu = torch.empty_like(u)
         D.df_mp_loss_adjoint(u, a, e, gloss.contiguous(), gu, stream=_stream())

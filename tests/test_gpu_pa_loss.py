@@ -104,3 +104,25 @@ def test_adaptation_loss_equals_torch_expression(x_grad):
         assert torch.equal(out[0][2], out[1][2])
     with torch.no_grad():
         assert torch.equal(adaptation_loss(x, h, a, 2051), adaptation_loss(x, h, a, 2051))
+
+
+@pytest.mark.parametrize("h_grad", [False, True])
+def test_adaptation_loss_with_a_variable_amplifier(h_grad):
+    """A model whose coefficients require a gradient is fixed all the same: the
+    backward runs and leaves none there, as PAFunction's does."""
+    from paper_1611_03226_amd.autograd import adaptation_loss
+    say(f"adaptation loss, a requires grad, h_grad={h_grad}")
+    rng = np.random.default_rng(11)
+    x = _t(complex_gaussian(rng, (2, 300), rms=0.3))
+    a0 = _t(pa_coeffs(rng))
+    h0 = _t((0.02 * rng.standard_normal((4, 8)) + 0j).astype(np.complex64))
+    a, h = a0.clone().requires_grad_(True), h0.clone().requires_grad_(h_grad)
+    loss = adaptation_loss(x, h, a, 300)
+    loss.backward()
+    assert a.grad is None
+    hr = h0.clone().requires_grad_(True)
+    ref = adaptation_loss(x, hr, a0, 300)
+    ref.backward()
+    assert loss.item() == ref.item()
+    if h_grad:
+        assert (h.grad - hr.grad).norm() == 0
