@@ -85,5 +85,33 @@ inline bool scan_in_rows(int64_t n_segs, int64_t seg_firings, int B_max) {
   return seg_firings <= kRowFirings && n_segs <= kMaxThreads / (64 * B_max);
 }
 
+// Shape of a predistortion tile: outputs per thread and per workgroup (at
+// most 256 threads).  A caller's own choice of either value stands.
+// By default 2048 outputs with eight per thread where firings fill such tiles
+// and there is one for each of the 256 compute units (fewer scalar loads, LDS
+// reads and |x|^2 per output; ms against 1024 with four: 32 firings of 65536,
+// 10 taps 0.022 / 0.029; 256 of 4096, 16 taps 0.016 / 0.021; 4096 of 4096
+// 0.108 / 0.107; 128 of 4096 0.014 / 0.014), else 1024 with four (777 firings
+// of 1000: 0.019 / 0.023).  The matrix-core form (mx) keeps 1024 with four:
+// its row sums make a 2048-output tile 88 KB of LDS, one workgroup a compute
+// unit (us a pass, 2048/8 and 1024/4: 4096 firings of 4096 361 / 281, 256 of
+// 4096 48 / 47, 32 of 65536 66 / 59).
+// The tile is a multiple of 64*K outputs and no larger than needed for one
+// firing.
+struct TileShape {
+  int K, tile;
+};
+inline TileShape tile_shape(int64_t n_firings, int64_t r, bool mx, int tile, int outputs_per_thread) {
+  const bool big = !mx && tile <= 0 && r >= 2048 && n_firings * r >= 256 * 2048;
+  const int K = outputs_per_thread == 8 || (outputs_per_thread == 0 && big) ? 8 : 4;
+  int tl = tile > 0 ? tile : (outputs_per_thread == 0 && big ? 2048 : 1024);
+  const int64_t rr = ((r + 64 * K - 1) / (64 * K)) * (64 * K);
+  if ((int64_t)tl > rr) tl = (int)rr;
+  tl = (tl / (64 * K)) * (64 * K);
+  if (tl < 64 * K) tl = 64 * K;
+  if (tl / K > 256) tl = 256 * K;
+  return TileShape{K, tl};
+}
+
 }  // namespace host
 }  // namespace dfh

@@ -522,29 +522,8 @@ hipError_t launch_dpd_heads(const DpdArgs &a, hipStream_t s) {
   return hipSuccess;
 }
 
-struct TileShape {
-  int K, tile;
-};
-
-static TileShape tile_shape(const DpdArgs &a, int tile, int outputs_per_thread) {
-  // Shape: 2048 outputs with eight per thread where firings fill such tiles
-  // and there is one for each of the 256 compute units (fewer scalar loads,
-  // LDS reads and |x|^2 per output; ms against 1024 with four: 32 firings of
-  // 65536, 10 taps 0.022 / 0.029; 256 of 4096, 16 taps 0.016 / 0.021; 4096 of
-  // 4096 0.108 / 0.107; 128 of 4096 0.014 / 0.014), else 1024 with four (777
-  // firings of 1000: 0.019 / 0.023).  A caller's own choice of either value
-  // stands (df_set_tile).
-  // The tile is a multiple of 64*K outputs, at most 256 threads, no larger
-  // than needed for one firing.
-  const bool big = tile <= 0 && a.r >= 2048 && a.n_firings * a.r >= 256 * 2048;
-  const int K = outputs_per_thread == 8 || (outputs_per_thread == 0 && big) ? 8 : 4;
-  int tl = tile > 0 ? tile : (outputs_per_thread == 0 && big ? 2048 : 1024);
-  const int64_t rr = ((a.r + 64 * K - 1) / (64 * K)) * (64 * K);
-  if ((int64_t)tl > rr) tl = (int)rr;
-  tl = (tl / (64 * K)) * (64 * K);
-  if (tl < 64 * K) tl = 64 * K;
-  if (tl / K > 256) tl = 256 * K;
-  return {K, tl};
+static host::TileShape tile_shape(const DpdArgs &a, int tile, int outputs_per_thread) {
+  return host::tile_shape(a.n_firings, a.r, a.M == 16 && a.mx, tile, outputs_per_thread);
 }
 
 hipError_t launch_dpd_small(const DpdArgs &a, const ScanArgs &c, hipStream_t s, int tile, int outputs_per_thread,
@@ -552,7 +531,7 @@ hipError_t launch_dpd_small(const DpdArgs &a, const ScanArgs &c, hipStream_t s, 
   if (a.n_firings < 1 || a.n_firings > 64 || !a.ht || !a.h || !a.hist || !a.x_idx || !a.y_idx || !a.ticket || !c.ctrl ||
       !c.B_out || !c.prev_out || !c.off_out || !c.err || a.M < 1 || a.M > kMaxTaps)
     return hipErrorInvalidValue;
-  const TileShape sh = tile_shape(a, tile, outputs_per_thread);
+  const host::TileShape sh = tile_shape(a, tile, outputs_per_thread);
   const bool small = a.B_max <= 10;
 #define DF_SMALL(m, k)                                                                       \
   if ((m == 0 || a.M == m) && sh.K == k)                                                     \
@@ -568,7 +547,7 @@ hipError_t launch_dpd_small(const DpdArgs &a, const ScanArgs &c, hipStream_t s, 
 hipError_t launch_dpd_body(const DpdArgs &a, hipStream_t s, int tile, int outputs_per_thread, const KTiming *t) {
   if (a.n_firings <= 0) return hipSuccess;
   if (!a.ht || a.M < 1 || a.M > kMaxTaps) return hipErrorInvalidValue;
-  const TileShape sh = tile_shape(a, tile, outputs_per_thread);
+  const host::TileShape sh = tile_shape(a, tile, outputs_per_thread);
   const int K = sh.K, tl = sh.tile;
   // compiled paths: Horner lengths up to 10 or up to 16; branch sets that are
   // not prefixes (bit-mask tokens) take the masked paths up to 16

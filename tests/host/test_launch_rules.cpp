@@ -39,7 +39,26 @@ static void scan_rows() {
       }
 }
 
+// Predistortion tiles: whole wavefronts, at most 256 threads, no larger than
+// a firing needs; the caller's values stand; the matrix-core form keeps the
+// shape it is fastest with.
+static void tiles() {
+  for (int64_t n : {1, 63, 64, 300, 4096})
+    for (int64_t r = 1; r <= 1 << 17; r = r * 5 / 4 + 1)
+      for (int mx = 0; mx < 2; ++mx)
+        for (int tile : {0, 256, 512, 1024, 2048, 4096})
+          for (int k : {0, 4, 8}) {
+            const TileShape s = tile_shape(n, r, mx, tile, k);
+            CHECK((s.K == 4 || s.K == 8) && s.tile % (64 * s.K) == 0 && s.tile >= 64 * s.K && s.tile <= 256 * s.K);
+            CHECK(s.tile < r + 64 * s.K);
+            CHECK((k == 0 || s.K == k) && (tile == 0 || s.tile <= tile || s.tile == 64 * s.K));
+            if (mx && !tile && !k) CHECK(s.K == 4 && s.tile <= 1024);
+          }
+  CHECK(tile_shape(4096, 4096, false, 0, 0).tile == 2048 && tile_shape(4096, 4096, true, 0, 0).tile == 1024);
+}
+
 int main() {
+  tiles();
   motion();
   scan_rows();
   std::puts("launch rules: ok");
