@@ -11,6 +11,10 @@ constexpr int kMaxTaps = 32;
 // Complex coefficients per tap in the tap-major layout the bodies read (the
 // branches of one tap are consecutive).
 constexpr int kCoefRow = kMaxBranches;
+// Counters of a batch's finished workgroups (last_workgroup in k_dpd.hip):
+// one for the batch and one per group, 128 bytes apart.
+constexpr int kTicketGroups = 32, kTicketStride = 32;
+constexpr size_t kTicketBytes = sizeof(int32_t) * (1 + kTicketGroups) * kTicketStride;
 
 // Sticky device error bits (an int32 in device memory per graph).
 enum : int32_t { kErrControl = 1, kErrIndex = 2 };
@@ -166,7 +170,7 @@ struct DpdArgs {
   int32_t hist_mode;
   int32_t masked;         // branch sets may be non-prefix (bit-mask control tokens)
   int32_t mx;             // M = 16 tiled body on the matrix cores (else the VALU form)
-  int32_t *ticket;        // tiled kernel: the last workgroup to finish runs `commit` (nullptr: none)
+  int32_t *ticket;        // tiled kernel: kTicketBytes of zeros; the last workgroup to finish runs `commit` (nullptr: none)
   DpdCommitArgs commit;
   int32_t *err;           // sticky error word (head pass; may be nullptr)
   int32_t *err_ahead;     // errors of a scan run ahead of this batch: the head pass adds them to err

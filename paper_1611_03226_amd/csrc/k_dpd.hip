@@ -192,6 +192,36 @@ __global__ __launch_bounds__(256) void k_dpd_heads(DpdArgs a) {
   }
 }
 
+// Whether this workgroup is the launch's last to come here.  Every other
+// workgroup has read the channel indices by then (it read them before), and
+// the commit reads nothing another workgroup wrote, so relaxed counters
+// suffice (a device-scope fence here would write back the L2).
+// Increments of one word by the whole chip take about 13 ns each, one after
+// the other: more than the work of short firings (4096 of 64 samples: body 53
+// us, now 8; 30000 of 40, 16 taps: 105 and 53).  So a larger grid counts on kTicketGroups words first, each
+// on a cache line of its own and fed by workgroups of one XCD, and the last of
+// a group on the first word.  All words are left at zero for the next batch.
+__device__ __forceinline__ bool last_workgroup(int32_t *ticket) {
+  __shared__ int last;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const auto count = [](int32_t *p, int n) {
+      if (__hip_atomic_fetch_add(p, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != n - 1) return false;
+      __hip_atomic_store(p, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      return true;
+    };
+    const int grid = (int)gridDim.x, of = (int)blockIdx.x % kTicketGroups;
+    if (grid <= 4 * kTicketGroups) {
+      last = count(ticket, grid);
+    } else {
+      last = count(ticket + (1 + of) * kTicketStride, (grid - of + kTicketGroups - 1) / kTicketGroups) &&
+             count(ticket, kTicketGroups);
+    }
+  }
+  __syncthreads();
+  return last;
+}
+
 // ------------------------------------------------------------------ tiled
 // Tile descriptors of a single actor's batch: tile k is tile k % tpf of the
 // (k / tpf)-th firing in processing order (pairs (firing, branch set) from
@@ -241,21 +271,8 @@ __global__ __launch_bounds__(256, MT == 0 && BC == 10 ? 4 : 1) void k_dpd_tiled(
   float2 *sc = (float2 *)lds4 + a.tile, *sx = sc + lds_corr(MT ? MT : a.M);
   SingleSrc src(a);
   run_tiles<MT, K, BC, MASKED>(sx, sc, lds4, a.n_firings * a.tiles_per_firing, src, a.M);
-  if (!a.ticket) return;
-  // The last workgroup to finish commits the batch: every other workgroup
-  // has read the channel indices by then (it read them before finishing),
-  // and the commit reads nothing another workgroup wrote, so a relaxed
-  // counter suffices (a device-scope fence here would write back the L2).
-  __shared__ int last_block;
-  __syncthreads();
-  if (threadIdx.x == 0)
-    last_block = __hip_atomic_fetch_add(a.ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
-                 (int)gridDim.x - 1;
-  __syncthreads();
-  if (last_block) {
+  if (a.ticket && last_workgroup(a.ticket))
     dpd_commit_block(a.commit, [&](int b) { return a.commit.last[b]; });
-    if (threadIdx.x == 0) *a.ticket = 0;              // ready for the next batch
-  }
 }
 
 // ------------------------------------------------------------------ small batches
@@ -394,12 +411,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
   }
   __syncthreads();
   run_tiles<MT, K, BC, MASKED>(sx, sc, lds4, a.n_firings * a.tiles_per_firing, src, a.M);
-  __shared__ int last_block, last[kMaxBranches];         // commit by the last workgroup, as k_dpd_tiled
-  __syncthreads();
-  if (threadIdx.x == 0)
-    last_block = __hip_atomic_fetch_add(a.ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
-  __syncthreads();
-  if (!last_block) return;
+  if (!last_workgroup(a.ticket)) return;
+  __shared__ int last[kMaxBranches];
   if (threadIdx.x < 64)
     for (int b = 0; b < a.B_max; ++b) {
       const uint64_t f = src.fed(b);
@@ -407,7 +420,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     }
   __syncthreads();
   dpd_commit_block(a.commit, [&](int b) { return (int64_t)last[b]; });
-  if (threadIdx.x == 0) *a.ticket = 0;
 }
 
 // The same loop with matrix-core tiles (M = 16).
@@ -417,17 +429,8 @@ __global__ __launch_bounds__(256) void k_dpd_tiled_mx(DpdArgs a) {
   float2 *sc = lds, *sx = sc + lds_corr(16), *rb = sx + mx_window<K>(a.tile), *sh = rb + 4 * mx_row(a.tile);
   SingleSrc src(a);
   run_tiles_mx<K, BC, MASKED>(sx, sc, rb, sh, a.n_firings * a.tiles_per_firing, src);
-  if (!a.ticket) return;
-  __shared__ int last_block;                         // commit by the last workgroup, as above
-  __syncthreads();
-  if (threadIdx.x == 0)
-    last_block = __hip_atomic_fetch_add(a.ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
-                 (int)gridDim.x - 1;
-  __syncthreads();
-  if (last_block) {
+  if (a.ticket && last_workgroup(a.ticket))
     dpd_commit_block(a.commit, [&](int b) { return a.commit.last[b]; });
-    if (threadIdx.x == 0) *a.ticket = 0;
-  }
 }
 
 template <int K, int BC, bool MASKED>

@@ -387,7 +387,7 @@ extern "C" df_status df_actor_create(df_graph *g, df_actor_kind kind, const void
     const size_t o_h = region(sizeof(float2) * B * M), o_ht = region(coef_rows_bytes(p.n_taps)),
                  o_hist = region(sizeof(float2) * B * std::max<size_t>(M - 1, 1)),
                  o_last[2] = {region(sizeof(int64_t) * B), region(sizeof(int64_t) * B)},
-                 o_words = region(3 * sizeof(int32_t));
+                 o_ticket = region(kTicketBytes), o_words = region(2 * sizeof(int32_t));
     if ((e = hipMalloc((void **)&a.block, bytes)) != hipSuccess) return fail(g, DF_ENOMEM, "actor allocation failed");
     a.h = (float2 *)(a.block + o_h);
     a.ht = (float2 *)(a.block + o_ht);
@@ -396,14 +396,14 @@ extern "C" df_status df_actor_create(df_graph *g, df_actor_kind kind, const void
       a.scan[i].last = (int64_t *)(a.block + o_last[i]);
       a.scan[i].err = (int32_t *)(a.block + o_words) + i;
     }
-    a.ticket = (int32_t *)(a.block + o_words) + 2;
+    a.ticket = (int32_t *)(a.block + o_ticket);
     if (p.coeffs_on_device) {
       e = hipMemset(a.block, 0, bytes);
       if (e == hipSuccess) e = hipMemcpy(a.h, p.coeffs, sizeof(float2) * B * M, hipMemcpyDeviceToDevice);
       if (e == hipSuccess) e = launch_coef_rows(a.h, a.ht, p.n_branches_max, p.n_taps, nullptr);
       if (e == hipSuccess) e = hipStreamSynchronize(nullptr);   // the graph's stream does not wait for this one
     } else {
-      alignas(256) char image[16384] = {};               // 12.75 KiB at 16 branches and 32 taps
+      alignas(256) char image[18432] = {};               // 17 KiB at 16 branches and 32 taps
       if (bytes > sizeof image) {
         free_actor(a);
         return fail(g, DF_EINVAL, "actor state of %zu bytes", bytes);

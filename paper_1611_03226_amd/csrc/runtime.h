@@ -61,7 +61,7 @@ struct Actor {
   float2 *corr = nullptr;    // [scratch_n][M-1] head corrections
   int64_t *prev = nullptr;   // [B_max][scratch_n]
   int64_t *off = nullptr;    // [B_max][scratch_n]
-  int32_t *ticket = nullptr; // finished-workgroup counter of the body (commit by the last one)
+  int32_t *ticket = nullptr; // finished-workgroup counters of the body (commit by the last one)
   // Scan results of a batch, in two slots: the scan of the next batch (it
   // reads control tokens only) runs ahead, inside this batch's head pass,
   // and is used if the next batch starts where it assumed and has its size.
