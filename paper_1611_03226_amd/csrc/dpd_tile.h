@@ -278,33 +278,39 @@ __device__ __forceinline__ void head_correction(cfloat2p hg, BOf B_of, SrcOf src
   }
 }
 
-// The same for any tap count (M <= 32): rows of 32 lanes, two firings per
-// wavefront, the taps a loop and psi moved by lane shuffles.
-template <class BOf, class SrcOf, class Sample, class Emit>
+// The same for any tap count (M <= RL + 1): rows of RL lanes, the taps a loop
+// and psi moved by lane shuffles; branches b_first, b_first + 4, ...
+// (src_of also takes which of them it is).
+template <int RL, class BOf, class SrcOf, class Sample, class Emit>
 __device__ __forceinline__ void head_correction_any(cfloat2p hg, int M, BOf B_of, SrcOf src_of, Sample sample,
-                                                    int b_first, int b_step, Emit emit) {
+                                                    int b_first, Emit emit) {
   const int L = M - 1;
-  const int lane = threadIdx.x & 63, row = lane >> 5, i = lane & 31;
+  const int lane = threadIdx.x & 63, row = lane / RL, i = lane % RL;
   const uint32_t set = (uint32_t)B_of(row);
-  int Bw = set_len(set);
-  Bw = __builtin_amdgcn_readfirstlane(max(Bw, __shfl_xor(Bw, 32)));
-  for (int b = b_first; b < Bw; b += b_step) {           // uniform
+  int Bw = set_len(set);                                 // largest Horner length of the wavefront
+#pragma unroll
+  for (int o = RL; o < 64; o <<= 1) Bw = max(Bw, __shfl_xor(Bw, o));
+  Bw = __builtin_amdgcn_readfirstlane(Bw);
+#pragma unroll
+  for (int c = 0; c < kMaxBranches; c += 4) {
+    const int b = c + b_first;
+    if (b >= Bw) break;                                  // uniform
     float2 xv = make_float2(0.f, 0.f);
-    if (in_set(set, b) && i < L) xv = sample(row, b, src_of(row, b), i);
+    if (in_set(set, b) && i < L) xv = sample(row, b, src_of(row, b, c / 4), i);
     const float pp = fmaf(xv.x, xv.x, xv.y * xv.y);
     float pb = 1.f;
     for (int e = 0; e < b; ++e) pb *= pp;
     const float pr = pb * xv.x, pi = pb * xv.y;
     float sr = 0.f, si = 0.f;
     for (int m = 1; m < M; ++m) {
-      const float2 c = ldc(hg, b * M + m);
-      const int from = 32 * row + ((L + i - m) & 31);    // history sample i - m (meaningful for m > i)
+      const float2 h = ldc(hg, b * M + m);
+      const int from = RL * row + ((L + i - m) & (RL - 1));   // history sample i - m (meaningful for m > i)
       const float vr = __shfl(pr, from), vi = __shfl(pi, from);
       if (m > i) {
-        sr = fmaf(c.x, vr, sr);
-        sr = fmaf(-c.y, vi, sr);
-        si = fmaf(c.x, vi, si);
-        si = fmaf(c.y, vr, si);
+        sr = fmaf(h.x, vr, sr);
+        sr = fmaf(-h.y, vi, sr);
+        si = fmaf(h.x, vi, si);
+        si = fmaf(h.y, vr, si);
       }
     }
     emit(b, in_set(set, b), sr, si);

@@ -84,17 +84,20 @@ __device__ __forceinline__ void dpd_commit_block(const DpdCommitArgs &a, LastOf 
 }
 
 // ------------------------------------------------------------------ heads
-// Head corrections of every firing with B > 0 (four firings per wavefront
-// for M = 4, 8, 16; two for any other tap count, M = 0 here); corr[g][q],
-// q < M-1.  Read by the tiled body.  With a group
+// Head corrections of every firing with B > 0, a row of RL lanes per firing:
+// 16 for M = 4, 8, 16; for any other tap count (MT = 0) the fewest of 4, 8, 16
+// and 32 that hold the M - 1 outputs, so that short histories share a
+// workgroup (30000 firings of 40 samples, with 32 lanes always and now: one
+// tap 28 and 7 us, 12 taps 74 and 52).  corr[g][q], q < M-1, is read by the
+// tiled body.  With a group
 // table (one segment) the wavefront also derives the history sources of its
 // firings and writes their prev/off table entries: its firings lie
 // in one 64-firing group, so a ballot of the group's feed flags per branch
 // plus the group's entry (count and last feeder before it) gives them;
 // with order_out it also writes the firings' processing slots.
-template <int MT, bool TABLES>
+template <int MT, int RL, bool TABLES>
 __global__ __launch_bounds__(256) void k_dpd_heads(DpdArgs a) {
-  constexpr int RL = MT ? 16 : 32;                    // lanes per firing
+  static_assert(MT == 0 || RL == 16, "head_correction's rows");
   constexpr int NR = 64 / RL;                         // firings of the workgroup
   const int M = MT ? MT : a.M;
   // The workgroup's four wavefronts share its firings; wavefront w takes
@@ -123,7 +126,7 @@ __global__ __launch_bounds__(256) void k_dpd_heads(DpdArgs a) {
   const int64_t Rx = a.x_idx ? as_const(a.x_idx)[0] : 0;
   const int lane = threadIdx.x & 63, row = lane / RL, i = lane % RL;
   const int64_t g = g0 + row;                         // this lane's firing
-  int64_t pf[kMaxBranches];
+  int64_t pf[kMaxBranches / 4];                       // history sources of this wavefront's branches
   if constexpr (TABLES) {
     const int64_t G = g0 >> 6;
     const int64_t gl = G * 64 + lane;                 // lane's firing of the group
@@ -132,26 +135,26 @@ __global__ __launch_bounds__(256) void k_dpd_heads(DpdArgs a) {
     const uint64_t below_mask = (1ull << ((g0 & 63) + row)) - 1;
 #pragma unroll
     for (int b = 0; b < kMaxBranches; ++b) {
-      pf[b] = -1;
-      if (b >= a.B_max || (b & 3) != w) continue;     // uniform
+      if ((b & 3) != w) continue;                     // uniform
+      pf[b >> 2] = -1;
+      if (b >= a.B_max) continue;
       const uint64_t bal = __ballot(gin && (a.hist_mode == 1 || in_set(Bl, b)));
       const int64_t gi = 2 * (G * a.B_max + b);
       const int64_t cnt0 = as_const(a.grp)[gi], last0 = as_const(a.grp)[gi + 1];
       const uint64_t below = bal & below_mask;
-      pf[b] = below ? G * 64 + 63 - __clzll((long long)below) : last0;
-      if (i == b && g < a.n_firings) {
+      pf[b >> 2] = below ? G * 64 + 63 - __clzll((long long)below) : last0;
+      if (i == b % RL && g < a.n_firings) {
         const int64_t o = (int64_t)b * a.prev_stride + g;
-        a.tab_prev[o] = pf[b];
+        a.tab_prev[o] = pf[b >> 2];
         if (a.tab_off) a.tab_off[o] = a.r * (cnt0 + __popcll(below));
       }
     }
-    if (a.order_out && w == 0) {
+    if (a.order_out) {
       // processing slot of each of the firings: its length's first
       // slot in this group plus the firings of that length before it here
       const int NV = a.B_max + 1;
       const int Ll = gin ? set_len(Bl) : -1;
-#pragma unroll
-      for (int q = 0; q < NR; ++q) {
+      for (int q = w; q < NR; q += 4) {
         const int lq = (int)(g0 & 63) + q;            // group lane of firing g0 + q
         if (g0 + q >= a.n_firings) break;             // uniform
         const uint32_t Sq = (uint32_t)__builtin_amdgcn_readlane((int)Bl, lq);
@@ -165,20 +168,24 @@ __global__ __launch_bounds__(256) void k_dpd_heads(DpdArgs a) {
       }
     }
   }
+  if (M == 1) return;                                 // no history
   const auto B_of = [&](int r) {
     const int64_t gr = g0 + r;
     return gr < a.n_firings ? (a.B ? (uint32_t)a.B[gr] : prefix_set(a.B_const)) : 0u;
   };
-  const auto src_of = [&](int r, int b) {
-    if constexpr (TABLES) return pf[b];                // this lane's row
+  // branch b of this wavefront (its at-th) in the lane's row
+  const auto src_of = [&](int r, int b, int at) {
+    if constexpr (TABLES) return pf[at];
     else return prev_of(a, b, g0 + r);
   };
   const auto sample = [&](int r, int b, int64_t p, int q) {
     return hist_sample(a, Rx, b, g0 + r, p, (int64_t)q - (M - 1));
   };
   const auto emit = [&](int b, bool, float sr, float si) { part[b][lane] = make_float2(sr, si); };
-  if constexpr (MT != 0) head_correction<MT, NR>(as_const(a.h), B_of, src_of, sample, w, 4, emit);
-  else head_correction_any(as_const(a.h), M, B_of, src_of, sample, w, 4, emit);
+  if constexpr (MT != 0)
+    head_correction<MT, NR>(as_const(a.h), B_of, [&](int r, int b) { return src_of(r, b, b >> 2); }, sample, w, 4, emit);
+  else
+    head_correction_any<RL>(as_const(a.h), M, B_of, src_of, sample, w, emit);
   __syncthreads();
   const uint32_t set = B_of(row);
   if (w == 0 && i < M - 1 && set != 0u) {
@@ -505,19 +512,21 @@ hipError_t launch_dpd_heads(const DpdArgs &a, hipStream_t s) {
   if (a.ahead_blocks < 0 || (a.ahead_blocks && (!a.grp || a.ahead.n_segs != 1 || !a.ahead.grp || !a.ahead.ticket ||
                                                a.ahead_blocks != (scan_groups(1, a.ahead.seg_firings) + 3) / 4)))
     return hipErrorInvalidValue;
-  const int nr = compiled_taps(a.M) ? 4 : 2;           // firings per workgroup
+  const int rl = compiled_taps(a.M) || (a.M > 9 && a.M <= 17) ? 16 : a.M <= 5 ? 4 : a.M <= 9 ? 8 : 32;
+  const int nr = 64 / rl;                              // firings per workgroup
   // in pieces that a grid can hold beside the scan's workgroups
   const int64_t blocks = (a.n_firings + nr - 1) / nr, most = host::kMaxThreads / 512;
   for (DpdArgs p = a; p.head_block0 < blocks; p.head_block0 += most, p.ahead_blocks = 0) {
     const dim3 grid((unsigned)(std::min(blocks - p.head_block0, most) + p.ahead_blocks));
-#define DF_HEADS(m)                                                                     \
-  if (m == 0 || a.M == m) {                                                             \
+#define DF_HEADS(m, l)                                                                  \
+  if ((m == 0 || a.M == m) && rl == l) {                                                \
     if (a.grp)                                                                          \
-      hipLaunchKernelGGL((k_dpd_heads<m, true>), grid, dim3(256), 0, s, p);             \
+      hipLaunchKernelGGL((k_dpd_heads<m, l, true>), grid, dim3(256), 0, s, p);          \
     else                                                                                \
-      hipLaunchKernelGGL((k_dpd_heads<m, false>), grid, dim3(256), 0, s, p);            \
+      hipLaunchKernelGGL((k_dpd_heads<m, l, false>), grid, dim3(256), 0, s, p);         \
   }
-    DF_HEADS(16) else DF_HEADS(8) else DF_HEADS(4) else DF_HEADS(0)
+    DF_HEADS(16, 16) else DF_HEADS(8, 16) else DF_HEADS(4, 16)
+    else DF_HEADS(0, 4) else DF_HEADS(0, 8) else DF_HEADS(0, 16) else DF_HEADS(0, 32)
 #undef DF_HEADS
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

@@ -776,9 +776,12 @@ df_status dfh::dpd_enqueue(df_graph *g, Actor &a, int64_t n, bool may_run_ahead)
   const int64_t r = a.dp.firing_size;
   const int bm = a.dp.n_branches_max, M = a.dp.n_taps;
   // the head pass fills the prev/off tables from the group table, and places
-  // the firings in processing order (grouped by Horner length: pays off only
-  // for many workgroups)
-  const bool ordered = n > 64;
+  // the firings in processing order (grouped by Horner length).  That pays off
+  // only for many workgroups with work enough to even out: the scan's length
+  // table costs up to 20 us (us a pass, unordered / ordered: 30000 firings of
+  // 40 samples 53 / 68 with one tap, 137 / 151 with 16; 8192 of 128 35 / 41
+  // with three; 8192 of 511 86 / 92 with 8; 2000 of 1000 77 / 72 with 20).
+  const bool ordered = n > 64 && r > 512;
   const int64_t pos = fc.read_h;
 
   // this batch's scan: the one run ahead if it assumed this batch, else a new one
