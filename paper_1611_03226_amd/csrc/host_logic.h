@@ -113,5 +113,40 @@ inline TileShape tile_shape(int64_t n_firings, int64_t r, bool mx, int tile, int
   return TileShape{K, tl};
 }
 
+// Frame actors: words per strip of the word path (4 or 1), or 0 for the byte
+// path, by frame size, batch and actor (Gauss, else Med).  A strip of four
+// words is a wavefront's lane and walks kStripRows rows one after the other:
+// 12 us however little there is (one word 8, bytes 4), 3.7 ns more per
+// wavefront, idle lanes included, but least per pixel where the wavefronts are
+// full.  Bytes take 1.15 ns per 256 pixels (Gauss; Med 0.55).  us of Gauss and
+// Med, four words / the other path:
+//   width not a multiple of 4, bytes:
+//     333x251  6 frames 14 14 /  6  5    24  13 13 / 13  7    120   15 16 / 48 25
+//     65x48  481        17 16 / 11  7   962  13 14 / 19 11   3205   26 23 / 51 30
+//     33x17 1783        18 17 /  9  5  17825 79 80 / 52 29
+//   a multiple of 4, one word:
+//     1000x600 17       15 19 / 12 13    33  17 20 / 19 17     67   29 24 / 38 29
+//     100x75 1333       20 19 / 17  9  13333 191 112 / 195 93
+//     20x20 25000      105 106 / 47 42
+// Multiples of 16 take four words at any size.
+constexpr int kStripRows = 16;
+
+inline int64_t strip_lanes(int64_t W, int64_t H, int V) {
+  return (H + kStripRows - 1) / kStripRows * ((W + 4 * V - 1) / (4 * V));
+}
+
+inline int strip_words(int64_t W, int64_t H, int64_t n_frames, bool gauss) {
+  if (W % 16 == 0) return 4;
+  const int other = W % 4 == 0 ? 1 : 0;
+  if (W < 20) return other;                  // no room for the word left of the last strip
+  const int64_t lanes = strip_lanes(W, H, 4), waves = (lanes + 63) / 64;
+  if (other) {
+    const bool full = 4 * lanes >= 3 * 64 * waves;
+    return full && n_frames * W * H >= (gauss ? 20000000 : 32000000) ? 4 : 1;
+  }
+  const int64_t blocks = (W * H + 255) / 256;
+  return n_frames * blocks * (gauss ? 1150 : 550) > 8500000 + n_frames * waves * 3700 ? 4 : 0;   // picoseconds
+}
+
 }  // namespace host
 }  // namespace dfh

@@ -4,24 +4,24 @@
 // threshold) and Med (5-pixel median).  Each batch covers n_frames
 // consecutive tokens of the actor's channels; see MdpArgs.
 //
-// Word path (any width from 20 on, and 4, 8, 12, 16): a work item is a strip
-// of V words (4V pixels; V = 1 below width 16, else 4) of kRun consecutive
-// output rows of one frame; consecutive lanes take consecutive strips, so
-// every row load of a wave is one contiguous run.  The last strip of a row
-// ends at the row's last pixel and may overlap its neighbour (whose pixels it
+// Word path (host::strip_words: multiples of 4, and any width from 20 on where
+// a batch is large enough): a work item is a strip of V words (4V pixels; V = 4
+// or 1) of kRun consecutive output rows of one frame; consecutive lanes take
+// consecutive strips, so every row load of a wave is one contiguous run.  The
+// last strip of a row ends at the row's last pixel and may overlap its neighbour (whose pixels it
 // rewrites with the same values); rows start at any byte, which the loads and
 // stores of words allow.  The vertical window slides down the item in
 // registers; the words left and right of the strip give the horizontal halo,
 // with the nearest in-frame pixel repeated at the left and right frame edges.
-// Pixels are processed four per word in 16-bit lanes (md_swar.h).  Any other
-// width takes the byte path: one thread per pixel (64 frames of 854x480:
-// Gauss 121 us and Med 73 us by bytes, 22 and 21 us by strips;
+// Pixels are processed four per word in 16-bit lanes (md_swar.h).  The rest takes
+// the byte path: one thread per pixel (64 frames of 854x480: Gauss 121 us and Med 73 us by bytes, 22 and 21 us by strips;
 // 128 frames of 1000x600: 70 and 52 us with one word per strip, 60 and 45 with
 // four).
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
 #include "common.h"
+#include "host_logic.h"
 #include "md_swar.h"
 
 namespace dfh {
@@ -29,7 +29,7 @@ namespace {
 
 constexpr int kMdThreads = 256;
 constexpr int kWordThreads = 64;           // word-path workgroup: one wave, little padding per frame
-constexpr int kRun = 16;                   // output rows per word-path work item
+constexpr int kRun = host::kStripRows;     // output rows per word-path work item
 constexpr int64_t kMaxBlocks = 1 << 23;    // per launch: threads stay below 2^31
 
 // Frame f of the batch in an input channel (from its read counter) or an
@@ -90,7 +90,7 @@ struct Strip {
   int avail;                                // pixels of the row right of the strip
   __device__ Strip(int s, int W) {
     x0 = (uint32_t)min(4 * V * s, W - 4 * V);
-    left_edge = x0 == 0;                    // else x0 >= 4 (see word_path)
+    left_edge = x0 == 0;                    // else x0 >= 4 (see host::strip_words)
     avail = W - (int)x0 - 4 * V;
     xl = left_edge ? 0 : x0 - 4;
     xr = avail ? (uint32_t)min((int)x0 + 4 * V, W - 4) : x0 + 4 * V - 4;
@@ -553,18 +553,10 @@ __global__ void k_advance_n(Counters c, int n, int32_t *err) {
 
 namespace {
 
-// Words per strip of the word path, or 0: the byte path.  With four words the
-// last strip starts at pixel W - 16, which must be 0 or leave room for the
-// word on its left (W >= 20).
-int word_path(int32_t W) {
-  if (W >= 20 || W == 16) return 4;
-  return W % 4 == 0 ? 1 : 0;
-}
-
 template <int V>
 hipError_t launch_gauss5_words(const MdpArgs &a, hipStream_t s, const KTiming *t) {
   const int32_t n_runs = div_up32(a.H, kRun);
-  const int32_t bpf = div_up32((int64_t)n_runs * div_up32(a.W, 4 * V), kWordThreads);
+  const int32_t bpf = div_up32(host::strip_lanes(a.W, a.H, V), kWordThreads);
   const bool full = a.H >= kRun;
   if (a.out1)
     return full ? launch_frames(k_gauss5_w<V, true, true>, kWordThreads, a, bpf, s, t, n_runs)
@@ -576,7 +568,7 @@ hipError_t launch_gauss5_words(const MdpArgs &a, hipStream_t s, const KTiming *t
 template <int V>
 hipError_t launch_med5_words(const MdpArgs &a, hipStream_t s, const KTiming *t) {
   const int32_t n_runs = div_up32(a.H, kRun);
-  const int32_t bpf = div_up32((int64_t)n_runs * div_up32(a.W, 4 * V), kWordThreads);
+  const int32_t bpf = div_up32(host::strip_lanes(a.W, a.H, V), kWordThreads);
   return a.H >= kRun ? launch_frames(k_med5_w<V, true>, kWordThreads, a, bpf, s, t, n_runs)
                      : launch_frames(k_med5_w<V, false>, kWordThreads, a, bpf, s, t, n_runs);
 }
@@ -585,8 +577,9 @@ hipError_t launch_med5_words(const MdpArgs &a, hipStream_t s, const KTiming *t) 
 
 hipError_t launch_gauss5(const MdpArgs &a, hipStream_t s, const KTiming *t) {
   if (a.n_frames <= 0) return hipSuccess;
-  if (word_path(a.W) == 4) return launch_gauss5_words<4>(a, s, t);
-  if (word_path(a.W) == 1) return launch_gauss5_words<1>(a, s, t);
+  const int V = host::strip_words(a.W, a.H, a.n_frames, true);
+  if (V == 4) return launch_gauss5_words<4>(a, s, t);
+  if (V == 1) return launch_gauss5_words<1>(a, s, t);
   return launch_frames(k_gauss5_b, kMdThreads, a, div_up32((int64_t)a.W * a.H, kMdThreads), s, t);
 }
 
@@ -599,8 +592,9 @@ hipError_t launch_thres(const MdpArgs &a, hipStream_t s, const KTiming *t) {
 
 hipError_t launch_med5(const MdpArgs &a, hipStream_t s, const KTiming *t) {
   if (a.n_frames <= 0) return hipSuccess;
-  if (word_path(a.W) == 4) return launch_med5_words<4>(a, s, t);
-  if (word_path(a.W) == 1) return launch_med5_words<1>(a, s, t);
+  const int V = host::strip_words(a.W, a.H, a.n_frames, false);
+  if (V == 4) return launch_med5_words<4>(a, s, t);
+  if (V == 1) return launch_med5_words<1>(a, s, t);
   return launch_frames(k_med5_b, kMdThreads, a, div_up32((int64_t)a.W * a.H, kMdThreads), s, t);
 }
 

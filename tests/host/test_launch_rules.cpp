@@ -57,7 +57,31 @@ static void tiles() {
   CHECK(tile_shape(4096, 4096, false, 0, 0).tile == 2048 && tile_shape(4096, 4096, true, 0, 0).tile == 1024);
 }
 
+// Frame strips: four words only where the last strip has room for the word
+// on its left, small batches of other widths never, large ones of large
+// frames always, and never back to the other path as a batch grows.
+static void strips() {
+  for (int64_t W = 1; W <= 2000; ++W)
+    for (int64_t H : {1, 16, 40, 251, 1080})
+      for (int gauss = 0; gauss < 2; ++gauss) {
+        const int few = strip_words(W, H, 1, gauss);
+        CHECK(few == 4 || few == (W % 4 == 0 ? 1 : 0));
+        CHECK(W % 16 != 0 || few == 4);
+        bool four = false;
+        for (int64_t n = 1; n <= 1ll << 34; n *= 4) {
+          const int v = strip_words(W, H, n, gauss);
+          CHECK(v == few || (v == 4 && W >= 20));
+          CHECK(!four || v == 4);
+          four = v == 4;
+        }
+        CHECK(four || W < 200 || H < 200);
+      }
+  CHECK(strip_words(854, 480, 64, true) == 4 && strip_words(854, 480, 64, false) == 4);
+  CHECK(strip_words(333, 251, 4, true) == 0 && strip_words(20, 20, 1000, true) == 1);
+}
+
 int main() {
+  strips();
   tiles();
   motion();
   scan_rows();
