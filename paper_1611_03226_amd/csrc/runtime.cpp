@@ -1254,26 +1254,33 @@ extern "C" df_status df_stream_dpd(df_graph *g, int32_t actor, const void *x_hos
   // the batch whose slots a write of positions up to `last` reuses: the one
   // holding position last - cap, if any (batches start at `base`, n apart)
   const auto reused = host::reused_batch;
-  // The copy streams carry the samples only; every counter update and the
-  // control tokens' copy run on the graph stream.  The runtime copies a few
-  // KB, and a batch's output, with kernels, and the two copy streams may
-  // share a hardware queue: with the control tokens on copy_in, the input of
-  // batch k+1 stood behind the output of batch k, and the two directions of
-  // the link took turns (4 batches of 2^20 samples: 1233 us, now 1129; two
-  // other graphs' streams beside it 1072, now 1021.  A batch takes 153 us in
-  // one direction alone, 190 in both at once; feeding a batch earlier, waits
-  // on the host and more streams gave 1240 to 1270, 1220 to 1290, 1130 to
-  // 1470 us).
+  // Every counter update runs on the graph stream, after the copy it accounts
+  // for (a kernel on a copy stream would share a hardware queue with the
+  // firings and serialise them).  The control tokens' copy too, up to 16 KiB:
+  // the runtime copies that little, and a batch's output, with kernels, and the
+  // two copy streams may share a hardware queue: on copy_in the input of batch
+  // k+1 stood behind the output of batch k, and the two directions of the link
+  // took turns.  More than that is copied by a DMA engine, and the graph stream
+  // would wait for it between two firings.  us for four batches of 2^20 samples
+  // with the tokens on the graph stream / on copy_in: 256 firings a batch 1021
+  // / 1072, 4096 1015 / 1090, 8192 1215 / 1123, 16384 1320 / 1140.  (A batch
+  // takes 153 us in one direction alone, 190 in both at once; feeding a batch
+  // earlier, waits on the host and more streams gave 1240 to 1270, 1220 to
+  // 1290, 1130 to 1470 us.)
+  const bool ctrl_on_copy_in = nb * (int64_t)sizeof(int32_t) > (16 << 10);
   int64_t y_drained = 0;          // batches whose output-copy has been accounted on the graph stream
   for (int64_t k = 0; k < n_batches; ++k) {
     // input: samples of batch k, and its control tokens behind the firings
     // that read their slots before
     int64_t j = reused(x_write0 + (k + 1) * ns - 1, fx.cap, x_read0, ns);
+    if (ctrl_on_copy_in) j = std::max(j, reused(fc.write_hi + nb - 1, fc.cap, fc.read_h - k * nb, nb));
     if (j >= k) return fail(g, DF_EINVAL, "channel too small for two batches");
     if (j >= 0) HIPCHK(g, hipStreamWaitEvent(g->copy_in, ev_fired[j], 0));
+    void *tokens = (void *)(ch + k * nb * sizeof(int32_t));
+    if (ctrl_on_copy_in) HIPCHK(g, ring_copy(g, fc, fc.write_hi, tokens, nb, true, false, g->copy_in));
     HIPCHK(g, ring_copy(g, fx, fx.write_hi, (void *)(xh + k * ns * fx.token_bytes), ns, true, false, g->copy_in));
     HIPCHK(g, hipEventRecord(ev_in[k], g->copy_in));
-    HIPCHK(g, ring_copy(g, fc, fc.write_hi, (void *)(ch + k * nb * sizeof(int32_t)), nb, true, false));
+    if (!ctrl_on_copy_in) HIPCHK(g, ring_copy(g, fc, fc.write_hi, tokens, nb, true, false));
     fc.write_lo += nb;
     fc.write_hi += nb;
     fx.write_lo += ns;
