@@ -283,15 +283,23 @@ hipError_t launch_adj(const AdjArgs &a, hipStream_t s) {
 
 // ------------------------------------------------------------------ amplifier model
 //
-// Forward with loss and input adjoint of the memory polynomial.  A workgroup
-// takes a run of one row, a thread four consecutive samples of it: with four
-// orders and four taps (the model in use) the thread's window sits in
-// registers, the sixteen coefficients in scalar registers, and everything
-// moves in 16-byte accesses; other sizes, and the samples whose taps cross
-// the row's end, go sample by sample.  HBM-bound at 2^22 samples: the loss
-// reads u and x and writes e (100 MB, 22 us), the adjoint reads u and g and
-// writes Gu (100 MB, 22 us, 32 us with a thread per sample that reloaded
-// its coefficients and formed the powers per tap).
+// Forward with loss and input adjoint of the memory polynomial, in two forms.
+// Runs: a workgroup takes a run of one row, a thread four consecutive samples
+// of it: with four orders and four taps (the model in use) the thread's window
+// sits in registers, the sixteen coefficients in scalar registers, and
+// everything moves in 16-byte accesses; samples whose taps cross the row's end
+// go sample by sample.  HBM-bound at 2^22 samples: the loss reads u and x and
+// writes e (100 MB, 22 us), the adjoint reads u and g and writes Gu (100 MB, 20
+// us, 32 us with a thread per sample that reloaded its coefficients and formed
+// the powers per tap).
+// Sample-wise, for any orders and taps and any rows: consecutive lanes take
+// consecutive samples of the batch, so every access of a tap is one contiguous
+// run, and a thread's U samples share the coefficients' scalar loads.  Bound by
+// VALU and the scalar loads' latency, so U grows with the batch.  us of the
+// adjoint with four consecutive samples a thread / a sample a thread / now, and
+// of the loss with four consecutive / now: 5 orders, 4 taps, 2^22 samples 56 /
+// 37 / 27, 61 / 31; 8 orders, 16 taps 160 / 151 / 98, 164 / 78; 20000 rows of
+// 40 samples, 4 and 4 29 / 8.7 / 6.9, 53 / 11.
 typedef float f4_any __attribute__((ext_vector_type(4), aligned(8)));
 
 __device__ __forceinline__ void load4(const float2 *p, float2 (&v)[4]) {
@@ -306,16 +314,30 @@ __device__ __forceinline__ void store4(float2 *p, const float2 (&v)[4]) {
 }
 
 // Tap q's polynomial at p: P = sum_k a[k][q] p^k, and with DERIV its
-// derivative D = sum_{k>=1} k a[k][q] p^(k-1) (Horner for both).
-template <bool DERIV>
-__device__ __forceinline__ void tap_poly(cfloat2p a, int K, int Q, int q, float p, float2 &P, float2 &D) {
-  P = ldc(a, (K - 1) * Q + q);
-  D = make_float2(0.f, 0.f);
+// derivative D = sum_{k>=1} k a[k][q] p^(k-1) (Horner for both), for U values
+// of p at once (the coefficients are the same).
+template <bool DERIV, int U>
+__device__ __forceinline__ void tap_polys(cfloat2p a, int K, int Q, int q, const float (&p)[U], float2 (&P)[U],
+                                          float2 (&D)[U]) {
+  const float2 top = ldc(a, (K - 1) * Q + q);
+#pragma unroll
+  for (int u = 0; u < U; ++u) P[u] = top, D[u] = make_float2(0.f, 0.f);
   for (int k = K - 2; k >= 0; --k) {
     const float2 c = ldc(a, k * Q + q);
-    if (DERIV) D = make_float2(fmaf(D.x, p, P.x), fmaf(D.y, p, P.y));
-    P = make_float2(fmaf(P.x, p, c.x), fmaf(P.y, p, c.y));
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (DERIV) D[u] = make_float2(fmaf(D[u].x, p[u], P[u].x), fmaf(D[u].y, p[u], P[u].y));
+      P[u] = make_float2(fmaf(P[u].x, p[u], c.x), fmaf(P[u].y, p[u], c.y));
+    }
   }
+}
+
+template <bool DERIV>
+__device__ __forceinline__ void tap_poly(cfloat2p a, int K, int Q, int q, float p, float2 &P, float2 &D) {
+  const float pp[1] = {p};
+  float2 Pp[1], Dp[1];
+  tap_polys<DERIV, 1>(a, K, Q, q, pp, Pp, Dp);
+  P = Pp[0], D = Dp[0];
 }
 
 __device__ __forceinline__ float norm2(float2 v) { return fmaf(v.x, v.x, v.y * v.y); }
@@ -362,22 +384,33 @@ __device__ __forceinline__ float2 mp_adjoint(float2 uv, const float2 *g, cfloat2
   return G;
 }
 
-// Runs of 4 * blockDim samples: run i is run i % runs_per_row of row
+// The workgroup's sum of every thread's `sum`, in a fixed order.
+__device__ __forceinline__ void block_sum(double sum, double (&ws)[4], double *out) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+  if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = sum;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < (int)(blockDim.x >> 6); ++w) sum += ws[w];
+    out[blockIdx.x] = sum;
+  }
+}
+
+// Runs of 1024 samples: run i is run i % runs_per_row of row
 // i / runs_per_row; workgroups stride over them.
 // k_mp_loss: e = v - x (stored when e is given) and per workgroup the sum of
 // |e|^2 (each thread's in fp32 over its four samples, the rest in fp64).
-template <bool FOUR>
 __global__ __launch_bounds__(256) void k_mp_loss(MpArgs m, int64_t runs, int64_t runs_per_row) {
   __shared__ double ws[4];
   const cfloat2p a = as_const(m.a);
   double sum = 0.0;
   for (int64_t i = blockIdx.x; i < runs; i += gridDim.x) {
     const int64_t row = i / runs_per_row;
-    const int64_t n0 = ((i - row * runs_per_row) * blockDim.x + threadIdx.x) * 4;
+    const int64_t n0 = ((i - row * runs_per_row) * 256 + threadIdx.x) * 4;
     const float2 *u = m.u + row * m.len, *x = m.x + row * m.len;
     float2 *e = m.out ? m.out + row * m.len : nullptr;
     float part = 0.f;
-    if (FOUR && n0 >= 4 && n0 + 4 <= m.len) {
+    if (n0 >= 4 && n0 + 4 <= m.len) {
       float2 h[4], c[4], w[7], xv[4];
       load4(u + n0 - 4, h);
       load4(u + n0, c);
@@ -403,7 +436,7 @@ __global__ __launch_bounds__(256) void k_mp_loss(MpArgs m, int64_t runs, int64_t
       for (int k = 0; k < 4; ++k) part = fmaf(v[k].x, v[k].x, fmaf(v[k].y, v[k].y, part));
     } else {
       for (int64_t n = n0; n < n0 + 4 && n < m.len; ++n) {
-        float2 v = mp_value(u, a, n, m.K, m.Q);
+        float2 v = mp_value(u, a, n, 4, 4);
         v = make_float2(v.x - x[n].x, v.y - x[n].y);
         if (e) e[n] = v;
         part = fmaf(v.x, v.x, fmaf(v.y, v.y, part));
@@ -411,13 +444,89 @@ __global__ __launch_bounds__(256) void k_mp_loss(MpArgs m, int64_t runs, int64_t
     }
     sum += (double)part;
   }
+  block_sum(sum, ws, m.partial);
+}
+
+// Samples left in t's row from t on (1 for the row's last), 0 past the batch.
+__device__ __forceinline__ int64_t row_left(int64_t t, int64_t len, int64_t total) {
+  if (t >= total) return 0;
+  const int64_t row = total >> 32 ? t / len : (int64_t)((uint32_t)t / (uint32_t)len);
+  return len - (t - row * len);
+}
+
+// Sample-wise forms: the batch's samples in one sequence, U per thread and 256
+// apart.
+template <bool FOUR, int U>
+__global__ __launch_bounds__(256) void k_mp_loss_any(MpArgs m) {
+  __shared__ double ws[4];
+  const cfloat2p a = as_const(m.a);
+  const int K = FOUR ? 4 : m.K, Q = FOUR ? 4 : m.Q;
+  const int64_t total = m.S * m.len;
+  double sum = 0.0;
+  for (int64_t t0 = (int64_t)blockIdx.x * (256 * U) + threadIdx.x; t0 < total; t0 += (int64_t)gridDim.x * (256 * U)) {
+    int64_t n[U];                                        // the sample's place in its row, -1 past the batch
+    float2 v[U], w[U], P[U], D[U];
+    float p[U];
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
-  if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = sum;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int w = 1; w < (int)(blockDim.x >> 6); ++w) sum += ws[w];
-    m.partial[blockIdx.x] = sum;
+    for (int u = 0; u < U; ++u) {
+      const int64_t left = row_left(t0 + 256 * u, m.len, total);
+      n[u] = left ? m.len - left : -1;
+      v[u] = make_float2(0.f, 0.f);
+    }
+    for (int q = 0; q < Q; ++q) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        w[u] = q <= n[u] ? m.u[t0 + 256 * u - q] : make_float2(0.f, 0.f);
+        p[u] = norm2(w[u]);
+      }
+      tap_polys<false, U>(a, K, Q, q, p, P, D);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (q <= n[u]) add_product(v[u], w[u], P[u]);
+    }
+    float part = 0.f;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t t = t0 + 256 * u;
+      if (n[u] < 0) continue;
+      const float2 xv = m.x[t];
+      v[u] = make_float2(v[u].x - xv.x, v[u].y - xv.y);
+      if (m.out) m.out[t] = v[u];
+      part = fmaf(v[u].x, v[u].x, fmaf(v[u].y, v[u].y, part));
+    }
+    sum += (double)part;
+  }
+  block_sum(sum, ws, m.partial);
+}
+
+template <bool FOUR, int U>
+__global__ __launch_bounds__(256) void k_mp_adj_any(MpArgs m) {
+  const cfloat2p a = as_const(m.a);
+  const int K = FOUR ? 4 : m.K, Q = FOUR ? 4 : m.Q;
+  const float sc = m.scale ? 2.f * m.scale[0] : 1.f;
+  const int64_t total = m.S * m.len;
+  for (int64_t t0 = (int64_t)blockIdx.x * (256 * U) + threadIdx.x; t0 < total; t0 += (int64_t)gridDim.x * (256 * U)) {
+    int64_t left[U];
+    float2 uv[U], G[U], g[U], P[U], D[U];
+    float p[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      left[u] = row_left(t0 + 256 * u, m.len, total);
+      uv[u] = left[u] ? m.u[t0 + 256 * u] : make_float2(0.f, 0.f);
+      p[u] = norm2(uv[u]);
+      G[u] = make_float2(0.f, 0.f);
+    }
+    for (int q = 0; q < Q; ++q) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) g[u] = q < left[u] ? m.x[t0 + 256 * u + q] : make_float2(0.f, 0.f);
+      tap_polys<true, U>(a, K, Q, q, p, P, D);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (q < left[u]) add_adjoint(G[u], g[u], P[u], D[u], p[u], square(uv[u]));
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (left[u]) m.out[t0 + 256 * u] = make_float2(sc * G[u].x, sc * G[u].y);
   }
 }
 
@@ -434,16 +543,15 @@ __global__ __launch_bounds__(256) void k_mp_loss_sum(const double *partial, int 
 }
 
 // Gu from u and the upstream gradient g, or (m.scale) 2 * scale[0] * g.
-template <bool FOUR>
 __global__ __launch_bounds__(256) void k_mp_adj(MpArgs m, int64_t runs, int64_t runs_per_row) {
   const cfloat2p a = as_const(m.a);
   const float sc = m.scale ? 2.f * m.scale[0] : 1.f;
   for (int64_t i = blockIdx.x; i < runs; i += gridDim.x) {
     const int64_t row = i / runs_per_row;
-    const int64_t n0 = ((i - row * runs_per_row) * blockDim.x + threadIdx.x) * 4;
+    const int64_t n0 = ((i - row * runs_per_row) * 256 + threadIdx.x) * 4;
     const float2 *u = m.u + row * m.len, *g = m.x + row * m.len;
     float2 *out = m.out + row * m.len;
-    if (FOUR && n0 + 8 <= m.len) {
+    if (n0 + 8 <= m.len) {
       float2 uv[4], g0[4], g1[4], G[4], P, D;
       load4(u + n0, uv);
       load4(g + n0, g0);
@@ -463,7 +571,7 @@ __global__ __launch_bounds__(256) void k_mp_adj(MpArgs m, int64_t runs, int64_t 
       store4(out + n0, G);
     } else {
       for (int64_t n = n0; n < n0 + 4 && n < m.len; ++n) {
-        const float2 G = mp_adjoint(u[n], g, a, n, m.len, m.K, m.Q);
+        const float2 G = mp_adjoint(u[n], g, a, n, m.len, 4, 4);
         out[n] = make_float2(sc * G.x, sc * G.y);
       }
     }
@@ -473,17 +581,24 @@ __global__ __launch_bounds__(256) void k_mp_adj(MpArgs m, int64_t runs, int64_t 
 namespace {
 
 struct MpGrid {
-  int threads;
   int64_t runs, runs_per_row;
 };
 
 MpGrid mp_grid(const MpArgs &m) {
-  const int64_t t = (m.len + 3) / 4;                     // threads a row needs
-  MpGrid g;
-  g.threads = (int)std::min<int64_t>(256, (t + 63) / 64 * 64);
-  g.runs_per_row = (t + g.threads - 1) / g.threads;
-  g.runs = m.S * g.runs_per_row;
-  return g;
+  const int64_t per_row = (m.len + 1023) / 1024;
+  return {m.S * per_row, per_row};
+}
+
+// The runs form needs the model in use, rows that fill its workgroups, and
+// enough of them to fill the chip (us of adjoint and loss, runs / sample-wise:
+// 64 rows of 65536 19 24 / 23 27, 32 rows 11 15 / 14 17, 16 rows 7.6 11 / 7.4
+// 11; 1024 of 4096 20 23 / 22 26, 3000 of 1000 18 21 / 18 21).
+bool mp_runs(const MpArgs &m) {
+  return m.K == 4 && m.Q == 4 && m.len >= 4096 && m.S * m.len >= (1 << 21);
+}
+
+unsigned mp_blocks(const MpArgs &m, int U, int64_t most) {
+  return (unsigned)std::min<int64_t>((m.S * m.len + 256 * U - 1) / (256 * U), most);
 }
 
 }  // namespace
@@ -491,12 +606,20 @@ MpGrid mp_grid(const MpArgs &m) {
 hipError_t launch_mp_loss(const MpArgs &m, float *loss, hipStream_t s) {
   int blocks = 0;
   if (m.S > 0 && m.len > 0) {
-    const MpGrid g = mp_grid(m);
-    blocks = (int)std::min<int64_t>(g.runs, kMpLossBlocks);
-    if (m.K == 4 && m.Q == 4)
-      hipLaunchKernelGGL(k_mp_loss<true>, dim3(blocks), dim3(g.threads), 0, s, m, g.runs, g.runs_per_row);
-    else
-      hipLaunchKernelGGL(k_mp_loss<false>, dim3(blocks), dim3(g.threads), 0, s, m, g.runs, g.runs_per_row);
+    const bool four = m.K == 4 && m.Q == 4;
+    const int U = !four && m.S * m.len >= (1 << 19) ? 4 : 1;
+    blocks = (int)mp_blocks(m, U, kMpLossBlocks);
+    if (mp_runs(m)) {
+      const MpGrid g = mp_grid(m);
+      blocks = (int)std::min<int64_t>(g.runs, kMpLossBlocks);
+      hipLaunchKernelGGL(k_mp_loss, dim3(blocks), dim3(256), 0, s, m, g.runs, g.runs_per_row);
+    } else if (four) {
+      hipLaunchKernelGGL((k_mp_loss_any<true, 1>), dim3(blocks), dim3(256), 0, s, m);
+    } else if (U == 4) {
+      hipLaunchKernelGGL((k_mp_loss_any<false, 4>), dim3(blocks), dim3(256), 0, s, m);
+    } else {
+      hipLaunchKernelGGL((k_mp_loss_any<false, 1>), dim3(blocks), dim3(256), 0, s, m);
+    }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -506,12 +629,20 @@ hipError_t launch_mp_loss(const MpArgs &m, float *loss, hipStream_t s) {
 
 hipError_t launch_mp_adj(const MpArgs &m, hipStream_t s) {
   if (m.S <= 0 || m.len <= 0) return hipSuccess;
-  const MpGrid g = mp_grid(m);
-  const unsigned blocks = (unsigned)std::min<int64_t>(g.runs, 1 << 20);
-  if (m.K == 4 && m.Q == 4)
-    hipLaunchKernelGGL(k_mp_adj<true>, dim3(blocks), dim3(g.threads), 0, s, m, g.runs, g.runs_per_row);
-  else
-    hipLaunchKernelGGL(k_mp_adj<false>, dim3(blocks), dim3(g.threads), 0, s, m, g.runs, g.runs_per_row);
+  const bool four = m.K == 4 && m.Q == 4;
+  const int U = m.S * m.len >= (1 << 19) ? 2 : 1;
+  const dim3 grid(mp_blocks(m, U, 1 << 20));
+  if (mp_runs(m)) {
+    const MpGrid g = mp_grid(m);
+    const unsigned blocks = (unsigned)std::min<int64_t>(g.runs, 1 << 20);
+    hipLaunchKernelGGL(k_mp_adj, dim3(blocks), dim3(256), 0, s, m, g.runs, g.runs_per_row);
+  } else if (four) {
+    if (U == 2) hipLaunchKernelGGL((k_mp_adj_any<true, 2>), grid, dim3(256), 0, s, m);
+    else hipLaunchKernelGGL((k_mp_adj_any<true, 1>), grid, dim3(256), 0, s, m);
+  } else {
+    if (U == 2) hipLaunchKernelGGL((k_mp_adj_any<false, 2>), grid, dim3(256), 0, s, m);
+    else hipLaunchKernelGGL((k_mp_adj_any<false, 1>), grid, dim3(256), 0, s, m);
+  }
   return hipGetLastError();
 }
 

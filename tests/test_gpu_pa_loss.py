@@ -126,3 +126,34 @@ def test_adaptation_loss_with_a_variable_amplifier(h_grad):
     assert loss.item() == ref.item()
     if h_grad:
         assert (h.grad - hr.grad).norm() == 0
+
+
+@pytest.mark.parametrize("K,Q,S,L", [(4, 4, 1, 1 << 21), (4, 4, 512, 4099), (4, 4, 3, 200003), (4, 4, 9000, 61),
+                                     (5, 4, 2, 300001), (3, 7, 20001, 31), (8, 16, 7, 80001), (1, 1, 1, 600000)])
+def test_large_batches(K, Q, S, L):
+    """Batches large enough for the forms with several samples per thread: the
+    run form's rows at and off a run's length, the sample-wise forms with rows
+    that end anywhere in a thread's samples."""
+    import torch
+    from paper_1611_03226_amd import dfhip as D
+    say(f"pa loss large K={K} Q={Q} {S}x{L}")
+    rng = np.random.default_rng(K * 1000 + Q * 100 + S)
+    a = pa_coeffs(rng, K, Q, sigma=0.1)
+    u, x, g = (complex_gaussian(rng, (S, L), rms=0.7) for _ in range(3))
+    ref = opa.pa_forward(u, a) - x
+    e, Gp = (torch.zeros(S, L, dtype=torch.complex64, device="cuda") for _ in range(2))
+    loss = torch.zeros((), device="cuda")
+    work = torch.empty(D.df_mp_loss_work_bytes(), dtype=torch.uint8, device="cuda")
+    du, da, dx, dg = _t(u), _t(a), _t(x), _t(g)
+    D.df_mp_loss(du, da, dx, e, loss, work)
+    D.df_mp_input_adjoint(du, da, dg, Gp)
+    torch.cuda.synchronize()
+    scale = np.sqrt(np.mean(np.abs(ref) ** 2))
+    assert np.abs(e.cpu().numpy() - ref).max() <= TOL * (scale + np.abs(ref).max())
+    want = float(np.sum(np.abs(ref) ** 2))
+    assert abs(loss.item() - want) <= TOL * want
+    r = opa.pa_input_vjp(u, a, g)
+    err = np.abs(Gp.cpu().numpy() - r)
+    assert np.linalg.norm(err) <= TOL * np.linalg.norm(r)
+    D.df_mp_input_adjoint(du, da, dg, du)                # in place of u, as a caller may
+    assert torch.equal(du, Gp)
