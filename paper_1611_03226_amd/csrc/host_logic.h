@@ -5,7 +5,12 @@
 // build it under AddressSanitizer / UndefinedBehaviorSanitizer.
 #pragma once
 
+#include <stddef.h>
 #include <stdint.h>
+
+#include <map>
+#include <mutex>
+#include <tuple>
 
 namespace dfh {
 namespace host {
@@ -147,6 +152,27 @@ inline int strip_words(int64_t W, int64_t H, int64_t n_frames, bool gauss) {
   const int64_t blocks = (W * H + 255) / 256;
   return n_frames * blocks * (gauss ? 1150 : 550) > 8500000 + n_frames * waves * 3700 ? 4 : 0;   // picoseconds
 }
+
+// Numbers known per launch shape (kernel, threads, LDS bytes, device), for any
+// number of shapes (a program has as many as its actors' tap counts, branch
+// counts and tiles make), from any thread.
+class ShapeTable {
+ public:
+  // The shape's number; made by `make` when it is not known yet.
+  template <class Make>
+  int64_t get(const void *kernel, int threads, size_t lds_bytes, int device, Make make) {
+    std::lock_guard<std::mutex> lock(mu_);
+    const Key k{kernel, threads, lds_bytes, device};
+    const auto it = known_.find(k);
+    if (it != known_.end()) return it->second;
+    return known_[k] = make();
+  }
+
+ private:
+  typedef std::tuple<const void *, int, size_t, int> Key;
+  std::mutex mu_;
+  std::map<Key, int64_t> known_;
+};
 
 }  // namespace host
 }  // namespace dfh

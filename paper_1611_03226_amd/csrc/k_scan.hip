@@ -32,7 +32,6 @@
 // (popcount / highest bit of the ballot bits below its lane) and writes
 // off_b, prev_b (paths without a head pass that does it).
 #include <algorithm>
-#include <mutex>
 
 #include "host_logic.h"
 #include "scan_dev.h"
@@ -129,28 +128,16 @@ void scan_scratch_assign(ScanArgs &a, void *scratch, bool ordered) {
 }
 
 int64_t resident_blocks(const void *kernel, int threads, size_t lds_bytes) {
-  struct Entry {
-    const void *k;
-    int threads, dev;
-    size_t lds;
-    int64_t n;
-  };
-  static Entry cache[64];
-  static int used = 0;
-  static std::mutex mu;
+  static host::ShapeTable table;
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) dev = 0;
-  std::lock_guard<std::mutex> lock(mu);
-  for (int i = 0; i < used; ++i)
-    if (cache[i].k == kernel && cache[i].threads == threads && cache[i].lds == lds_bytes && cache[i].dev == dev)
-      return cache[i].n;
-  int per_cu = 0, ncu = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, lds_bytes) != hipSuccess || per_cu < 1)
-    per_cu = 1;
-  if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu < 1) ncu = 1;
-  const int64_t n = (int64_t)per_cu * ncu;
-  if (used < 64) cache[used++] = Entry{kernel, threads, dev, lds_bytes, n};
-  return n;
+  return table.get(kernel, threads, lds_bytes, dev, [&] {
+    int per_cu = 0, ncu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, lds_bytes) != hipSuccess || per_cu < 1)
+      per_cu = 1;
+    if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || ncu < 1) ncu = 1;
+    return (int64_t)per_cu * ncu;
+  });
 }
 
 hipError_t launch_scan(const ScanArgs &a, hipStream_t s, bool tables, bool zero_tickets) {

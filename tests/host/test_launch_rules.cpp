@@ -80,7 +80,23 @@ static void strips() {
   CHECK(strip_words(333, 251, 4, true) == 0 && strip_words(20, 20, 1000, true) == 1);
 }
 
+// Launch shapes: each asked for once, however many there are.
+static void shapes() {
+  ShapeTable t;
+  static char kernels[3];
+  int made = 0;
+  for (int pass = 0; pass < 2; ++pass)
+    for (int k = 0; k < 3; ++k)
+      for (int threads = 64; threads <= 256; threads += 64)
+        for (size_t lds = 0; lds < 400; ++lds)
+          for (int dev = 0; dev < 2; ++dev)
+            CHECK(t.get(kernels + k, threads, lds, dev, [&] { return ++made, (int64_t)(k + threads + lds) * 2 + dev; }) ==
+                  (int64_t)(k + threads + lds) * 2 + dev);
+  CHECK(made == 3 * 4 * 400 * 2);
+}
+
 int main() {
+  shapes();
   strips();
   tiles();
   motion();
