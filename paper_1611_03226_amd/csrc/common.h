@@ -378,6 +378,8 @@ hipError_t launch_dpd_small(const DpdArgs &a, const ScanArgs &c, hipStream_t s, 
 bool dpd_body_mx_env();
 hipError_t launch_dpd_body(const DpdArgs &a, hipStream_t s, int tile, int outputs_per_thread,
                            const KTiming *timing = nullptr);
+// The body of short firings (host::sample_wise): reads prev, not corr.
+hipError_t launch_dpd_samples(const DpdArgs &a, hipStream_t s, const KTiming *timing = nullptr);
 // Add delta to one counter (word 0 or 1 of a channel slot) and check the
 // channel's ring invariant.
 hipError_t launch_advance(int64_t *idx, int64_t delta, int32_t *err, hipStream_t s);

@@ -153,6 +153,39 @@ inline int strip_words(int64_t W, int64_t H, int64_t n_frames, bool gauss) {
   return n_frames * blocks * (gauss ? 1150 : 550) > 8500000 + n_frames * waves * 3700 ? 4 : 0;   // picoseconds
 }
 
+// Lanes of a firing's row in the head pass: 16 for the compiled tap counts (4,
+// 8, 16), else the fewest that hold the M - 1 outputs.
+inline bool compiled_taps(int M) { return M == 4 || M == 8 || M == 16; }
+inline int head_lanes(int M) { return compiled_taps(M) || (M > 9 && M <= 17) ? 16 : M <= 5 ? 4 : M <= 9 ? 8 : 32; }
+
+// Whether a batch of n firings (or rows) of r samples runs sample by sample
+// (k_dpd_samples) and not in tiles: rows without histories with any taps, the
+// rest where the taps are not compiled in (a compiled head pass adds its terms
+// in another form).
+// A tile costs 0.45 ns and 14.5 ps per coefficient however few of its 256
+// outputs a short firing fills, and firings with histories cost the head pass
+// 70 ps a lane (110 with the tables).  A sample costs 2 ps (6 with histories)
+// and 0.24 per coefficient, and where firings have histories its share of the
+// wavefront's corrections, 0.055 per term, of which one thread forms all of its
+// own (12 ns a term).  us of a call, samples / tiles:
+//   rows without control tokens, 10 branches of 12 taps: 100 of 16 20 / 26,
+//     30000 of 16 26 / 80, of 64 68 / 78, of 96 96 / 77; 100000 of 16 with 16
+//     taps 66 / 266
+//   rows of 100 firings, in all 30000 of 3 branches and 3 taps: of 8 26 / 33, of
+//     64 34 / 35, of 96 42 / 35; 200000 of 8 with 10 and 9 180 / 312
+//   a batch of 30000 with 3 and 3: of 2 42 / 60, of 48 67 / 67, of 96 88 / 73;
+//     with 6 and 12: of 16 94 / 113, of 32 134 / 116; 200000 of 16 408 / 592
+enum DpdBatch { kRows, kTokens, kBatch };    // stateless without and with control tokens, an actor's batch
+inline bool sample_wise(int64_t n, int64_t r, int M, int B, DpdBatch kind) {
+  if (compiled_taps(M) && kind != kRows) return false;
+  const int64_t N = n * r, tiles = n * ((r + 255) / 256), terms = (M - 1) * B * (B + 19) / 2;   // picoseconds below
+  if (kind == kRows) return N / 1000 * (2000 + 240 * M * B) < 6000000 + tiles * (450 + 29 * M * B / 2);
+  const int64_t each = 6000 + 240 * M * B + 55 * terms, tile = 450 + 29 * M * (B + 1) / 4;
+  if (kind == kTokens)
+    return 12000 * terms + N / 1000 * (each * 27 / 20) < 8000000 + tiles * tile + n * 70 * head_lanes(M);
+  return 12000 * terms + N / 1000 * (each * 11 / 10) + n * 120 + 5000000 < tiles * tile + n * 110 * head_lanes(M);
+}
+
 // Numbers known per launch shape (kernel, threads, LDS bytes, device), for any
 // number of shapes (a program has as many as its actors' tap counts, branch
 // counts and tiles make), from any thread.

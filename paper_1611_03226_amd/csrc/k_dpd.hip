@@ -478,9 +478,124 @@ static hipError_t launch_tiled(const DpdArgs &a0, hipStream_t s, int tile, const
   return hipGetLastError();
 }
 
-// Tap counts compiled into the head pass and the bodies; any other count
-// runs the kernels whose taps are a loop.
-static bool compiled_taps(int M) { return M == 4 || M == 8 || M == 16; }
+// ------------------------------------------------------------------ samples
+//
+// One thread per output sample, for batches of firings (or rows) so short that
+// a tile would leave most of its lanes idle, or so few that a launch counts
+// (host::sample_wise has the figures).  Bound by VALU issue, and
+// where firings are short by the corrections, which few lanes of a wavefront
+// form.  No head pass: a sample that reaches before
+// its firing forms its own correction.  Every sum is the tiled body's, in its
+// order (zeros before the firing's start included), so the batches that take
+// this kernel give the bits of those that do not.
+// ROWS: every firing has all B_const branches and none before it.
+template <bool ROWS>
+__device__ __forceinline__ float2 sample_output(const DpdArgs &a, int64_t Rx, int64_t g, int64_t i) {
+  const int M = a.M;
+  const uint32_t set = ROWS ? prefix_set(a.B_const) : (uint32_t)a.B[g];
+  const int B = ROWS ? a.B_const : set_len(set);
+  int Bw = B;                                            // largest Horner length of the wavefront
+  if constexpr (!ROWS) {
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) Bw = max(Bw, __shfl_xor(Bw, o));
+    Bw = __builtin_amdgcn_readfirstlane(Bw);
+  }
+  const cfloat2p h = as_const(a.h);
+  const int64_t at = Rx + g * a.r + i;
+  float ar = 0.f, ai = 0.f;
+  for (int m = 0; m < M; ++m) {
+    const float2 xv = i >= m ? a.x[(at - m) & a.x_mask] : make_float2(0.f, 0.f);
+    const float p = fmaf(xv.x, xv.x, xv.y * xv.y);
+    float Pr = 0.f, Pi = 0.f;
+    for (int b = Bw - 1; b >= 0; --b) {
+      const float2 c = ldc(h, b * M + m);
+      if constexpr (ROWS) {
+        Pr = b == B - 1 ? c.x : fmaf(Pr, p, c.x);
+        Pi = b == B - 1 ? c.y : fmaf(Pi, p, c.y);
+      } else {                                           // branches outside the set: zeros
+        const bool on = in_set(set, b);
+        const float cx = on ? c.x : 0.f, cy = on ? c.y : 0.f;
+        Pr = b >= B - 1 ? cx : fmaf(Pr, p, cx);
+        Pi = b >= B - 1 ? cy : fmaf(Pi, p, cy);
+      }
+    }
+    ar = fmaf(xv.x, Pr, ar);
+    ar = fmaf(-xv.y, Pi, ar);
+    ai = fmaf(xv.x, Pi, ai);
+    ai = fmaf(xv.y, Pr, ai);
+  }
+  if constexpr (!ROWS) {
+    if (i < M - 1 && set != 0u) {                        // the head correction, as the head pass forms it
+      float cr = 0.f, ci = 0.f;
+      for (int b = 0; b < B; ++b) {
+        if (!in_set(set, b)) continue;
+        const int64_t pf = prev_of(a, b, g);
+        float sr = 0.f, si = 0.f;
+        for (int m0 = 1; m0 < M; m0 += 4) {              // four terms' loads and powers at once
+          float2 xv[4];
+          float pp[4], pb[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            xv[j] = make_float2(0.f, 0.f);
+            if (m0 + j > i && m0 + j < M) xv[j] = hist_sample(a, Rx, b, g, pf, i - (m0 + j));
+            pp[j] = fmaf(xv[j].x, xv[j].x, xv[j].y * xv[j].y);
+            pb[j] = 1.f;
+          }
+          for (int e = 0; e < b; ++e)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) pb[j] *= pp[j];
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            if (m0 + j > i && m0 + j < M) {
+              const float vr = pb[j] * xv[j].x, vi = pb[j] * xv[j].y;
+              const float2 c = ldc(h, b * M + m0 + j);
+              sr = fmaf(c.x, vr, sr);
+              sr = fmaf(-c.y, vi, sr);
+              si = fmaf(c.x, vi, si);
+              si = fmaf(c.y, vr, si);
+            }
+        }
+        cr += sr;
+        ci += si;
+      }
+      ar += cr;
+      ai += ci;
+    }
+  }
+  return set ? make_float2(ar, ai) : make_float2(0.f, 0.f);   // (no branch: not 0 x infinity)
+}
+
+template <bool ROWS>
+__global__ __launch_bounds__(256) void k_dpd_samples(DpdArgs a) {
+  const int64_t Rx = a.x_idx ? as_const(a.x_idx)[0] : 0, Wy = a.y_idx ? as_const(a.y_idx)[1] : 0;
+  const int64_t total = a.n_firings * a.r, all = (total + 255) / 256 * 256;   // whole wavefronts
+  for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < all; t += (int64_t)gridDim.x * 256) {
+    const int64_t tc = t < total ? t : total - 1;
+    const int64_t g = total >> 32 ? tc / a.r : (int64_t)((uint32_t)tc / (uint32_t)a.r);
+    const float2 v = sample_output<ROWS>(a, Rx, g, tc - g * a.r);
+    if (t < total) a.y[(Wy + t) & a.y_mask] = v;
+  }
+  if (a.ticket && last_workgroup(a.ticket))
+    dpd_commit_block(a.commit, [&](int b) { return a.commit.last[b]; });
+}
+
+hipError_t launch_dpd_samples(const DpdArgs &a, hipStream_t s, const KTiming *t) {
+  if (a.n_firings <= 0) return hipSuccess;
+  if (a.M < 1 || a.M > kMaxTaps || a.order || (a.B && !a.prev)) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)std::min<int64_t>((a.n_firings * a.r + 255) / 256, host::kMaxThreads / 256));
+#define DF_SAMPLES(rows)                                                                              \
+  if (t)                                                                                              \
+    hipExtLaunchKernelGGL(k_dpd_samples<rows>, grid, dim3(256), 0, s, t->start, t->stop, 0, a);       \
+  else                                                                                                \
+    hipLaunchKernelGGL(k_dpd_samples<rows>, grid, dim3(256), 0, s, a);
+  if (a.B) {
+    DF_SAMPLES(false)
+  } else {
+    DF_SAMPLES(true)
+  }
+#undef DF_SAMPLES
+  return hipGetLastError();
+}
 
 template <int MT, int K, int BC, bool MASKED>
 static hipError_t launch_small(const DpdArgs &a0, const ScanArgs &c, hipStream_t s, int tile, const KTiming *t) {
@@ -512,7 +627,7 @@ hipError_t launch_dpd_heads(const DpdArgs &a, hipStream_t s) {
   if (a.ahead_blocks < 0 || (a.ahead_blocks && (!a.grp || a.ahead.n_segs != 1 || !a.ahead.grp || !a.ahead.ticket ||
                                                a.ahead_blocks != (scan_groups(1, a.ahead.seg_firings) + 3) / 4)))
     return hipErrorInvalidValue;
-  const int rl = compiled_taps(a.M) || (a.M > 9 && a.M <= 17) ? 16 : a.M <= 5 ? 4 : a.M <= 9 ? 8 : 32;
+  const int rl = host::head_lanes(a.M);
   const int nr = 64 / rl;                              // firings per workgroup
   // in pieces that a grid can hold beside the scan's workgroups
   const int64_t blocks = (a.n_firings + nr - 1) / nr, most = host::kMaxThreads / 512;

@@ -775,13 +775,15 @@ df_status dfh::dpd_enqueue(df_graph *g, Actor &a, int64_t n, bool may_run_ahead)
   Fifo &fy = g->fifos[a.ports[DF_DPD_OUT]];
   const int64_t r = a.dp.firing_size;
   const int bm = a.dp.n_branches_max, M = a.dp.n_taps;
+  const bool small = n <= 64 && !(g->body_mx && M == 16);   // one launch does it all
+  const bool samples = !small && host::sample_wise(n, r, M, bm, host::kBatch);   // no head pass
   // the head pass fills the prev/off tables from the group table, and places
   // the firings in processing order (grouped by Horner length).  That pays off
   // only for many workgroups with work enough to even out: the scan's length
   // table costs up to 20 us (us a pass, unordered / ordered: 30000 firings of
   // 40 samples 53 / 68 with one tap, 137 / 151 with 16; 8192 of 128 35 / 41
   // with three; 8192 of 511 86 / 92 with 8; 2000 of 1000 77 / 72 with 20).
-  const bool ordered = n > 64 && r > 512;
+  const bool ordered = n > 64 && r > 512 && !samples;
   const int64_t pos = fc.read_h;
 
   // this batch's scan: the one run ahead if it assumed this batch, else a new one
@@ -802,9 +804,8 @@ df_status dfh::dpd_enqueue(df_graph *g, Actor &a, int64_t n, bool may_run_ahead)
     a.ahead = -1;
   }
   Actor::ScanSlot &sl = a.scan[s];
-  const bool small = n <= 64 && !(g->body_mx && M == 16);   // one launch does it all
   if (!scanned && !small)
-    HIPCHK(g, launch_scan(scan_args(g, a, sl, pos, n, ordered, g->err_dev), g->stream, false, false));
+    HIPCHK(g, launch_scan(scan_args(g, a, sl, pos, n, ordered, g->err_dev), g->stream, samples, false));
   ScanArgs sa{};                                     // where the scan left its tables
   sa.n_segs = 1;
   sa.seg_firings = n;
@@ -845,14 +846,14 @@ df_status dfh::dpd_enqueue(df_graph *g, Actor &a, int64_t n, bool may_run_ahead)
   // (pushed before this batch): run by extra workgroups of the head pass into
   // the other slot (whose last readers, the previous batch's kernels, are
   // done), beside this batch's head corrections.
-  const bool run_ahead = may_run_ahead && !g->no_scan_ahead && n > 64 &&
+  const bool run_ahead = may_run_ahead && !g->no_scan_ahead && n > 64 && !samples &&
                          fc.write_lo - (pos + n) >= n;
   if (run_ahead) {
     const int t = s ^ 1;
     da.ahead = scan_args(g, a, a.scan[t], pos + n, n, ordered, a.scan[t].err);
     da.ahead_blocks = (int32_t)((scan_groups(1, n) + 3) / 4);
   }
-  if (!small) HIPCHK(g, launch_dpd_heads(da, g->stream));
+  if (!small && !samples) HIPCHK(g, launch_dpd_heads(da, g->stream));
   DpdCommitArgs ca{};
   ca.x = (const float2 *)fx.ring;
   ca.x_idx = fx.idx;
@@ -873,6 +874,8 @@ df_status dfh::dpd_enqueue(df_graph *g, Actor &a, int64_t n, bool may_run_ahead)
   if (small)
     HIPCHK(g, launch_dpd_small(da, scan_args(g, a, sl, pos, n, false, g->err_dev), g->stream, g->tile,
                                g->outputs_per_thread, g->prof ? &kt : nullptr));
+  else if (samples)
+    HIPCHK(g, launch_dpd_samples(da, g->stream, g->prof ? &kt : nullptr));
   else
     HIPCHK(g, launch_dpd_body(da, g->stream, g->tile, g->outputs_per_thread, g->prof ? &kt : nullptr));
 

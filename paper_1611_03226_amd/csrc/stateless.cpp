@@ -7,6 +7,7 @@
 
 #include "common.h"
 #include "dfhip.h"
+#include "host_logic.h"
 #include "runtime.h"
 
 using namespace dfh;
@@ -117,6 +118,7 @@ hipError_t dfh::dpd_forward_enqueue(const FwdScratch &sc, hipStream_t s, const v
     a.seg_firings = 1;
     a.n_firings = S;
     a.r = len;
+    if (!(a.mx && M == 16) && host::sample_wise(S, len, M, B_max, host::kRows)) return launch_dpd_samples(a, s);
     hipError_t e = launch_coef_rows(a.h, a.ht, B_max, M, s);
     if (e == hipSuccess) e = launch_dpd_body(a, s, 0, 0);
     return e;
@@ -146,6 +148,7 @@ hipError_t dfh::dpd_forward_enqueue(const FwdScratch &sc, hipStream_t s, const v
   a.seg_firings = nf;
   a.n_firings = n;
   a.r = r;
+  if (host::sample_wise(n, r, M, B_max, host::kTokens)) return launch_dpd_samples(a, s);
   e = launch_dpd_heads(a, s);
   if (e == hipSuccess) e = launch_dpd_body(a, s, 0, 0);
   return e;

@@ -95,7 +95,23 @@ static void shapes() {
   CHECK(made == 3 * 4 * 400 * 2);
 }
 
+// Sample by sample: never for compiled taps with histories, always for one-sample rows,
+// never for long firings in number; head rows hold the outputs.
+static void samples() {
+  for (int M = 1; M <= 32; ++M) {
+    CHECK(head_lanes(M) >= M - 1 && (compiled_taps(M) == (M == 4 || M == 8 || M == 16)));
+    for (int B = 1; B <= 16; ++B)
+      for (DpdBatch k : {kRows, kTokens, kBatch}) {
+        CHECK(!sample_wise(1 << 20, 4096, M, B, k));
+        if (k == kRows) CHECK(sample_wise(1ll << 33, 1, M, B, k) && sample_wise(1, 1, M, B, k));
+        else if (compiled_taps(M)) CHECK(!sample_wise(1 << 20, 1, M, B, k));
+        if (M <= 2) CHECK(sample_wise(1ll << 30, 2, M, B, k));
+      }
+  }
+}
+
 int main() {
+  samples();
   shapes();
   strips();
   tiles();
