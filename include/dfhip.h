@@ -375,7 +375,11 @@ df_status df_stream_dpd(df_graph *g, int32_t actor, const void *x_host,
  * workgroup work item (a multiple of 64*outputs_per_thread, at most
  * 512*outputs_per_thread), outputs_per_thread (4 or 8), and the persistent
  * kernel's workgroups per compute unit (1..16).  0 keeps the current value.
- * Used by the autotuner.  Errors: DF_EINVAL. */
+ * Until tile_outputs or outputs_per_thread is set, df_fire chooses the shape by
+ * the batch (2048 outputs with eight per thread for large batches of long
+ * firings, else 1024 with four); a value once set, by the autotuner too, stands
+ * for the graph's life.  The shape does not change results.
+ * Errors: DF_EINVAL. */
 df_status df_set_tile(df_graph *g, int32_t tile_outputs, int32_t outputs_per_thread,
                       int32_t blocks_per_cu);
 

@@ -95,7 +95,7 @@ hipError_t launch_hbm_ref(int mode, const void *src, void *dst, int64_t bytes, h
 //
 // Copy of a push or pop between device memory and a channel, with the counter
 // update, in place of a runtime copy and a kernel for the counter (64 firings
-// of 256 samples pushed, fired and popped: 36 us a pass before, 24 now; half
+// of 256 samples pushed, fired and popped: 37 us a pass before, 27 with it; half
 // of it was the host's part of the two calls).  HBM-bound where it is large:
 // one thread moves U 16-byte vectors, 4 KiB apart inside
 // the workgroup's span, all loads in flight before the first store; any byte

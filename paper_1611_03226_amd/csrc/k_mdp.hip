@@ -8,15 +8,15 @@
 // a batch is large enough): a work item is a strip of V words (4V pixels; V = 4
 // or 1) of kRun consecutive output rows of one frame; consecutive lanes take
 // consecutive strips, so every row load of a wave is one contiguous run.  The
-// last strip of a row ends at the row's last pixel and may overlap its neighbour (whose pixels it
-// rewrites with the same values); rows start at any byte, which the loads and
-// stores of words allow.  The vertical window slides down the item in
-// registers; the words left and right of the strip give the horizontal halo,
+// last strip of a row ends at the row's last pixel and may overlap its neighbour
+// (whose pixels it rewrites with the same values); rows start at any byte, which
+// the loads and stores of words allow.  The vertical window slides down the item
+// in registers; the words left and right of the strip give the horizontal halo,
 // with the nearest in-frame pixel repeated at the left and right frame edges.
-// Pixels are processed four per word in 16-bit lanes (md_swar.h).  The rest takes
-// the byte path: one thread per pixel (64 frames of 854x480: Gauss 121 us and Med 73 us by bytes, 22 and 21 us by strips;
-// 128 frames of 1000x600: 70 and 52 us with one word per strip, 60 and 45 with
-// four).
+// Pixels are processed four per word in 16-bit lanes (md_swar.h).  The rest
+// takes the byte path: one thread per pixel (64 frames of 854x480: Gauss 121 us
+// and Med 73 us by bytes, 22 and 21 us by strips; 128 frames of 1000x600: 70 and
+// 52 us with one word per strip, 60 and 45 with four).
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 

@@ -320,9 +320,9 @@ __device__ __forceinline__ void pers_head(const PersArgs &a, int64_t w) {
   if (head_live<M, 4>(B_of(row))) a.corr_all[(f0 + row) * (M - 1) + q] = make_float2(cr, ci);
 }
 
-// Tiles whose outputs pass through LDS on their way to memory (tile_store):
-// with 4096 outputs that buffer and the window would be more than the 64 KiB
-// of LDS a workgroup has without asking.
+// Outputs of a tile that pass through LDS on their way to memory (tile_store).
+// A 4096-output tile would need 69 KB with its window, two workgroups of a
+// compute unit's 160 KB instead of four; it stores directly.
 __host__ __device__ constexpr int staged_outputs(int tile) { return tile <= 2048 ? tile : 0; }
 
 // Persistent body: a grid-stride walk over the work items (run_tiles).
