@@ -56,3 +56,26 @@ def test_range_past_the_allocation_is_refused(pop):
     finally:
         hip.hipFree(buf)
     torch.cuda.synchronize()                             # and nothing is left to fail
+
+
+def test_push_and_pop_are_capturable():
+    """The buffer checks ask nothing that a stream capture forbids."""
+    import torch
+    from paper_1611_03226_amd import dfhip as D
+    from paper_1611_03226_amd.graph import Graph
+    say("push and pop under capture")
+    s = torch.cuda.Stream()
+    src = torch.arange(100, dtype=torch.int64, device="cuda")
+    dst = torch.zeros(100, dtype=torch.int64, device="cuda")
+    torch.cuda.synchronize()
+    with Graph(0, stream=s) as G:
+        f = G.fifo(D.DF_I64, 1, 128)
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            G.push(f, src)
+            assert G.pop(f, dst) == 100
+        assert int(dst.abs().sum()) == 0
+        with torch.cuda.stream(s):
+            g.replay()
+        G.sync()
+    assert torch.equal(src, dst)
