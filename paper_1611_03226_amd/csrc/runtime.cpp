@@ -10,6 +10,8 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <mutex>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -136,6 +138,69 @@ extern "C" df_status df_graph_create(df_graph **out, int device, void *stream) {
   return DF_OK;
 }
 
+// Page-locked words for motion actors' counts.  Pinning and unpinning memory
+// takes the host 50 and 220 us, more than the rest of an actor's life, so the
+// process keeps pages of 256 slots; a page that is empty is given back when
+// another still has room.  A slot is put back after its graph's stream has
+// finished.
+namespace {
+
+class CountsPool {
+ public:
+  MotionCounts *get() {
+    std::lock_guard<std::mutex> lock(mu_);
+    Page *p = pages_;
+    while (p && p->n_used == kSlots) p = p->next;
+    if (!p) {
+      p = new (std::nothrow) Page();
+      if (!p) return nullptr;
+      if (hipHostMalloc((void **)&p->slots, sizeof(MotionCounts) * kSlots, hipHostMallocPortable) != hipSuccess) {
+        delete p;
+        return nullptr;
+      }
+      p->next = pages_;
+      pages_ = p;
+    }
+    int i = 0;
+    while (p->used[i]) ++i;
+    p->used[i] = true;
+    ++p->n_used;
+    p->slots[i] = MotionCounts{};
+    return p->slots + i;
+  }
+  void put(MotionCounts *c) {
+    std::lock_guard<std::mutex> lock(mu_);
+    Page **at = &pages_;
+    while (*at && (c < (*at)->slots || c >= (*at)->slots + kSlots)) at = &(*at)->next;
+    Page *p = *at;
+    if (!p) return;
+    p->used[c - p->slots] = false;
+    if (--p->n_used) return;
+    for (Page *q = pages_; q; q = q->next)
+      if (q != p && q->n_used < kSlots) {
+        *at = p->next;
+        (void)hipHostFree(p->slots);
+        delete p;
+        return;
+      }
+  }
+
+ private:
+  static constexpr int kSlots = 256;
+  struct Page {
+    MotionCounts *slots = nullptr;
+    bool used[kSlots] = {};
+    int n_used = 0;
+    Page *next = nullptr;
+  };
+  std::mutex mu_;
+  Page *pages_ = nullptr;
+};
+
+CountsPool g_counts;                                   // its pages stay until the process ends
+
+}  // namespace
+
 static void free_actor(Actor &a) {
   (void)hipFree(a.block);
   (void)hipFree(a.order);
@@ -150,7 +215,7 @@ static void free_actor(Actor &a) {
   (void)hipFree(a.count);
   (void)hipFree(a.emit_off);
   (void)hipFree(a.bits);
-  if (a.counts) (void)hipHostFree(a.counts);
+  if (a.counts) g_counts.put(a.counts);
   a = Actor();
 }
 
@@ -429,9 +494,7 @@ extern "C" df_status df_actor_create(df_graph *g, df_actor_kind kind, const void
       return fail(g, DF_EINVAL, "min_changed_permille outside 0..1000");
     if (p.self_delay != 0 && p.self_delay != 1) return fail(g, DF_EINVAL, "self_delay must be 0 or 1");
     a.mp = p;
-    if ((e = hipHostMalloc((void **)&a.counts, sizeof(MotionCounts), hipHostMallocDefault)) != hipSuccess)
-      return fail(g, DF_ENOMEM, "actor allocation failed");
-    *a.counts = MotionCounts{};
+    if (!(a.counts = g_counts.get())) return fail(g, DF_ENOMEM, "actor allocation failed");
     if (p.self_delay) {
       const size_t wh = (size_t)p.width * p.height;
       if ((e = hipMalloc(&a.state, wh + kFrameSlack)) != hipSuccess) {

@@ -102,3 +102,35 @@ def test_batch_beyond_one_launch(self_delay):
     late = out[0][1] > lo
     assert np.array_equal(out[0][1][late], ref_i[ref_i > 0] + lo)
     assert np.array_equal(out[0][0][late], ref_m[ref_i > 0])
+
+
+def test_many_actors_share_the_page_locked_words():
+    """More motion actors than one page has words, some destroyed and made again
+    in between: every actor pops its own frames."""
+    from paper_1611_03226_amd.graph import Graph
+    say("300 motion actors")
+    W, H = 32, 6
+    f = _frames(5, W, H, 9)
+    ref = {n: omo.run_motion(f[:n], permille=0)[0] for n in range(1, 6)}
+    graphs = []
+
+    def make(k):
+        G = Graph(0)
+        chains = [G.motion_chain(W, H, permille=0, cap_in=8, cap_out=8) for _ in range(30)]
+        for i, mc in enumerate(chains):
+            n = 1 + (i + k) % 5
+            G.push(mc.cur, f[:n])
+            assert G.fire(mc.actor, n) == n
+        return G, chains, k
+
+    for k in range(10):
+        graphs.append(make(k))
+    for k in (1, 4, 8):
+        graphs[k][0].close()
+        graphs[k] = make(k + 2)
+    for G, chains, k in graphs:
+        for i, mc in enumerate(chains):
+            n, out = 1 + (i + k) % 5, np.zeros((8, H, W), np.uint8)
+            assert G.pop(mc.mask, out) == n
+            assert np.array_equal(out[:n], ref[n])
+        G.close()
