@@ -10,6 +10,7 @@
 
 #include <map>
 #include <mutex>
+#include <new>
 #include <tuple>
 
 namespace dfh {
@@ -198,7 +199,12 @@ class ShapeTable {
     const Key k{kernel, threads, lds_bytes, device};
     const auto it = known_.find(k);
     if (it != known_.end()) return it->second;
-    return known_[k] = make();
+    const int64_t n = make();
+    try {
+      known_[k] = n;
+    } catch (const std::bad_alloc &) {                   // not kept
+    }
+    return n;
   }
 
  private:
