@@ -472,6 +472,10 @@ __global__ __launch_bounds__(256) void k_mp_loss_any(MpArgs m) {
       const int64_t left = row_left(t0 + 256 * u, m.len, total);
       n[u] = left ? m.len - left : -1;
       v[u] = make_float2(0.f, 0.f);
+      if (left) {                                        // from -x on: e is often much smaller than v
+        const float2 xv = m.x[t0 + 256 * u];
+        v[u] = make_float2(-xv.x, -xv.y);
+      }
     }
     for (int q = 0; q < Q; ++q) {
 #pragma unroll
@@ -489,8 +493,6 @@ __global__ __launch_bounds__(256) void k_mp_loss_any(MpArgs m) {
     for (int u = 0; u < U; ++u) {
       const int64_t t = t0 + 256 * u;
       if (n[u] < 0) continue;
-      const float2 xv = m.x[t];
-      v[u] = make_float2(v[u].x - xv.x, v[u].y - xv.y);
       if (m.out) m.out[t] = v[u];
       part = fmaf(v[u].x, v[u].x, fmaf(v[u].y, v[u].y, part));
     }

@@ -157,3 +157,24 @@ def test_large_batches(K, Q, S, L):
     assert np.linalg.norm(err) <= TOL * np.linalg.norm(r)
     D.df_mp_input_adjoint(du, da, dg, du)                # in place of u, as a caller may
     assert torch.equal(du, Gp)
+
+
+@pytest.mark.parametrize("K,Q,S,L", [(1, 1, 3, 501), (4, 4, 5, 999), (4, 4, 700, 1003), (3, 6, 300, 2500)])
+def test_error_of_a_close_model(K, Q, S, L):
+    """With one real coefficient the error sample is one fused product onto -x:
+    its own rounding is 2^-24 of the sample, however much larger the two parts
+    are, and twice that leaves room for nothing at the parts' size."""
+    import torch
+    from paper_1611_03226_amd import dfhip as D
+    say(f"pa loss close K={K} Q={Q} {S}x{L}")
+    rng = np.random.default_rng(L)
+    a = np.zeros((K, Q), np.complex64)
+    a[0, 0] = np.float32(1) / np.float32(3)
+    u = complex_gaussian(rng, (S, L), rms=0.7).astype(np.complex64)
+    x = (u / 3 * (1 + 1e-3 * rng.standard_normal((S, L)))).astype(np.complex64)
+    e, loss = torch.zeros(S, L, dtype=torch.complex64, device="cuda"), torch.zeros((), device="cuda")
+    work = torch.empty(D.df_mp_loss_work_bytes(), dtype=torch.uint8, device="cuda")
+    D.df_mp_loss(_t(u), _t(a), _t(x), e, loss, work)
+    torch.cuda.synchronize()
+    ref = (u.astype(np.complex128) * np.float64(a[0, 0].real) - x).view(np.float64)
+    assert np.all(np.abs(e.cpu().numpy().view(np.float32) - ref) <= 2.0 ** -23 * np.abs(ref))
