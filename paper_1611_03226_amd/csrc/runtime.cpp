@@ -48,11 +48,14 @@ df_status dfh::fail_hip(df_graph *g, hipError_t e, const char *what) {
     if (e_ != hipSuccess) return fail_hip((g), e_, #expr); \
   } while (0)
 
+// A thread's device is set only where the process sees several: with one it
+// can be no other, and the call (0.07 us) is half of what the check of a
+// pushed or popped buffer takes (0.15 us).
 #define ENTER(g)                                                          \
   do {                                                                    \
     if (!(g)) return fail(nullptr, DF_EINVAL, "null graph");              \
     if ((g)->poisoned) return fail((g), DF_EDEVICE, "graph poisoned by an earlier HIP error"); \
-    hipError_t e0_ = hipSetDevice((g)->device);                           \
+    hipError_t e0_ = (g)->many_devices ? hipSetDevice((g)->device) : hipSuccess; \
     if (e0_ != hipSuccess) return fail_hip((g), e0_, "hipSetDevice");     \
   } while (0)
 
@@ -100,6 +103,7 @@ extern "C" df_status df_graph_create(df_graph **out, int device, void *stream) {
   df_graph *g = new (std::nothrow) df_graph();
   if (!g) return fail(nullptr, DF_ENOMEM, "host allocation failed");
   g->device = device;
+  g->many_devices = n > 1;
   if ((e = hipSetDevice(device)) != hipSuccess) {
     delete g;
     return fail(nullptr, DF_EDEVICE, "hipSetDevice: %s", hipGetErrorString(e));

@@ -95,6 +95,7 @@ struct Persistent;  // multi-instance batching state
 
 struct df_graph {
   int device = 0;
+  bool many_devices = false;         // the process sees other GPUs too
   hipStream_t stream = nullptr;
   hipStream_t copy_in = nullptr, copy_out = nullptr;  // host transfers of df_stream_dpd (created on first use)
   bool no_scan_ahead = false;        // DFHIP_SCAN_AHEAD=0: no scan of the next batch in the head pass
